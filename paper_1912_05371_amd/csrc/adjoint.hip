@@ -9,6 +9,7 @@
 #include <tuple>
 
 #include "resolve.h"
+#include "stage.h"
 #include "wacm_internal.h"
 
 namespace wacm {
@@ -21,7 +22,60 @@ void free_adj_plans(wacm_grid* g) {
   g->plan[1] = AdjPlan{};
 }
 
-// Every ghost point of the set (0: all ng layers, 1: depth-3 face star) of
+// Face-star plan, for the RK4 step's adjoint.  Same-level faces need no plan
+// (adj_stage_kernel reads the neighbours in place).  For each face next to
+// another level adj_face_kernel leaves in its slot of the face buffer, per
+// field, what the ghost values of that face return: next to a finer leaf one
+// value per ghost point, due to the coincident fine point; next to a coarser
+// one a value per point of the lattice box the prediction reads.  Rows are
+// the interior points that receive such values (field 0 element offset in the
+// compact layout), entries the positions in the face buffer, in order, so the
+// sums are fixed.  Kept on the host until the grid changes.
+constexpr int adj_face_stride(int bs) { return 3 * bs * bs; }  // per field and face
+
+static void build_face_plan(const wacm_grid* g, AdjPlan& pl) {
+  const int bs = g->d.bs, S = bs / 2 + 3, F = adj_face_stride(bs);
+  Layout L;
+  L.P = bs;
+  L.ng = 0;
+  L.fstride = (int64_t)bs * bs * bs;
+  L.bstride = 4 * L.fstride;
+  std::vector<std::pair<int64_t, int64_t>> ent;  // (receiving point, buffer position)
+  ent.reserve((size_t)g->n_cface * F);
+  int64_t k = 0;  // position in the list of faces next to another level (coarse_faces)
+  for (const Tab& t : g->h_tab)
+    for (int f = 0; f < 6; ++f) {
+      const int kind = t.kind[FACE_REGION[f]];
+      if (kind == 0) continue;
+      const int axis = f >> 1, side = f & 1, ua = axis == 0 ? 1 : 0, ub = axis == 2 ? 1 : 2;
+      const int n0 = kind > 0 ? (side ? bs : -1) : (side ? bs - 2 : -6);
+      const int dn = kind > 0 ? (side ? 1 : -1) : 2;
+      const int nn = kind > 0 ? 3 : (side ? 4 : 5), nt = kind > 0 ? bs : S;
+      for (int p = 0; p < nn * nt * nt; ++p) {
+        const int q = p % (nt * nt);
+        int li[3];
+        li[axis] = n0 + dn * (p / (nt * nt));
+        li[ua] = kind > 0 ? q % nt : 2 * (q % nt) - 2;
+        li[ub] = kind > 0 ? q / nt : 2 * (q / nt) - 2;
+        ent.emplace_back(point_offset(t, bs, L, li[0], li[1], li[2]), 4 * F * k + p);
+      }
+      ++k;
+    }
+  std::sort(ent.begin(), ent.end());
+  pl.h_src.reserve(ent.size());
+  for (size_t e = 0; e < ent.size(); ++e) {
+    if (e == 0 || ent[e].first != ent[e - 1].first) {
+      pl.h_dst.push_back(ent[e].first);
+      pl.h_ptr.push_back((int64_t)e);
+    }
+    pl.h_src.push_back(ent[e].second);
+  }
+  pl.h_ptr.push_back((int64_t)ent.size());
+  pl.nrows = (int64_t)pl.h_dst.size();
+  pl.nnz = (int64_t)pl.h_src.size();
+}
+
+// Full plan (all ng layers), for wacm_sync_ghosts_adj: every ghost point of
 // every active block, with the interior points its value was taken from:
 // rows are the source interior points, entries the ghost points that read
 // them with their prediction weights, sorted so the gather is deterministic.
@@ -31,13 +85,19 @@ int build_adj_plan(wacm_grid* g, int face_only, std::string& err) {
   AdjPlan& pl = g->plan[face_only ? 1 : 0];
   if (pl.built || !pl.h_ptr.empty()) return WACM_OK;
   (void)err;
+  AdjPlan np;
+  if (face_only) {
+    build_face_plan(g, np);
+    pl = std::move(np);
+    return WACM_OK;
+  }
   const int bs = g->d.bs, ng = g->d.ng, P = g->P;
   Layout L;
   L.P = P;
   L.ng = ng;
   L.fstride = (int64_t)P * P * P;
   L.bstride = 4 * L.fstride;
-  const int npts = face_only ? 18 * bs * bs : P * P * P - bs * bs * bs;
+  const int npts = P * P * P - bs * bs * bs;
   std::vector<std::tuple<int64_t, int64_t, double>> ent;
   std::vector<int64_t> ghosts;
   ghosts.reserve((size_t)g->nb * npts);
@@ -47,7 +107,7 @@ int build_adj_plan(wacm_grid* g, int face_only, std::string& err) {
     const int64_t base = (int64_t)t.meta[0] * L.bstride;
     for (int p = 0; p < npts; ++p) {
       int i, j, k;
-      shell_point(p, bs, ng, P, face_only ? 1 : 0, i, j, k);
+      shell_point(p, bs, ng, P, 0, i, j, k);
       const int64_t go = base + ((int64_t)(k + ng) * P + (j + ng)) * P + (i + ng);
       ghosts.push_back(go);
       ghost_taps<double>(t, bs, L, i, j, k,
@@ -55,7 +115,6 @@ int build_adj_plan(wacm_grid* g, int face_only, std::string& err) {
     }
   }
   std::sort(ent.begin(), ent.end());
-  AdjPlan np;
   np.h_src.reserve(ent.size());
   np.h_w.reserve(ent.size());
   for (size_t e = 0; e < ent.size(); ++e) {
@@ -77,7 +136,8 @@ int build_adj_plan(wacm_grid* g, int face_only, std::string& err) {
 
 static size_t up256(size_t v) { return (v + 255) / 256 * 256; }
 
-// device bytes of a plan: dst, ptr, src, w, ghost, each 256-byte aligned
+// device bytes of a plan: dst, ptr, src, w, ghost, each 256-byte aligned (the
+// face-star plan has no weights and no ghost list)
 size_t adj_plan_bytes(const AdjPlan& p) {
   return up256(8 * p.h_dst.size()) + up256(8 * p.h_ptr.size()) + up256(8 * p.h_src.size()) +
          up256(8 * p.h_w.size()) + up256(8 * p.h_ghost.size());
@@ -196,6 +256,7 @@ __global__ __launch_bounds__(NT_GEN) void rhs_adj_kernel(AdjArgs<T> a) {
     auto inside = [&](int i, int j, int k) {
       return i >= 0 && i < bs && j >= 0 && j < bs && k >= 0 && k < bs;
     };
+    const PlateAdjTime pm = plate_adj_time(p, a.t);
     double th[3] = {0, 0, 0};
     for (int pt = threadIdx.x; pt < n3 + nf; pt += blockDim.x) {
       int q[3];
@@ -268,10 +329,9 @@ __global__ __launch_bounds__(NT_GEN) void rhs_adj_kernel(AdjArgs<T> a) {
         }
         if (p.mask) {
           const int qi = (q[2] * bs + q[1]) * bs + q[0];
-          double chi, dchi = 0.0, us[3], dsd[3] = {0, 0, 0}, dal[3] = {0, 0, 0},
-                      dad[3] = {0, 0, 0};
+          double chi, dchi = 0.0, us[3], dsd[3] = {0, 0, 0};
           if (p.mask == WACM_MASK_PLATE)
-            plate_eval_adj(p, a.t, xg, yg, zg, chi, dchi, us, dsd, dal, dad);
+            plate_adj_point(p, pm, xg, yg, zg, chi, dchi, us, dsd);
           else
             mask_eval(p, a.t, xg, yg, zg, chi, us);
           double gal = 0.0, gad = 0.0;
@@ -283,7 +343,7 @@ __global__ __launch_bounds__(NT_GEN) void rhs_adj_kernel(AdjArgs<T> a) {
             gal += -dchi / p.c_eta * ((double)u[c] - us[c] - e) * (double)v[c];
             gad += chi / p.c_eta * dsd[c] * (double)v[c];
           }
-          for (int k2 = 0; k2 < 3; ++k2) th[k2] += gal * dal[k2] + gad * dad[k2];
+          for (int k2 = 0; k2 < 3; ++k2) th[k2] += gal * pm.dal[k2] + gad * pm.dad[k2];
         }
       }
       for (int c = 0; c < 4; ++c) B[oj + c * fs] += acc[c];
@@ -308,6 +368,7 @@ __global__ __launch_bounds__(NT_GEN) void force_adj_kernel(AdjArgs<T> a) {
   const int bs = a.bs, ng = a.L.ng, P = a.L.P;
   const int n3 = bs * bs * bs;
   const wacm_params& p = a.p;
+  const PlateAdjTime pm = plate_adj_time(p, a.t);
   for (int64_t ib = blockIdx.x; ib < a.nb; ib += gridDim.x) {
     const int32_t* m = a.tab[ib].meta;
     const int slot = m[0], J = m[1];
@@ -315,14 +376,23 @@ __global__ __launch_bounds__(NT_GEN) void force_adj_kernel(AdjArgs<T> a) {
     const double vol = h * h * h;
     const int64_t base = (int64_t)slot * a.L.bstride;
     double th[3] = {0, 0, 0};
+    // where the mask vanishes at time t on the whole block every term is 0;
+    // 0 times a value that is not finite is not
+    wacm_params pq = p;
+    pq.sponge = 0;
+    const bool far = pen_far(pq, a.Ldom, bs, m, pitch_window(p, a.t, a.t));
     for (int qi = threadIdx.x; qi < n3; qi += blockDim.x) {
       const int i = qi % bs, j = (qi / bs) % bs, k = qi / (bs * bs);
       const int64_t o = base + ((int64_t)(k + ng) * P + (j + ng)) * P + (i + ng);
+      if (far) {
+        for (int k2 = 0; k2 < 3; ++k2) th[k2] += 0.0 * (double)a.U[o];
+        continue;
+      }
       const double xg = (double)(m[2] * bs + i) * h, yg = (double)(m[3] * bs + j) * h,
                    zg = (double)(m[4] * bs + k) * h;
-      double chi, dchi = 0.0, us[3], dsd[3] = {0, 0, 0}, dal[3] = {0, 0, 0}, dad[3] = {0, 0, 0};
+      double chi, dchi = 0.0, us[3], dsd[3] = {0, 0, 0};
       if (p.mask == WACM_MASK_PLATE)
-        plate_eval_adj(p, a.t, xg, yg, zg, chi, dchi, us, dsd, dal, dad);
+        plate_adj_point(p, pm, xg, yg, zg, chi, dchi, us, dsd);
       else
         mask_eval(p, a.t, xg, yg, zg, chi, us);
       const double cw = a.weight * chi * vol / p.c_eta;
@@ -331,7 +401,7 @@ __global__ __launch_bounds__(NT_GEN) void force_adj_kernel(AdjArgs<T> a) {
       const double e = a.dus ? (double)a.dus[((int64_t)slot * 3) * n3 + qi] : 0.0;
       const double gal = a.weight * dchi * ((double)a.U[o] - us[0] - e) * vol / p.c_eta;
       const double gad = -cw * dsd[0];
-      for (int k2 = 0; k2 < 3; ++k2) th[k2] += gal * dal[k2] + gad * dad[k2];
+      for (int k2 = 0; k2 < 3; ++k2) th[k2] += gal * pm.dal[k2] + gad * pm.dad[k2];
     }
     __syncthreads();
     for (int k2 = 0; k2 < 3; ++k2) red[k2][threadIdx.x] = th[k2];
@@ -365,34 +435,487 @@ __global__ __launch_bounds__(NT_GEN) void theta_finalize(const double* __restric
 }
 
 // --------------------------------------------------------------------------
-// elementwise helpers on pool-layout registers
+// one RK stage of the adjoint step
 // --------------------------------------------------------------------------
-// Y = a X + b Z on the interior points of every active block (X, Z may be null)
+// B = S^T J_rhs(U)^T kb, with kb the rhs adjoint of the stage, U its
+// synchronised input and S^T the transpose of the ghost fill.  The stencils of
+// the rhs transpose are the forward ones applied to kb and to the products
+// kb_c u_d; next to a same-level block the ghost values it returns to that
+// block are what these stencils give when kb and u are read across the face,
+// so same-level faces need no ghost layers at all.  Next to another level kb
+// counts as 0 outside the block; what the block returns across such a face is
+// formed by adj_face_kernel and added by adj_gather_kernel.
 template <typename T>
-__global__ __launch_bounds__(NT_GEN) void axpby_interior(const Tab* __restrict__ tab, int64_t nb,
-                                                         Layout L, int bs, T* Y, double a,
-                                                         const T* X, double b, const T* Z) {
-  const int n3 = bs * bs * bs;
-  for (int64_t ib = blockIdx.x; ib < nb; ib += gridDim.x) {
-    const int64_t base = (int64_t)tab[ib].meta[0] * L.bstride;
-    for (int q = threadIdx.x; q < 4 * n3; q += blockDim.x) {
-      const int c = q / n3, r = q - c * n3;
-      const int i = r % bs, j = (r / bs) % bs, k = r / (bs * bs);
-      const int64_t o = base + c * L.fstride + ((int64_t)(k + L.ng) * L.P + (j + L.ng)) * L.P +
-                        (i + L.ng);
-      T v = T(0);
-      if (X) v += T(a) * X[o];
-      if (Z) v += T(b) * Z[o];
-      Y[o] = v;
+struct AdjStage {
+  const Tab* tab;
+  int64_t nb;
+  const T* u;  // stage input: the pool, or x-split
+  Layout Lu;
+  const T* hb;  // its face halos next to other levels [slot][6][4][3][bs][bs]
+  const T* v;   // rhs adjoint kb = vs v
+  Layout Lv;
+  T vs;
+  const T* lam;  // adjoint of the step's output (pool layout)
+  Layout Lp;
+  const T* sin;  // running sum lam + B_4 + ..., in and out
+  Layout Lsi;
+  T* sout;
+  Layout Lso;
+  T* kn;  // next rhs adjoint = lamw lam + kw B (compact), null at the last stage
+  Layout Lc;
+  T lamw, kw;
+  double Ldom, t;
+  wacm_params p;
+  const T* dus;    // [slot][3][bs^3] or null
+  double* dusbar;  // [slot][3][bs^3] or null (accumulated, FP64)
+  double* part;    // theta partials, 3 per work item
+};
+
+// Element offset (field 0) of a block's interior point in a register.
+__device__ __forceinline__ int64_t point_in(const Layout& L, int bs, int slot, int i, int j,
+                                            int k) {
+  return (int64_t)slot * L.bstride +
+         (L.xs ? (int64_t)xsplit_offset(bs, i, j, k)
+               : ((int64_t)(k + L.ng) * L.P + (j + L.ng)) * L.P + (i + L.ng));
+}
+
+// Bound: memory (24 values per point).  Same scheme as the forward stage
+// kernel: work items are tiles of TY rows of a block (TY = BS = 16: the whole
+// block), one thread per column marching in z, the planes of kb (4 fields) and
+// u (3) in a double-buffered LDS slab, their z neighbours in registers, one
+// LDS barrier per plane, the next plane's loads issued before it.  It replaces
+// per stage a clear of a whole pool, the point-wise gather of 18 neighbours,
+// a gather over every ghost entry, a second clear and two combination passes
+// (1632 blocks of 16^3, FP32: 2.9 -> 0.84 ms).
+// The plate's terms are evaluated only in blocks where the mask does not
+// vanish (pen_far); elsewhere they are exactly 0.
+template <typename T, int BS, int TY>
+__global__ __launch_bounds__(BS* TY) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 2 : 3)))
+void adj_stage_kernel(AdjStage<T> a) {
+  constexpr int H = 3, W = BS + 2 * H, WY = TY + 2 * H, NT = BS * TY, NTY = BS / TY;
+  constexpr int NH = 6 * TY + 6 * BS, B3 = BS * BS * BS;
+  static_assert(NH <= NT, "one halo point per thread and plane");
+  __shared__ T slab[2][7][W * WY];  // kb_u, kb_v, kb_w, kb_p, u, v, w
+  __shared__ FaceDesc<T> fu[6], fv[6];
+  __shared__ int32_t meta[6];
+  __shared__ double red[3][NT / 64];
+  const int tid = threadIdx.x, x = tid % BS, yl = tid / BS;
+  const wacm_params& p = a.p;
+  const T am[3] = {T(TW1), T(TW2), T(TW3)};
+  const T c2a = T(D2A), c2b = T(D2B), c2c = T(D2C);
+  const T nu = T(p.nu), c0sq = T(p.c0 * p.c0), cg = T(p.c_gamma), vs = a.vs;
+  const bool xin = a.Lu.xs != 0;
+  const int cidx = (yl + H) * W + (x + H);
+  const PlateAdjTime pm = plate_adj_time(p, a.t);
+  // this thread's halo point of every plane: x faces of the tile's rows, then
+  // the 3 rows below and above the tile
+  const bool hthr = tid < NH;
+  int hkind = 0, hd = 0, hs = 0, hli = 0;
+  if (tid < 6 * TY) {
+    hkind = tid / (3 * TY);
+    const int rem = tid - hkind * 3 * TY;
+    hd = rem / TY;
+    hs = rem - hd * TY;
+    hli = (hs + H) * W + ((hkind == 0 ? -1 - hd : BS + hd) + H);
+  } else if (hthr) {
+    const int q = tid - 6 * TY;
+    hkind = 2 + q / (3 * BS);
+    const int rem = q - (hkind - 2) * 3 * BS;
+    hd = rem / BS;
+    hs = rem - hd * BS;
+    hli = ((hkind == 2 ? -1 - hd : TY + hd) + H) * W + (hs + H);
+  }
+  const int64_t nitems = a.nb * NTY;
+  BlockIter it(nitems, 1);
+  for (; it.ib < it.end; it.ib += it.step) {
+    const int64_t item = it.ib, ibk = item / NTY;
+    const int y0 = (int)(item - ibk * NTY) * TY, y = y0 + yl;
+    __syncthreads();
+    if (tid < 6) {
+      const Tab& tb = a.tab[ibk];
+      fu[tid] = face_desc<T, BS, HALO_NB>(tb, a.u, a.Lu, a.hb, tid, xin);
+      fv[tid] = face_desc<T, BS, HALO_NB>(tb, a.v, a.Lv, nullptr, tid, false);
+      const int r = tid == 0 ? 12 : (tid == 1 ? 14 : (tid == 2 ? 10 : (tid == 3 ? 16 : (tid == 4 ? 4 : 22))));
+      if (tb.kind[r] != 0) fv[tid].ptr = nullptr;
+    }
+    if (tid < 5) meta[tid] = a.tab[ibk].meta[tid];
+    if (tid == 5) {
+      wacm_params pq = p;
+      pq.sponge = 0;
+      meta[5] = p.mask && !pen_far(pq, a.Ldom, BS, a.tab[ibk].meta, pitch_window(p, a.t, a.t));
+    }
+    __syncthreads();
+    const int slot = __builtin_amdgcn_readfirstlane(meta[0]);
+    const int J = __builtin_amdgcn_readfirstlane(meta[1]);
+    const bool masked = __builtin_amdgcn_readfirstlane(meta[5]) != 0;
+    const double h = a.Ldom / (double(int64_t(1) << J) * BS);
+    const T ih = T(1.0 / h), ih2 = T(1.0 / (h * h));
+    const int ufs = (int)a.Lu.fstride, vfs = (int)a.Lv.fstride;
+    const int ucol = xin ? xsplit_offset(BS, x, y, 0)
+                         : (a.Lu.ng * a.Lu.P + (y + a.Lu.ng)) * a.Lu.P + (x + a.Lu.ng);
+    const int uzs = xin ? xsplit_zstride(BS, x) : a.Lu.P * a.Lu.P;
+    const int vzs = a.Lv.P * a.Lv.P;
+    const T* __restrict__ ub = a.u + (int64_t)slot * a.Lu.bstride + ucol;
+    const int vcol = (a.Lv.ng * a.Lv.P + (y + a.Lv.ng)) * a.Lv.P + (x + a.Lv.ng);
+    const T* __restrict__ vb = a.v + (int64_t)slot * a.Lv.bstride + vcol;
+    // pointwise operands: uniform block origins, this thread's column offsets
+    // and plane steps in the pool (lam) and in a compact register
+    const T* lb = a.lam + (int64_t)slot * a.Lp.bstride;
+    const T* sib = a.sin + (int64_t)slot * a.Lsi.bstride;
+    T* sob = a.sout + (int64_t)slot * a.Lso.bstride;
+    T* kob = a.kn + (int64_t)slot * a.Lc.bstride;
+    const int pcol = (a.Lp.ng * a.Lp.P + (y + a.Lp.ng)) * a.Lp.P + (x + a.Lp.ng);
+    const int ccol = y * BS + x;
+    const int sicol = a.Lsi.ng ? pcol : ccol, socol = a.Lso.ng ? pcol : ccol;
+    // values of this thread's column at depth d below (f = 4) or above (f = 5)
+    auto zu = [&](int f, int d, int c) -> T {
+      const FaceDesc<T>& fz = fu[f];
+      if (fz.mode == 1) return fz.ptr[c * ufs + ucol + (f == 4 ? BS - 1 - d : d) * uzs];
+      return fz.ptr[c * fz.fs + d * fz.sd + x * fz.s0 + y * fz.s1];
+    };
+    auto zv = [&](int f, int d, int c) -> T {
+      const FaceDesc<T>& fz = fv[f];
+      return fz.ptr ? vs * fz.ptr[c * fz.fs + d * fz.sd + x * fz.s0 + y * fz.s1] : T(0);
+    };
+    // this thread's halo point as an affine map in z: ptr[c fs + z zs]
+    const T *hu = nullptr, *hv = nullptr;
+    int hufs = 0, huzs = 0, hvfs = 0, hvzs = 0;
+    if (hthr) {
+      const int hy = hkind < 2 ? y0 + hs : (hkind == 2 ? y0 - 1 - hd : y0 + TY + hd);
+      if (hkind < 2 || hy < 0 || hy >= BS) {
+        const int f = hkind < 2 ? hkind : (hy < 0 ? 2 : 3);
+        const int d = hkind < 2 ? hd : (hy < 0 ? -1 - hy : hy - BS), s = hkind < 2 ? hy : hs;
+        const FaceDesc<T>& f1 = fu[f];
+        if (f1.mode == 1) {
+          hu = f1.ptr + xsplit_offset(BS, hs, hy < 0 ? BS + hy : hy - BS, 0);
+          hufs = ufs;
+          huzs = xsplit_zstride(BS, hs);
+        } else {
+          hu = f1.ptr + d * f1.sd + s * f1.s0;
+          hufs = f1.fs;
+          huzs = f1.s1;
+        }
+        const FaceDesc<T>& f2 = fv[f];
+        if (f2.ptr) hv = f2.ptr + d * f2.sd + s * f2.s0;
+        hvfs = f2.fs;
+        hvzs = f2.s1;
+      } else {  // a row of the block's other tiles
+        hu = a.u + point_in(a.Lu, BS, slot, hs, hy, 0);
+        hufs = ufs;
+        huzs = xin ? xsplit_zstride(BS, hs) : a.Lu.P * a.Lu.P;
+        hv = a.v + point_in(a.Lv, BS, slot, hs, hy, 0);
+        hvfs = vfs;
+        hvzs = vzs;
+      }
+    }
+    T q[7][7];  // column values at z - 3 .. z + 3: kb (4), u (3)
+#pragma unroll
+    for (int mm = 0; mm < 7; ++mm) {
+      const int z = mm - 3;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) q[c][mm] = z < 0 ? zv(4, -1 - z, c) : vs * vb[c * vfs + z * vzs];
+#pragma unroll
+      for (int c = 0; c < 3; ++c) q[4 + c][mm] = z < 0 ? zu(4, -1 - z, c) : ub[c * ufs + z * uzs];
+    }
+#pragma unroll
+    for (int c = 0; c < 7; ++c) slab[0][c][cidx] = q[c][3];
+    if (hthr) {
+#pragma unroll
+      for (int c = 0; c < 4; ++c) slab[0][c][hli] = hv ? vs * hv[c * hvfs] : T(0);
+#pragma unroll
+      for (int c = 0; c < 3; ++c) slab[0][4 + c][hli] = hu[c * hufs];
+    }
+    double th[3] = {0, 0, 0};
+#pragma unroll 1
+    for (int z = 0; z < BS; ++z) {
+      T(*sb)[W * WY] = slab[z & 1];
+      T nq[7], hn[7];
+      if (z + 1 < BS) {
+        const int zz = z + 4;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) nq[c] = zz < BS ? vs * vb[c * vfs + zz * vzs] : zv(5, zz - BS, c);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) nq[4 + c] = zz < BS ? ub[c * ufs + zz * uzs] : zu(5, zz - BS, c);
+        if (hthr) {
+#pragma unroll
+          for (int c = 0; c < 4; ++c) hn[c] = hv ? vs * hv[c * hvfs + (z + 1) * hvzs] : T(0);
+#pragma unroll
+          for (int c = 0; c < 3; ++c) hn[4 + c] = hu[c * hufs + (z + 1) * huzs];
+        }
+      }
+      lds_barrier();
+      const T v[4] = {q[0][3], q[1][3], q[2][3], q[3][3]};
+      T acc[4] = {T(0), T(0), T(0), T(0)};
+#pragma unroll
+      for (int d = 0; d < 3; ++d) {
+        const int st = d == 0 ? 1 : W;
+        auto at = [&](int c, int o) -> T { return d == 2 ? q[c][3 + o] : sb[c][cidx + o * st]; };
+        T up[3], um[3];  // u_d at +m, -m
+#pragma unroll
+        for (int m = 0; m < 3; ++m) {
+          up[m] = at(4 + d, m + 1);
+          um[m] = at(4 + d, -1 - m);
+        }
+        T dv = T(0);  // D1_d kb_d
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+          T pr = T(0), lap = c2c * v[c], du = T(0);
+#pragma unroll
+          for (int m = 0; m < 3; ++m) {
+            const T vp = at(c, m + 1), vm = at(c, -1 - m);
+            pr += am[m] * (vp * up[m] - vm * um[m]);
+            if (m < 2) lap += (m == 0 ? c2b : c2a) * (vp + vm);
+            if (c == d) dv += am[m] * (vp - vm);
+            du += am[m] * (c == d ? up[m] - um[m] : at(4 + c, m + 1) - at(4 + c, -1 - m));
+          }
+          acc[c] += ih * pr + (nu * ih2) * lap;
+          acc[d] -= v[c] * (ih * du);
+          // keep the LDS reads of a field with its arithmetic (hoisted
+          // together they spill)
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        T dp = T(0);
+#pragma unroll
+        for (int m = 0; m < 3; ++m) dp += am[m] * (at(3, m + 1) - at(3, -1 - m));
+        acc[d] += c0sq * (ih * dp);
+        acc[3] += ih * dv;
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      acc[3] -= cg * v[3];
+      const int qi = (z * BS + y) * BS + x;
+      if (p.sponge || masked) {
+        const double xg = (double)(meta[2] * BS + x) * h, yg = (double)(meta[3] * BS + y) * h,
+                     zg = (double)(meta[4] * BS + z) * h;
+        if (p.sponge) {
+          const T sp = T(sponge_eval(p, a.Ldom, xg, yg, zg) / p.c_sp);
+#pragma unroll
+          for (int c = 0; c < 4; ++c) acc[c] -= sp * v[c];
+        }
+        if (masked) {
+          double chi, dchi = 0.0, us[3], dsd[3] = {0, 0, 0};
+          if (p.mask == WACM_MASK_PLATE)
+            plate_adj_point(p, pm, xg, yg, zg, chi, dchi, us, dsd);
+          else
+            mask_eval(p, a.t, xg, yg, zg, chi, us);
+          double gal = 0.0, gad = 0.0;
+#pragma unroll
+          for (int c = 0; c < 3; ++c) {
+            const int64_t o = ((int64_t)slot * 3 + c) * B3 + qi;
+            acc[c] -= T(chi / p.c_eta) * v[c];
+            if (a.dusbar) a.dusbar[o] += chi / p.c_eta * (double)v[c];
+            const double e = a.dus ? (double)a.dus[o] : 0.0;
+            gal += -dchi / p.c_eta * ((double)q[4 + c][3] - us[c] - e) * (double)v[c];
+            gad += chi / p.c_eta * dsd[c] * (double)v[c];
+          }
+#pragma unroll
+          for (int k = 0; k < 3; ++k) th[k] += gal * pm.dal[k] + gad * pm.dad[k];
+        }
+      }
+      if (p.mask && !masked) {
+        // 0 times a value that is not finite is not 0
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+          th[c] += 0.0 * (double)v[c];
+          if (a.dusbar && !isfinite(v[c])) a.dusbar[((int64_t)slot * 3 + c) * B3 + qi] += 0.0 * v[c];
+        }
+      }
+      {
+        const int lo = pcol + z * a.Lp.P * a.Lp.P, co = ccol + z * BS * BS;
+        const int sio = sicol + z * a.Lsi.P * a.Lsi.P, soo = socol + z * a.Lso.P * a.Lso.P;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          sob[soo + c * (int)a.Lso.fstride] = sib[sio + c * (int)a.Lsi.fstride] + acc[c];
+          if (a.kn) kob[co + c * B3] = a.lamw * lb[lo + c * (int)a.Lp.fstride] + a.kw * acc[c];
+        }
+      }
+      if (z + 1 < BS) {
+        T(*nb_)[W * WY] = slab[(z + 1) & 1];
+#pragma unroll
+        for (int c = 0; c < 7; ++c) nb_[c][cidx] = q[c][4];
+        if (hthr) {
+#pragma unroll
+          for (int c = 0; c < 7; ++c) nb_[c][hli] = hn[c];
+        }
+#pragma unroll
+        for (int c = 0; c < 7; ++c) {
+#pragma unroll
+          for (int mm = 0; mm < 6; ++mm) q[c][mm] = q[c][mm + 1];
+          q[c][6] = nq[c];
+        }
+      }
+    }
+    if (p.mask) {
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        double s = th[k];
+        for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+        if ((tid & 63) == 0) red[k][tid >> 6] = s;
+      }
+      __syncthreads();
+      if (tid < 3) {
+        double s = red[tid][0];
+        for (int w = 1; w < NT / 64; ++w) s += red[tid][w];
+        a.part[item * 3 + tid] = s;
+      }
     }
   }
 }
 
+// What a block returns across its faces next to another level: the rhs
+// transpose at the 3 ghost layers of the face, which only the 3 interior
+// layers next to it reach, along the normal.  Next to a coarser leaf the
+// transpose of the prediction takes these values to the lattice box the
+// forward fill reads, one axis at a time (t1, t0, normal) through LDS, in
+// FP64; next to a finer leaf they go to the coincident fine points as they
+// are.  One work item per face of the list, results in its slot of fb.
+template <typename T, int BS>
+__global__ __launch_bounds__(NT_GEN) void adj_face_kernel(const Tab* __restrict__ tab,
+                                                          const int32_t* __restrict__ cf,
+                                                          int64_t n, AdjStage<T> a,
+                                                          double* __restrict__ fb) {
+  constexpr int B2 = BS * BS, S = BS / 2 + 3, F = adj_face_stride(BS);
+  constexpr int PER = (B2 + NT_GEN - 1) / NT_GEN;
+  __shared__ double gb[3 * B2];      // ghost values of one field [d][t1][t0]
+  __shared__ double pb[3 * S * BS];  // after t1
+  __shared__ double pa[3 * S * S];   // after t0
+  constexpr double W4[4] = {DDW0, DDW1, DDW1, DDW0};
+  const int tid = threadIdx.x;
+  const T am[3] = {T(TW1), T(TW2), T(TW3)};
+  const T w2[3] = {T(D2C), T(D2B), T(D2A)};
+  const T nu = T(a.p.nu), c0sq = T(a.p.c0 * a.p.c0);
+  for (int64_t wk = blockIdx.x; wk < n; wk += gridDim.x) {
+    const Tab& tb = tab[cf[2 * wk]];
+    const int f = cf[2 * wk + 1], axis = f >> 1, side = f & 1;
+    const int ua = axis == 0 ? 1 : 0, ub = axis == 2 ? 1 : 2;
+    const int r = (axis == 0 ? 2 * side : 1) + 3 * (axis == 1 ? 2 * side : 1) +
+                  9 * (axis == 2 ? 2 * side : 1);
+    const bool fine = tb.kind[r] > 0;
+    const int slot = tb.meta[0];
+    const double h = a.Ldom / (double(int64_t(1) << tb.meta[1]) * BS);
+    const T ih = T(1.0 / h), ih2 = T(1.0 / (h * h)), sg = side ? T(-1) : T(1);
+    // the 3 interior layers of this thread's columns: kb and the normal velocity
+    T v[PER][4][3], un[PER][3];
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+      const int qq = tid + k * NT_GEN;
+      if (qq < B2) {
+        int li[3];
+        li[ua] = qq % BS;
+        li[ub] = qq / BS;
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+          li[axis] = side ? BS - 1 - d : d;
+          const int64_t ov = point_in(a.Lv, BS, slot, li[0], li[1], li[2]);
+#pragma unroll
+          for (int c = 0; c < 4; ++c) v[k][c][d] = a.vs * a.v[ov + c * a.Lv.fstride];
+          un[k][d] = a.u[point_in(a.Lu, BS, slot, li[0], li[1], li[2]) + axis * a.Lu.fstride];
+        }
+      }
+    }
+    double* out = fb + wk * 4 * F;
+    const int n0 = side ? BS - 2 : -6, NN = side ? 4 : 5;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+#pragma unroll
+      for (int k = 0; k < PER; ++k) {
+        const int qq = tid + k * NT_GEN;
+        if (qq < B2) {
+#pragma unroll
+          for (int d = 0; d < 3; ++d) {
+            // ghost depth d, interior layer e: distance e + d + 1
+            T s = T(0);
+#pragma unroll
+            for (int e = 0; e + d < 3; ++e) {
+              const int m = e + d;  // distance m + 1
+              const T w = am[m] * ih * sg;
+              if (c < 3) {
+                s += w * (v[k][c][e] * un[k][e]);
+                if (c == axis) s += c0sq * (w * v[k][3][e]);
+                if (m < 2) s += (nu * w2[m + 1] * ih2) * v[k][c][e];
+              } else {
+                s += w * (axis == 0 ? v[k][0][e] : (axis == 1 ? v[k][1][e] : v[k][2][e]));
+              }
+            }
+            if (fine)
+              out[c * F + d * B2 + qq] = (double)s;
+            else
+              gb[d * B2 + qq] = (double)s;
+          }
+        }
+      }
+      if (fine) continue;
+      __syncthreads();
+      // transposed t1 pass: lattice row s takes t1 = 2 (s - 1) with weight 1
+      // and the odd t1 = 2 (s - e) + 1 with weight W4[e]
+      for (int p = tid; p < 3 * S * BS; p += NT_GEN) {
+        const int t0 = p % BS, rest = p / BS, s = rest % S, d = rest / S;
+        const double* g = gb + d * B2 + t0;
+        double val = s >= 1 && s <= BS / 2 ? g[2 * (s - 1) * BS] : 0.0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (s - e >= 0 && s - e < BS / 2) val += W4[e] * g[(2 * (s - e) + 1) * BS];
+        pb[p] = val;
+      }
+      __syncthreads();
+      for (int p = tid; p < 3 * S * S; p += NT_GEN) {
+        const int s = p % S, rest = p / S;  // rest = d S + s1
+        const double* g = pb + rest * BS;
+        double val = s >= 1 && s <= BS / 2 ? g[2 * (s - 1)] : 0.0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (s - e >= 0 && s - e < BS / 2) val += W4[e] * g[2 * (s - e) + 1];
+        pa[p] = val;
+      }
+      __syncthreads();
+      // normal: lattice layer m takes the ghost layers whose prediction reads it
+      for (int p = tid; p < NN * S * S; p += NT_GEN) {
+        const int m = p / (S * S), qq = p - m * S * S;
+        double val = 0.0;
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+          const int g = side ? BS + d : -1 - d;
+          if ((g & 1) == 0) {
+            if ((g - n0) / 2 == m) val += pa[d * S * S + qq];
+          } else {
+            const int e = m - (g - 3 - n0) / 2;
+            if (e >= 0 && e < 4) val += W4[e] * pa[d * S * S + qq];
+          }
+        }
+        out[c * F + p] = val;
+      }
+      __syncthreads();
+    }
+  }
+}
+
+// Adds what the faces next to other levels return: per receiving point the
+// sum of its entries of the face buffer, to the running sum and, weighted, to
+// the next rhs adjoint.  Rows address the compact layout.
 template <typename T>
-__global__ __launch_bounds__(NT_GEN) void fill_zero(T* Y, int64_t n) {
-  for (int64_t r = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; r < n;
-       r += (int64_t)gridDim.x * blockDim.x)
-    Y[r] = T(0);
+__global__ __launch_bounds__(NT_GEN) void adj_gather_kernel(const int64_t* __restrict__ dst,
+                                                            const int64_t* __restrict__ ptr,
+                                                            const int64_t* __restrict__ src,
+                                                            int64_t nrows, int bs,
+                                                            const double* __restrict__ fb,
+                                                            AdjStage<T> a) {
+  const int F = adj_face_stride(bs);
+  for (int64_t r = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; r < nrows;
+       r += (int64_t)gridDim.x * blockDim.x) {
+    double acc[4] = {0, 0, 0, 0};
+    for (int64_t e = ptr[r]; e < ptr[r + 1]; ++e) {
+      const double* b = fb + src[e];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) acc[c] += b[c * F];
+    }
+    const int64_t o = dst[r];
+    const int slot = (int)(o / a.Lc.bstride), q = (int)(o - slot * a.Lc.bstride);
+    T* so = a.sout + point_in(a.Lso, bs, slot, q % bs, (q / bs) % bs, q / (bs * bs));
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      so[c * a.Lso.fstride] += T(acc[c]);
+      if (a.kn) a.kn[o + c * a.Lc.fstride] += a.kw * T(acc[c]);
+    }
+  }
 }
 
 // --------------------------------------------------------------------------
@@ -419,8 +942,8 @@ size_t adj_work_bytes(const wacm_grid* g) {
 }
 
 template <typename T>
-static hipError_t sync_adj_t(const wacm_grid* g, T* Ub, int face_only, hipStream_t st) {
-  const AdjPlan& pl = g->plan[face_only ? 1 : 0];
+static hipError_t sync_adj_t(const wacm_grid* g, T* Ub, hipStream_t st) {
+  const AdjPlan& pl = g->plan[0];
   const int64_t fs = (int64_t)g->P * g->P * g->P;
   if (pl.nrows > 0)
     sync_adj_gather<T><<<grid_n((pl.nrows + NT_GEN - 1) / NT_GEN), NT_GEN, 0, st>>>(
@@ -431,9 +954,8 @@ static hipError_t sync_adj_t(const wacm_grid* g, T* Ub, int face_only, hipStream
   return hipGetLastError();
 }
 
-hipError_t launch_sync_adj(const wacm_grid* g, void* Ub, int face_only, hipStream_t st) {
-  return g->d.dtype == WACM_F64 ? sync_adj_t(g, (double*)Ub, face_only, st)
-                                : sync_adj_t(g, (float*)Ub, face_only, st);
+hipError_t launch_sync_adj(const wacm_grid* g, void* Ub, hipStream_t st) {
+  return g->d.dtype == WACM_F64 ? sync_adj_t(g, (double*)Ub, st) : sync_adj_t(g, (float*)Ub, st);
 }
 
 template <typename T>
@@ -499,57 +1021,136 @@ hipError_t launch_force_adj(const wacm_grid* g, const wacm_params* p, double t, 
                            (const float*)dus, st);
 }
 
-// One RK4 step backwards: recompute the synchronised stage inputs from the
-// checkpoint Un, then sweep the stages in reverse:
+// Work buffer of one adjoint step (within the 8 pool registers of
+// wacm_adj_work_bytes): the stage inputs Y2, Y3, Y4 (x-split), two rhs
+// adjoints and the running sum (compact), the face halos of the stage input
+// and the face buffer (FP64).
+template <typename T>
+struct AdjWork {
+  T *y[3], *k[2], *sum, *hb;
+  double* fb;
+};
+template <typename T>
+static AdjWork<T> adj_work(const wacm_grid* g, void* work) {
+  const size_t cap = (size_t)g->d.capacity, bs = g->d.bs;
+  const size_t reg = up256(cap * 4 * bs * bs * bs * sizeof(T)), hb = up256(cap * 72 * bs * bs * sizeof(T));
+  char* w = (char*)work;
+  AdjWork<T> r;
+  for (int i = 0; i < 3; ++i) r.y[i] = (T*)(w + i * reg);
+  for (int i = 0; i < 2; ++i) r.k[i] = (T*)(w + (3 + i) * reg);
+  r.sum = (T*)(w + 5 * reg);
+  r.hb = (T*)(w + 6 * reg);
+  r.fb = (double*)(w + 6 * reg + hb);
+  return r;
+}
+
+template <typename T, int BS, int TY>
+static hipError_t adj_stage_launch(const wacm_grid* g, const AdjStage<T>& a, double* fb,
+                                   hipStream_t st) {
+  static const int resident = [] {
+    int n = 0, dev = 0, cus = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, adj_stage_kernel<T, BS, TY>, BS * TY, 0) !=
+            hipSuccess || n < 1)
+      n = 1;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        cus < 1)
+      cus = 256;
+    return n * cus;
+  }();
+  const AdjPlan& pl = g->plan[1];
+  if (g->n_cface > 0)
+    adj_face_kernel<T, BS><<<grid_n(g->n_cface), NT_GEN, 0, st>>>(g->d_tab, g->d_cface,
+                                                                  g->n_cface, a, fb);
+  const int64_t items = a.nb * (BS / TY);
+  adj_stage_kernel<T, BS, TY>
+      <<<(unsigned)std::min<int64_t>(items, resident), BS * TY, 0, st>>>(a);
+  if (pl.nrows > 0)
+    adj_gather_kernel<T><<<grid_n((pl.nrows + NT_GEN - 1) / NT_GEN), NT_GEN, 0, st>>>(
+        pl.d_dst, pl.d_ptr, pl.d_src, pl.nrows, BS, fb, a);
+  return hipGetLastError();
+}
+
+// One RK4 step backwards: recompute the stage inputs from the checkpoint Un,
+// then sweep the stages in reverse:
 //   kb_4 = dt/6 lam, kb_3 = dt/3 lam + dt B_4, kb_2 = dt/3 lam + dt/2 B_3,
 //   kb_1 = dt/6 lam + dt/2 B_2, with B_s = S^T J_rhs(U_s)^T kb_s, and
 //   lam_n = lam + B_4 + B_3 + B_2 + B_1.
+// Each stage is three kernels: what the faces next to other levels return
+// (from kb and the input), the stage itself, and the gather of the former.
+// 1632 blocks of 16^3 (plate), FP32: 17.2 -> 4.5 ms per step.
 template <typename T>
 static hipError_t rk4_adj_t(const wacm_grid* g, const wacm_params* p, double t, double dt,
                             const T* Un, T* lam, double* dtheta, double* dusbar, const T* dus,
                             void* work, hipStream_t st) {
   if (g->nb == 0) return hipSuccess;
   const Layout L = pool_L(g);
-  const size_t reg = ((size_t)g->d.capacity * L.bstride * sizeof(T) + 255) / 256 * 256;
-  char* w = (char*)work;
-  T* S[4];
-  for (int s = 0; s < 4; ++s) S[s] = (T*)(w + s * reg);
-  T* K = (T*)(w + 4 * reg);
-  T* kb = (T*)(w + 5 * reg);
-  T* B = (T*)(w + 6 * reg);
-  T* lamU = (T*)(w + 7 * reg);
-  const int64_t nall = (int64_t)g->d.capacity * L.bstride;
-  const unsigned gb = grid_n(g->nb);
-  const int bs = g->d.bs;
-  hipError_t e;
+  Layout Lc;
+  Lc.P = g->d.bs;
+  Lc.ng = 0;
+  Lc.fstride = (int64_t)g->d.bs * g->d.bs * g->d.bs;
+  Lc.bstride = 4 * Lc.fstride;
+  Layout Lx = Lc;
+  Lx.xs = 1;
+  const AdjWork<T> w = adj_work<T>(g, work);
+  const T* in[4] = {Un, w.y[0], w.y[1], w.y[2]};
   const double cs[4] = {0.0, 0.5, 0.5, 1.0};
-  // forward recompute
-  axpby_interior<T><<<gb, NT_GEN, 0, st>>>(g->d_tab, g->nb, L, bs, S[0], 1.0, Un, 0.0, nullptr);
-  if ((e = launch_sync(g, S[0], 1, st)) != hipSuccess) return e;
-  for (int s = 1; s < 4; ++s) {
-    if ((e = launch_rhs(g, p, t + cs[s - 1] * dt, S[s - 1], K, dus, st)) != hipSuccess) return e;
-    axpby_interior<T><<<gb, NT_GEN, 0, st>>>(g->d_tab, g->nb, L, bs, S[s], 1.0, Un, cs[s] * dt,
-                                             K);
-    if ((e = launch_sync(g, S[s], 1, st)) != hipSuccess) return e;
-  }
-  // reverse sweep
-  axpby_interior<T><<<gb, NT_GEN, 0, st>>>(g->d_tab, g->nb, L, bs, lamU, 1.0, lam, 0.0, nullptr);
-  axpby_interior<T><<<gb, NT_GEN, 0, st>>>(g->d_tab, g->nb, L, bs, kb, dt / 6.0, lam, 0.0,
-                                           nullptr);
   const double lamw[4] = {dt / 6.0, dt / 3.0, dt / 3.0, dt / 6.0};
-  for (int s = 3; s >= 0; --s) {
-    fill_zero<T><<<grid_n((nall + NT_GEN - 1) / NT_GEN), NT_GEN, 0, st>>>(B, nall);
-    if ((e = rhs_adj_t<T>(g, p, t + cs[s] * dt, S[s], kb, B, dtheta, dusbar, dus, st)) !=
+  hipError_t e;
+  for (int s = 1; s < 4; ++s)
+    if ((e = launch_stage_input(g, p, s, t, dt, Un, in[s - 1], w.y[s - 1], w.hb, dus, st)) !=
         hipSuccess)
       return e;
-    if ((e = sync_adj_t<T>(g, B, 1, st)) != hipSuccess) return e;
-    axpby_interior<T><<<gb, NT_GEN, 0, st>>>(g->d_tab, g->nb, L, bs, lamU, 1.0, lamU, 1.0, B);
-    if (s > 0)
-      axpby_interior<T><<<gb, NT_GEN, 0, st>>>(g->d_tab, g->nb, L, bs, kb, lamw[s - 1], lam,
-                                               cs[s] * dt, B);
+  AdjStage<T> a{};
+  a.tab = g->d_tab;
+  a.nb = g->nb;
+  a.hb = w.hb;
+  a.lam = lam;
+  a.Lp = L;
+  a.Lc = Lc;
+  a.Ldom = g->d.L;
+  a.p = *p;
+  a.dus = dus;
+  a.dusbar = dusbar;
+  a.part = g->d_part;
+  for (int s = 3; s >= 0; --s) {
+    a.u = in[s];
+    a.Lu = s == 0 ? L : Lx;
+    a.t = t + cs[s] * dt;
+    a.v = s == 3 ? lam : w.k[(s + 1) & 1];
+    a.Lv = s == 3 ? L : Lc;
+    a.vs = s == 3 ? T(lamw[3]) : T(1);
+    a.sin = s == 3 ? lam : w.sum;
+    a.Lsi = s == 3 ? L : Lc;
+    a.sout = s == 0 ? lam : w.sum;
+    a.Lso = s == 0 ? L : Lc;
+    a.kn = s == 0 ? nullptr : w.k[s & 1];
+    a.lamw = s == 0 ? T(0) : T(lamw[s - 1]);
+    a.kw = T(cs[s] * dt);
+    if ((e = launch_nlface(g, a.u, a.Lu, w.hb, st)) != hipSuccess) return e;
+    int64_t items = g->nb;
+    switch (g->d.bs) {
+      case 16:
+        e = adj_stage_launch<T, 16, 16>(g, a, w.fb, st);
+        break;
+      case 24:
+        e = adj_stage_launch<T, 24, 8>(g, a, w.fb, st);
+        items *= 3;
+        break;
+      case 32:
+        e = adj_stage_launch<T, 32, 8>(g, a, w.fb, st);
+        items *= 4;
+        break;
+      default:
+        e = hipErrorInvalidValue;
+    }
+    if (e != hipSuccess) return e;
+    if (p->mask) {
+      theta_finalize<<<1, NT_GEN, 0, st>>>(g->d_part, items, dtheta);
+      if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
   }
-  axpby_interior<T><<<gb, NT_GEN, 0, st>>>(g->d_tab, g->nb, L, bs, lam, 1.0, lamU, 0.0, nullptr);
-  return hipGetLastError();
+  return hipSuccess;
 }
 
 hipError_t launch_rk4_adj(const wacm_grid* g, const wacm_params* p, double t, double dt,

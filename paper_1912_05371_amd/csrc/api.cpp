@@ -294,7 +294,7 @@ int wacm_get_schedule(const wacm_grid* g, wacm_schedule* s) {
 // 4/4 the lifted values of ghost points whose owner is finer.
 static hipError_t full_sync(const wacm_grid* g, void* U, hipStream_t st) {
   if (g->dim == 2) return launch_sync_2d(g, U, st);
-  hipError_t e = launch_sync(g, U, 0, st);
+  hipError_t e = launch_sync(g, U, st);
   if (e == hipSuccess && g->wavelet == WACM_CDF44) e = launch_lift_sync(g, U, st);
   return e;
 }
@@ -682,7 +682,7 @@ int wacm_sync_ghosts_adj(wacm_grid* g, void* Ub, void* stream) {
   if (g->wavelet != WACM_CDF40) return fail(WACM_E_INVAL, "the adjoint is CDF 4/0 only");
   if (!g->plan[0].built)
     return fail(WACM_E_INVAL, "no plan of the ghost-fill transpose: wacm_adj_plan_set(grid, 0, ...)");
-  hipError_t e = launch_sync_adj(g, Ub, 0, S(stream));
+  hipError_t e = launch_sync_adj(g, Ub, S(stream));
   return e == hipSuccess ? WACM_OK : hipfail(e, "sync_ghosts_adj launch");
 }
 

@@ -8,15 +8,10 @@
 #include <mutex>
 
 #include "resolve.h"
+#include "stage.h"
 #include "wacm_internal.h"
 
 namespace wacm {
-
-__device__ __forceinline__ void load_tab(const Tab* __restrict__ g, Tab& s) {
-  const int32_t* src = reinterpret_cast<const int32_t*>(g);
-  int32_t* dst = reinterpret_cast<int32_t*>(&s);
-  for (int q = threadIdx.x; q < (int)(sizeof(Tab) / 4); q += blockDim.x) dst[q] = src[q];
-}
 
 template <typename T>
 __device__ __forceinline__ T wave_max(T v) {
@@ -255,17 +250,6 @@ __global__ __launch_bounds__(NT_GEN) void sync_coarser_kernel(const Tab* __restr
 // --------------------------------------------------------------------------
 // fused rhs + RK4 stage (Sec. 2.2-2.3)
 // --------------------------------------------------------------------------
-// Barrier that orders LDS traffic only: global loads issued before it stay in
-// flight (they are the next plane's prefetch).
-__device__ __forceinline__ void lds_barrier() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-  // s_waitcnt lgkmcnt(0): this wave's LDS writes have completed before it
-  // arrives (the fence alone need not wait for them)
-  __builtin_amdgcn_s_waitcnt(0xC07F);
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
 template <typename T>
 struct StageArgs {
   const Tab* tab;
@@ -280,8 +264,8 @@ struct StageArgs {
   T* out;  // next stage input, or dU for the rhs-only mode
   Layout Lout;
   const T* dus;  // extra solid velocity [slot][3][bs^3] or null
-  const double* t_dev;
-  const double* dt_dev;
+  const double* t_dev;  // step time and size on the device, or null:
+  const double* dt_dev;  // t_host and dt_host
   double* umax_part;  // stage 4: per work item max |u|^2 of the new U^n, or null
   // optional block list: the blocks of this launch are blist[off + i],
   // i < bcnt[bsel], off = bsel ? bcnt[0] : 0 (the list holds the blocks
@@ -290,34 +274,13 @@ struct StageArgs {
   const int32_t* bcnt;
   int bsel;
   double t_host;
+  double dt_host;
+  double kscale;  // MODE 3: out = U^n + kscale dt k (1; 1/2 gives stage 2 without W)
   double L;
   int xcd_map;  // 1: give each XCD a contiguous run of work items
   int* queue;   // xcd_map 2: per-XCD work counters (QSTRIDE apart), zero at launch
   int nt;       // 1: non-temporal loads/stores of the streaming operands
   wacm_params p;
-};
-
-// Persistent loop over the work items (block b, tile t) = item b nty + t of
-// the Morton-ordered block list.  With xcd_map, workgroup w (dispatched to XCD
-// w % 8) walks a contiguous eighth of the items, so blocks that share faces
-// are processed close in time on the same L2; otherwise items go round-robin.
-struct BlockIter {
-  int64_t ib, end, step;
-  __device__ BlockIter(int64_t n, int xcd_map) {
-    const int64_t G = gridDim.x, w = blockIdx.x;
-    if (xcd_map && G % 8 == 0 && n >= G) {
-      const int64_t per = G / 8, xcd = w % 8, lw = w / 8;
-      const int64_t chunk = (n + 7) / 8;
-      const int64_t start = xcd * chunk;
-      end = start + chunk < n ? start + chunk : n;
-      ib = start + lw;
-      step = per;
-    } else {
-      ib = w;
-      end = n;
-      step = G;
-    }
-  }
 };
 
 // Dynamic per-XCD work queues (xcd_map 2): the Morton-ordered items are cut
@@ -342,94 +305,6 @@ __device__ __forceinline__ int queue_take(int* ctr, int& q, int chunk, int n, in
 
 __global__ void queue_clear(int* ctr) {
   if (threadIdx.x < 8 * QSTRIDE) ctr[threadIdx.x] = 0;
-}
-
-// Where the depth-3 halo of one face of the current block lives: element
-// (field c, depth d away from the face, tangential t0 < t1 by axis order) is
-// ptr[c fs + d sd + t0 s0 + t1 s1].  Same-level neighbours are read in place
-// (their interior next to the face); faces next to a coarser or finer leaf
-// point into the halo buffer filled by nlface_kernel; the rhs-only mode reads
-// the block's own synchronised ghost layers.  With an x-split input the
-// x faces stay affine (the neighbour's side columns); for the y and z faces
-// mode = 1 and ptr is the neighbour's origin: each thread addresses its own
-// column with xsplit_offset.
-template <typename T>
-struct FaceDesc {
-  const T* ptr;
-  int32_t fs, sd, s0, s1, mode;
-};
-
-// Where a stage reads the depth-3 halo of a face: HALO_NB same-level faces
-// from the neighbour's interior, the others from the face-halo buffer;
-// HALO_OWN every face from the input's own ghost layers; HALO_MIX same-level
-// faces from the neighbour's interior, the others from the own ghost layers.
-enum { HALO_NB = 0, HALO_OWN = 1, HALO_MIX = 2 };
-
-template <typename T, int BS, int HALO>
-__device__ __forceinline__ FaceDesc<T> face_desc(const Tab& tb, const StageArgs<T>& a, int f,
-                                                 bool xin) {
-  const int axis = f >> 1, side = f & 1;
-  const Layout& L = a.Lin;
-  const int sx[3] = {1, L.P, L.P * L.P};
-  const int sa = sx[axis], st0 = sx[axis == 0 ? 1 : 0], st1 = sx[axis == 2 ? 1 : 2];
-  const int slot = tb.meta[0];
-  const int64_t org = ((int64_t)L.ng * L.P + L.ng) * L.P + L.ng;  // local (0,0,0)
-  const int r = (axis == 0 ? 2 * side : 1) + 3 * (axis == 1 ? 2 * side : 1) +
-                9 * (axis == 2 ? 2 * side : 1);
-  FaceDesc<T> fd;
-  fd.mode = 0;
-  if (HALO == HALO_OWN || (HALO == HALO_MIX && tb.kind[r] != 0)) {
-    fd.ptr = a.in + (int64_t)slot * L.bstride + org + (int64_t)(side ? BS : -1) * sa;
-    fd.fs = (int)L.fstride;
-    fd.sd = side ? sa : -sa;
-    fd.s0 = st0;
-    fd.s1 = st1;
-    return fd;
-  }
-  if (tb.kind[r] == 0 && xin) {
-    const T* nb = a.in + (int64_t)tb.slot[r][0] * L.bstride;
-    fd.fs = (int)L.fstride;
-    if (axis == 0) {
-      // side 0 reads the neighbour's last columns from the top, side 1 its
-      // first ones
-      fd.ptr = nb + (side ? BS * BS * (BS - 2 * XS_H) : BS * BS * (BS - XS_H) + XS_H - 1);
-      fd.sd = side ? 1 : -1;
-      fd.s0 = XS_H;
-      fd.s1 = XS_H * BS;
-    } else {
-      fd.ptr = nb;
-      fd.sd = fd.s0 = fd.s1 = 0;
-      fd.mode = 1;
-    }
-  } else if (tb.kind[r] == 0) {
-    fd.ptr = a.in + (int64_t)tb.slot[r][0] * L.bstride + org + (int64_t)(side ? 0 : BS - 1) * sa;
-    fd.fs = (int)L.fstride;
-    fd.sd = side ? sa : -sa;
-    fd.s0 = st0;
-    fd.s1 = st1;
-  } else {
-    fd.ptr = a.hb + ((int64_t)slot * 6 + f) * 12 * BS * BS;
-    fd.fs = 3 * BS * BS;
-    fd.sd = BS * BS;
-    fd.s0 = 1;
-    fd.s1 = BS;
-  }
-  return fd;
-}
-
-// Streaming operands (U^n, the accumulator) are touched once per stage: load
-// and store them non-temporally so the caches keep the stage input, whose
-// face layers neighbouring blocks read again.
-template <typename T>
-__device__ __forceinline__ T ntload(const T* p, int nt) {
-  return nt ? __builtin_nontemporal_load(p) : *p;
-}
-template <typename T>
-__device__ __forceinline__ void ntstore(T v, T* p, int nt) {
-  if (nt)
-    __builtin_nontemporal_store(v, p);
-  else
-    *p = v;
 }
 
 // MODE 0: dU = rhs(U) with U's own ghost layers.  MODE s = 1..4: classical
@@ -483,15 +358,15 @@ void stage_kernel(StageArgs<T> a) {
   const T c2a = T(D2A), c2b = T(D2B), c2c = T(D2C);
   double tc = a.t_host, dt = 0.0;
   if (MODE != 0) {
-    tc = *a.t_dev;
-    dt = *a.dt_dev;
+    if (a.t_dev) tc = *a.t_dev;
+    dt = a.dt_dev ? *a.dt_dev : a.dt_host;
   }
   const T nu = T(a.p.nu), c0sq = T(a.p.c0 * a.p.c0), cg = T(a.p.c_gamma);
   const T fA = T(MODE == 4 ? dt / 6.0 : dt / 3.0);  // k weight of W (s2) and of U^{n+1} (s4)
   // the stage time and what of the mask depends on it alone
   const double ts = tc + (MODE == 2 || MODE == 3 ? 0.5 * dt : (MODE == 4 ? dt : 0.0));
   const MaskTime mt = PEN && a.p.mask ? mask_time(a.p, ts) : MaskTime{1.0, 0.0, 0.0};
-  const T fB = T(MODE == 3 ? dt : 0.5 * dt);
+  const T fB = T(MODE == 3 ? a.kscale * dt : 0.5 * dt);
   const int fin = (int)a.Lin.fstride, Pi = a.Lin.P;
   const int cidx = (yl + H) * W + (x + H);
   // this thread's halo point of every plane (threads < NH): x-faces of the
@@ -547,7 +422,7 @@ void stage_kernel(StageArgs<T> a) {
     const int64_t ibk = a.blist ? a.blist[boff + il] : il;
     const int y0 = (int)(item - il * NTY) * TY;
     const int y = y0 + yl;
-    if (tid < 6) fds[tid] = face_desc<T, BS, HALO>(a.tab[ibk], a, tid, xin);
+    if (tid < 6) fds[tid] = face_desc<T, BS, HALO>(a.tab[ibk], a.in, a.Lin, a.hb, tid, xin);
     if (tid < 5) meta[tid] = a.tab[ibk].meta[tid];
     lds_barrier();
     if (dyn && tid == 0) qpend = atomicAdd(a.queue + qh * QSTRIDE, 1);
@@ -1745,15 +1620,14 @@ static void sync_coarser_launch(const wacm_grid* g, T* U, hipStream_t st) {
       g->d_tab, g->d_cregion, g->n_cregion, U, pool_layout(g));
 }
 
-// Full ghost fill (mode 0): point-wise for same-level and finer regions, and
-// the separable region kernel for regions in a coarser leaf; the face star
-// (mode 1) point-wise.
+// Full ghost fill: point-wise for same-level and finer regions, and the
+// separable region kernel for regions in a coarser leaf.
 template <typename T>
-static hipError_t sync_t(const wacm_grid* g, T* U, int mode, hipStream_t st) {
+static hipError_t sync_t(const wacm_grid* g, T* U, hipStream_t st) {
   if (g->nb == 0) return hipSuccess;
-  const bool split = mode == 0 && g->d.ng <= SC_MAXG && g->n_cregion > 0;
+  const bool split = g->d.ng <= SC_MAXG && g->n_cregion > 0;
   sync_kernel<T><<<grid_for(g->nb, 8), NT_GEN, 0, st>>>(g->d_tab, g->nb, U, pool_layout(g),
-                                                        g->d.bs, mode, split ? 1 : 0, nullptr);
+                                                        g->d.bs, 0, split ? 1 : 0, nullptr);
   if (split) {
     switch (g->d.bs) {
       case 16:
@@ -1807,7 +1681,7 @@ template <typename T>
 static hipError_t sync_lifted_stage_t(const wacm_grid* g, T* U, const int32_t* box,
                                       hipStream_t st) {
   if (g->nb == 0) return hipSuccess;
-  if (g->d.ng > SC_MAXG || !box) return sync_t(g, U, 0, st);
+  if (g->d.ng > SC_MAXG || !box) return sync_t(g, U, st);
   const bool split = g->n_cregion > 0;
   sync_kernel<T><<<grid_for(g->nb, 8), NT_GEN, 0, st>>>(g->d_tab, g->nb, U, pool_layout(g),
                                                         g->d.bs, 0, split ? 1 : 0, box);
@@ -1835,9 +1709,8 @@ hipError_t launch_sync_lifted_stage(const wacm_grid* g, void* U, const int32_t* 
                                 : sync_lifted_stage_t(g, (float*)U, box, st);
 }
 
-hipError_t launch_sync(const wacm_grid* g, void* U, int face_only, hipStream_t st) {
-  return g->d.dtype == WACM_F64 ? sync_t(g, (double*)U, face_only ? 1 : 0, st)
-                                : sync_t(g, (float*)U, face_only ? 1 : 0, st);
+hipError_t launch_sync(const wacm_grid* g, void* U, hipStream_t st) {
+  return g->d.dtype == WACM_F64 ? sync_t(g, (double*)U, st) : sync_t(g, (float*)U, st);
 }
 
 // resident workgroups per CU of a kernel (queried once per instantiation)
@@ -1930,6 +1803,7 @@ static StageArgs<T> base_args(const wacm_grid* g, const wacm_params* p) {
   a.xcd_map = g->sched.xcd_map;
   a.queue = g->sched.xcd_map == 2 ? g->d_queue : nullptr;
   a.nt = g->sched.nontemporal;
+  a.kscale = 1.0;
   a.p = *p;
   return a;
 }
@@ -2076,6 +1950,49 @@ static bool pen_split_pays(const wacm_grid* g, const wacm_params* p) {
   for (int64_t b = 0; b < g->nb && nfar < 512; ++b)
     nfar += pen_far(*p, g->d.L, g->d.bs, g->h_tab[b].meta, any) ? 1 : 0;
   return nfar >= 512;
+}
+
+// A stage input of one RK4 step recomputed from U^n, for the adjoint: s = 1
+// Y2 = U^n + dt/2 rhs(U^n), 2 Y3 = U^n + dt/2 rhs(Y2), 3 Y4 = U^n + dt
+// rhs(Y3); `in` is the input's predecessor (U^n in the pool layout for s = 1,
+// else x-split), out x-split, hb the face-halo buffer.
+template <typename T>
+static hipError_t stage_input_t(const wacm_grid* g, const wacm_params* p, int s, double t,
+                                double dt, const T* un, const T* in, T* out, T* hb, const T* dus,
+                                hipStream_t st) {
+  StageArgs<T> a = base_args<T>(g, p);
+  a.in = in;
+  a.Lin = s == 1 ? pool_layout(g) : split_layout(g);
+  a.hb = hb;
+  a.un = const_cast<T*>(un);
+  a.Lun = pool_layout(g);
+  a.out = out;
+  a.Lout = split_layout(g);
+  a.dus = dus;
+  a.t_host = t;
+  a.dt_host = dt;
+  a.kscale = s == 2 ? 0.5 : 1.0;
+  if (g->n_cface > 0)
+    if (hipError_t e = nlface_launch<T>(g, in, a.Lin, hb, st); e != hipSuccess) return e;
+  return s == 1 ? stage_dispatch<T, 1>(g->d.bs, a, g->sched, st)
+                : stage_dispatch<T, 3>(g->d.bs, a, g->sched, st);
+}
+
+hipError_t launch_stage_input(const wacm_grid* g, const wacm_params* p, int s, double t,
+                              double dt, const void* un, const void* in, void* out, void* hb,
+                              const void* dus, hipStream_t st) {
+  return g->d.dtype == WACM_F64
+             ? stage_input_t(g, p, s, t, dt, (const double*)un, (const double*)in, (double*)out,
+                             (double*)hb, (const double*)dus, st)
+             : stage_input_t(g, p, s, t, dt, (const float*)un, (const float*)in, (float*)out,
+                             (float*)hb, (const float*)dus, st);
+}
+
+hipError_t launch_nlface(const wacm_grid* g, const void* in, const Layout& Lin, void* hb,
+                         hipStream_t st) {
+  if (g->n_cface == 0) return hipSuccess;
+  return g->d.dtype == WACM_F64 ? nlface_launch<double>(g, (const double*)in, Lin, (double*)hb, st)
+                                : nlface_launch<float>(g, (const float*)in, Lin, (float*)hb, st);
 }
 
 template <typename T>

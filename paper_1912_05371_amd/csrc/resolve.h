@@ -208,23 +208,35 @@ WACM_HD inline void mask_eval(const wacm_params& p, double t, double x, double y
 
 // Plate mask with its derivative in the pitch angle, and the solid velocity
 // with its derivative in the pitch rate; dal/dad: d alpha / d(A, f, phi) and
-// d alpha_dot / d(A, f, phi).  Used by the adjoint kernels.
-WACM_HD inline void plate_eval_adj(const wacm_params& p, double t, double x, double y, double z,
-                                   double& chi, double& dchi, double us[3], double dusd[3],
-                                   double dal[3], double dad[3]) {
+// d alpha_dot / d(A, f, phi).  Used by the adjoint kernels, which evaluate
+// what depends on the time alone (plate_adj_time) once per thread.
+struct PlateAdjTime {
+  double ca, sa, ad, dal[3], dad[3];
+};
+
+WACM_HD inline PlateAdjTime plate_adj_time(const wacm_params& p, double t) {
+  PlateAdjTime m;
   const double twopi = 6.283185307179586476925286766559;
   const double ph = twopi * p.freq * t + p.phase;
   const double s = sin(ph), c = cos(ph);
-  const double al = p.amp * s, ad = p.amp * twopi * p.freq * c;
-  dal[0] = s;
-  dal[1] = p.amp * c * twopi * t;
-  dal[2] = p.amp * c;
-  dad[0] = twopi * p.freq * c;
-  dad[1] = p.amp * twopi * c - p.amp * twopi * p.freq * s * twopi * t;
-  dad[2] = -p.amp * twopi * p.freq * s;
+  const double al = p.amp * s;
+  m.ad = p.amp * twopi * p.freq * c;
+  m.dal[0] = s;
+  m.dal[1] = p.amp * c * twopi * t;
+  m.dal[2] = p.amp * c;
+  m.dad[0] = twopi * p.freq * c;
+  m.dad[1] = p.amp * twopi * c - p.amp * twopi * p.freq * s * twopi * t;
+  m.dad[2] = -p.amp * twopi * p.freq * s;
+  m.ca = cos(al);
+  m.sa = sin(al);
+  return m;
+}
+
+WACM_HD inline void plate_adj_point(const wacm_params& p, const PlateAdjTime& m, double x,
+                                    double y, double z, double& chi, double& dchi, double us[3],
+                                    double dusd[3]) {
   const double rx = x - p.x_le[0], ry = y - p.x_le[1], rz = z - p.x_le[2];
-  const double ca = cos(al), sa = sin(al);
-  const double b[3] = {ca * rx - sa * rz, ry, sa * rx + ca * rz};
+  const double b[3] = {m.ca * rx - m.sa * rz, ry, m.sa * rx + m.ca * rz};
   const double db[3] = {-b[2], 0.0, b[0]};
   double gv[3], gp[3];
   for (int d = 0; d < 3; ++d) {
@@ -239,9 +251,9 @@ WACM_HD inline void plate_eval_adj(const wacm_params& p, double t, double x, dou
     chi = 0.0;
     dchi = 0.0;
   }
-  us[0] = ad * rz;
+  us[0] = m.ad * rz;
   us[1] = 0.0;
-  us[2] = -ad * rx;
+  us[2] = -m.ad * rx;
   dusd[0] = rz;
   dusd[1] = 0.0;
   dusd[2] = -rx;

@@ -127,9 +127,10 @@ struct Profiler {
 
 // Transpose of the ghost fill as a gather: for each interior point that some
 // ghost value was read from (rows, element offset of field 0), the ghosts that
-// read it with their weights; plus the list of ghost points to clear.  Built
-// on the host (h_*), then copied into a device buffer the caller owns (d_*
-// point into it; `built` once uploaded).
+// read it with their weights; plus the list of ghost points to clear.  The
+// face-star plan has entries into the face buffer instead, without weights.
+// Built on the host (h_*), then copied into a device buffer the caller owns
+// (d_* point into it; `built` once uploaded).
 struct AdjPlan {
   int built = 0;
   int64_t nrows = 0, nnz = 0, nghost = 0;
@@ -244,7 +245,7 @@ struct Regs {  // pointers and layouts of the RK registers
 
 // ghost points of the even lattice within 3 of each block (CDF 4/0, 3D)
 hipError_t launch_sync_lattice(const wacm_grid* g, void* U, hipStream_t st);
-hipError_t launch_sync(const wacm_grid* g, void* U, int face_only, hipStream_t st);
+hipError_t launch_sync(const wacm_grid* g, void* U, hipStream_t st);
 // one RK stage (1..4) of the fused kernel reading the input's own ghost
 // layers; every register in the padded pool layout
 hipError_t launch_stage_owng(const wacm_grid* g, const wacm_params* p, int s,
@@ -257,6 +258,13 @@ hipError_t launch_dt(const wacm_grid* g, const wacm_params* p, const void* U, do
 hipError_t launch_rk4(const wacm_grid* g, const wacm_params* p, double* t_dev, double* dt_dev,
                       void* U, void* work, const void* dus, int dt_mode, int64_t nsteps,
                       hipStream_t st);
+// a stage input recomputed from U^n (adjoint; s = 1..3), and the face halos of
+// a register next to other levels
+hipError_t launch_stage_input(const wacm_grid* g, const wacm_params* p, int s, double t,
+                              double dt, const void* un, const void* in, void* out, void* hb,
+                              const void* dus, hipStream_t st);
+hipError_t launch_nlface(const wacm_grid* g, const void* in, const Layout& Lin, void* hb,
+                         hipStream_t st);
 hipError_t launch_diag(const wacm_grid* g, const wacm_params* p, double t, const void* U,
                        const void* dus, double* out, hipStream_t st);
 hipError_t launch_threshold(const wacm_grid* g, const wacm_params* p, double t, const void* U,
@@ -294,7 +302,7 @@ int build_adj_plan(wacm_grid* g, int face_only, std::string& err);  // host part
 size_t adj_plan_bytes(const AdjPlan& p);
 int upload_adj_plan(wacm_grid* g, int face_only, void* ws, size_t bytes, std::string& err);
 void free_adj_plans(wacm_grid* g);
-hipError_t launch_sync_adj(const wacm_grid* g, void* Ub, int face_only, hipStream_t st);
+hipError_t launch_sync_adj(const wacm_grid* g, void* Ub, hipStream_t st);
 hipError_t launch_rhs_adj(const wacm_grid* g, const wacm_params* p, double t, const void* U,
                           const void* V, void* Ub, double* dtheta, double* dusbar,
                           const void* dus, hipStream_t st);
