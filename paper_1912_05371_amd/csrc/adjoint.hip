@@ -362,11 +362,12 @@ __global__ __launch_bounds__(NT_GEN) void rhs_adj_kernel(AdjArgs<T> a) {
 }
 
 // Gradient of weight * F_x (the x-force, Sec. 2.2 midpoint rule) at time t.
-template <typename T>
+template <typename T, int bs>
 __global__ __launch_bounds__(NT_GEN) void force_adj_kernel(AdjArgs<T> a) {
   __shared__ double red[3][NT_GEN];
-  const int bs = a.bs, ng = a.L.ng, P = a.L.P;
-  const int n3 = bs * bs * bs;
+  __shared__ PlateAdjTab<bs> ptab;
+  const int ng = a.L.ng, P = a.L.P;
+  constexpr int n3 = bs * bs * bs;
   const wacm_params& p = a.p;
   const PlateAdjTime pm = plate_adj_time(p, a.t);
   for (int64_t ib = blockIdx.x; ib < a.nb; ib += gridDim.x) {
@@ -376,25 +377,27 @@ __global__ __launch_bounds__(NT_GEN) void force_adj_kernel(AdjArgs<T> a) {
     const double vol = h * h * h;
     const int64_t base = (int64_t)slot * a.L.bstride;
     double th[3] = {0, 0, 0};
-    // where the mask vanishes at time t on the whole block every term is 0;
-    // 0 times a value that is not finite is not
-    wacm_params pq = p;
-    pq.sponge = 0;
-    const bool far = pen_far(pq, a.Ldom, bs, m, pitch_window(p, a.t, a.t));
-    for (int qi = threadIdx.x; qi < n3; qi += blockDim.x) {
+    const bool masked = (pen_reach(p, a.Ldom, bs, m, pm.ca, pm.sa) & 1) != 0;
+    const bool plate = masked && p.mask == WACM_MASK_PLATE;
+    if (plate) {  // uniform; the last block's reduction has ended
+      plate_adj_tab_fill<bs>(p, pm, m, h, 0, bs, ptab);
+      __syncthreads();
+    }
+    for (int qi = threadIdx.x; qi < n3; qi += NT_GEN) {
       const int i = qi % bs, j = (qi / bs) % bs, k = qi / (bs * bs);
       const int64_t o = base + ((int64_t)(k + ng) * P + (j + ng)) * P + (i + ng);
-      if (far) {
+      if (!masked) {
+        // every term is 0; 0 times a value that is not finite is not
         for (int k2 = 0; k2 < 3; ++k2) th[k2] += 0.0 * (double)a.U[o];
         continue;
       }
       const double xg = (double)(m[2] * bs + i) * h, yg = (double)(m[3] * bs + j) * h,
                    zg = (double)(m[4] * bs + k) * h;
-      double chi, dchi = 0.0, us[3], dsd[3] = {0, 0, 0};
-      if (p.mask == WACM_MASK_PLATE)
-        plate_adj_point(p, pm, xg, yg, zg, chi, dchi, us, dsd);
+      double chi, dchi = 0.0, us[3] = {0, 0, 0}, dsd[3] = {0, 0, 0};
+      if (plate)
+        plate_adj_tab_point<bs>(p, pm, ptab, i, j, k, xg, zg, chi, dchi, us, dsd);
       else
-        mask_eval(p, a.t, xg, yg, zg, chi, us);
+        chi = sphere_chi(p, xg, yg, zg);
       const double cw = a.weight * chi * vol / p.c_eta;
       a.Ub[o] += T(cw);
       if (a.dusbar) a.dusbar[((int64_t)slot * 3) * n3 + qi] -= cw;
@@ -468,7 +471,8 @@ struct AdjStage {
   wacm_params p;
   const T* dus;    // [slot][3][bs^3] or null
   double* dusbar;  // [slot][3][bs^3] or null (accumulated, FP64)
-  double* part;    // theta partials, 3 per work item
+  double* bad;     // per work item: 0, or NaN if kb is not finite somewhere
+  double* part;    // theta partials, 3 per work item of adj_pen_kernel
 };
 
 // Element offset (field 0) of a block's interior point in a register.
@@ -483,13 +487,11 @@ __device__ __forceinline__ int64_t point_in(const Layout& L, int bs, int slot, i
 // kernel: work items are tiles of TY rows of a block (TY = BS = 16: the whole
 // block), one thread per column marching in z, the planes of kb (4 fields) and
 // u (3) in a double-buffered LDS slab, their z neighbours in registers, one
-// LDS barrier per plane, the next plane's loads issued before it.  It replaces
-// per stage a clear of a whole pool, the point-wise gather of 18 neighbours,
-// a gather over every ghost entry, a second clear and two combination passes
-// (1632 blocks of 16^3, FP32: 2.9 -> 0.84 ms).
-// The plate's terms are evaluated only in blocks where the mask does not
-// vanish (pen_far); elsewhere they are exactly 0.
-template <typename T, int BS, int TY>
+// LDS barrier per plane, the next plane's loads and the point's other operands
+// issued before it, without branches (a conditional load, or a product with
+// what was loaded, would wait there).  The pointwise mask and sponge terms are
+// adj_pen_kernel's.  NEXT: another stage follows (kn is written).
+template <typename T, int BS, int TY, bool NEXT>
 __global__ __launch_bounds__(BS* TY) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 2 : 3)))
 void adj_stage_kernel(AdjStage<T> a) {
   constexpr int H = 3, W = BS + 2 * H, WY = TY + 2 * H, NT = BS * TY, NTY = BS / TY;
@@ -497,16 +499,14 @@ void adj_stage_kernel(AdjStage<T> a) {
   static_assert(NH <= NT, "one halo point per thread and plane");
   __shared__ T slab[2][7][W * WY];  // kb_u, kb_v, kb_w, kb_p, u, v, w
   __shared__ FaceDesc<T> fu[6], fv[6];
-  __shared__ int32_t meta[6];
-  __shared__ double red[3][NT / 64];
+  __shared__ int32_t meta[8];  // slot, level; 2 + f: kb is 0 beyond face f
+  __shared__ T red[NT / 64];
   const int tid = threadIdx.x, x = tid % BS, yl = tid / BS;
-  const wacm_params& p = a.p;
   const T am[3] = {T(TW1), T(TW2), T(TW3)};
   const T c2a = T(D2A), c2b = T(D2B), c2c = T(D2C);
-  const T nu = T(p.nu), c0sq = T(p.c0 * p.c0), cg = T(p.c_gamma), vs = a.vs;
+  const T nu = T(a.p.nu), c0sq = T(a.p.c0 * a.p.c0), cg = T(a.p.c_gamma), vs = a.vs;
   const bool xin = a.Lu.xs != 0;
   const int cidx = (yl + H) * W + (x + H);
-  const PlateAdjTime pm = plate_adj_time(p, a.t);
   // this thread's halo point of every plane: x faces of the tile's rows, then
   // the 3 rows below and above the tile
   const bool hthr = tid < NH;
@@ -525,47 +525,50 @@ void adj_stage_kernel(AdjStage<T> a) {
     hs = rem - hd * BS;
     hli = ((hkind == 2 ? -1 - hd : TY + hd) + H) * W + (hs + H);
   }
+  const int ufs = (int)a.Lu.fstride, vfs = (int)a.Lv.fstride;
+  const int vzs = a.Lv.P * a.Lv.P, pzs = a.Lp.P * a.Lp.P;
+  const int sizs = a.Lsi.P * a.Lsi.P, sozs = a.Lso.P * a.Lso.P;
   const int64_t nitems = a.nb * NTY;
   BlockIter it(nitems, 1);
   for (; it.ib < it.end; it.ib += it.step) {
     const int64_t item = it.ib, ibk = item / NTY;
     const int y0 = (int)(item - ibk * NTY) * TY, y = y0 + yl;
-    __syncthreads();
+    lds_barrier();
     if (tid < 6) {
       const Tab& tb = a.tab[ibk];
       fu[tid] = face_desc<T, BS, HALO_NB>(tb, a.u, a.Lu, a.hb, tid, xin);
-      fv[tid] = face_desc<T, BS, HALO_NB>(tb, a.v, a.Lv, nullptr, tid, false);
       const int r = tid == 0 ? 12 : (tid == 1 ? 14 : (tid == 2 ? 10 : (tid == 3 ? 16 : (tid == 4 ? 4 : 22))));
-      if (tb.kind[r] != 0) fv[tid].ptr = nullptr;
+      const bool none = tb.kind[r] != 0;  // (reads there stay inside the block)
+      FaceDesc<T> f = face_desc<T, BS, HALO_NB>(tb, a.v, a.Lv, a.v, tid, false);
+      if (none) {
+        f.ptr = a.v + point_in(a.Lv, BS, tb.meta[0], 0, 0, 0);
+        f.fs = vfs;
+        f.sd = f.s0 = f.s1 = 0;
+      }
+      fv[tid] = f;
+      meta[2 + tid] = none ? 1 : 0;
+      if (tid < 2) meta[tid] = tb.meta[tid];
     }
-    if (tid < 5) meta[tid] = a.tab[ibk].meta[tid];
-    if (tid == 5) {
-      wacm_params pq = p;
-      pq.sponge = 0;
-      meta[5] = p.mask && !pen_far(pq, a.Ldom, BS, a.tab[ibk].meta, pitch_window(p, a.t, a.t));
-    }
-    __syncthreads();
+    lds_barrier();
     const int slot = __builtin_amdgcn_readfirstlane(meta[0]);
     const int J = __builtin_amdgcn_readfirstlane(meta[1]);
-    const bool masked = __builtin_amdgcn_readfirstlane(meta[5]) != 0;
+    const bool zlo = __builtin_amdgcn_readfirstlane(meta[6]) != 0;
+    const bool zhi = __builtin_amdgcn_readfirstlane(meta[7]) != 0;
     const double h = a.Ldom / (double(int64_t(1) << J) * BS);
     const T ih = T(1.0 / h), ih2 = T(1.0 / (h * h));
-    const int ufs = (int)a.Lu.fstride, vfs = (int)a.Lv.fstride;
-    const int ucol = xin ? xsplit_offset(BS, x, y, 0)
-                         : (a.Lu.ng * a.Lu.P + (y + a.Lu.ng)) * a.Lu.P + (x + a.Lu.ng);
-    const int uzs = xin ? xsplit_zstride(BS, x) : a.Lu.P * a.Lu.P;
-    const int vzs = a.Lv.P * a.Lv.P;
-    const T* __restrict__ ub = a.u + (int64_t)slot * a.Lu.bstride + ucol;
-    const int vcol = (a.Lv.ng * a.Lv.P + (y + a.Lv.ng)) * a.Lv.P + (x + a.Lv.ng);
-    const T* __restrict__ vb = a.v + (int64_t)slot * a.Lv.bstride + vcol;
-    // pointwise operands: uniform block origins, this thread's column offsets
-    // and plane steps in the pool (lam) and in a compact register
+    // uniform block origins; this thread's column offsets and plane steps
+    const T* ub = a.u + (int64_t)slot * a.Lu.bstride;
+    const T* vb = a.v + (int64_t)slot * a.Lv.bstride;
     const T* lb = a.lam + (int64_t)slot * a.Lp.bstride;
     const T* sib = a.sin + (int64_t)slot * a.Lsi.bstride;
     T* sob = a.sout + (int64_t)slot * a.Lso.bstride;
     T* kob = a.kn + (int64_t)slot * a.Lc.bstride;
+    const int ucol = xin ? xsplit_offset(BS, x, y, 0)
+                         : (a.Lu.ng * a.Lu.P + (y + a.Lu.ng)) * a.Lu.P + (x + a.Lu.ng);
+    const int uzs = xin ? xsplit_zstride(BS, x) : a.Lu.P * a.Lu.P;
     const int pcol = (a.Lp.ng * a.Lp.P + (y + a.Lp.ng)) * a.Lp.P + (x + a.Lp.ng);
     const int ccol = y * BS + x;
+    const int vcol = a.Lv.ng ? pcol : ccol;
     const int sicol = a.Lsi.ng ? pcol : ccol, socol = a.Lso.ng ? pcol : ccol;
     // values of this thread's column at depth d below (f = 4) or above (f = 5)
     auto zu = [&](int f, int d, int c) -> T {
@@ -575,11 +578,13 @@ void adj_stage_kernel(AdjStage<T> a) {
     };
     auto zv = [&](int f, int d, int c) -> T {
       const FaceDesc<T>& fz = fv[f];
-      return fz.ptr ? vs * fz.ptr[c * fz.fs + d * fz.sd + x * fz.s0 + y * fz.s1] : T(0);
+      return fz.ptr[c * fz.fs + d * fz.sd + x * fz.s0 + y * fz.s1];
     };
-    // this thread's halo point as an affine map in z: ptr[c fs + z zs]
-    const T *hu = nullptr, *hv = nullptr;
+    // this thread's halo point as an affine map in z: ptr[c fs + z zs]; kb's
+    // value there is hz times the one loaded, or 0
+    const T *hu = a.u, *hv = a.v;
     int hufs = 0, huzs = 0, hvfs = 0, hvzs = 0;
+    bool hnone = false;
     if (hthr) {
       const int hy = hkind < 2 ? y0 + hs : (hkind == 2 ? y0 - 1 - hd : y0 + TY + hd);
       if (hkind < 2 || hy < 0 || hy >= BS) {
@@ -596,9 +601,10 @@ void adj_stage_kernel(AdjStage<T> a) {
           huzs = f1.s1;
         }
         const FaceDesc<T>& f2 = fv[f];
-        if (f2.ptr) hv = f2.ptr + d * f2.sd + s * f2.s0;
+        hv = f2.ptr + d * f2.sd + s * f2.s0;
         hvfs = f2.fs;
         hvzs = f2.s1;
+        hnone = meta[2 + f] != 0;
       } else {  // a row of the block's other tiles
         hu = a.u + point_in(a.Lu, BS, slot, hs, hy, 0);
         hufs = ufs;
@@ -613,35 +619,50 @@ void adj_stage_kernel(AdjStage<T> a) {
     for (int mm = 0; mm < 7; ++mm) {
       const int z = mm - 3;
 #pragma unroll
-      for (int c = 0; c < 4; ++c) q[c][mm] = z < 0 ? zv(4, -1 - z, c) : vs * vb[c * vfs + z * vzs];
+      for (int c = 0; c < 4; ++c) {
+        const T w = z < 0 ? zv(4, -1 - z, c) : vb[vcol + c * vfs + z * vzs];
+        q[c][mm] = z < 0 && zlo ? T(0) : vs * w;
+      }
 #pragma unroll
-      for (int c = 0; c < 3; ++c) q[4 + c][mm] = z < 0 ? zu(4, -1 - z, c) : ub[c * ufs + z * uzs];
+      for (int c = 0; c < 3; ++c)
+        q[4 + c][mm] = z < 0 ? zu(4, -1 - z, c) : ub[ucol + c * ufs + z * uzs];
     }
 #pragma unroll
     for (int c = 0; c < 7; ++c) slab[0][c][cidx] = q[c][3];
     if (hthr) {
 #pragma unroll
-      for (int c = 0; c < 4; ++c) slab[0][c][hli] = hv ? vs * hv[c * hvfs] : T(0);
+      for (int c = 0; c < 4; ++c) slab[0][c][hli] = hnone ? T(0) : vs * hv[c * hvfs];
 #pragma unroll
       for (int c = 0; c < 3; ++c) slab[0][4 + c][hli] = hu[c * hufs];
     }
-    double th[3] = {0, 0, 0};
+    T bad = T(0);  // not 0 if a value of kb is not finite
 #pragma unroll 1
     for (int z = 0; z < BS; ++z) {
       T(*sb)[W * WY] = slab[z & 1];
-      T nq[7], hn[7];
+      T nq[7], hn[7], lv[4], sv[4];
       if (z + 1 < BS) {
-        const int zz = z + 4;
+        if (z + 4 < BS) {
 #pragma unroll
-        for (int c = 0; c < 4; ++c) nq[c] = zz < BS ? vs * vb[c * vfs + zz * vzs] : zv(5, zz - BS, c);
+          for (int c = 0; c < 4; ++c) nq[c] = vb[vcol + c * vfs + (z + 4) * vzs];
 #pragma unroll
-        for (int c = 0; c < 3; ++c) nq[4 + c] = zz < BS ? ub[c * ufs + zz * uzs] : zu(5, zz - BS, c);
+          for (int c = 0; c < 3; ++c) nq[4 + c] = ub[ucol + c * ufs + (z + 4) * uzs];
+        } else {
+#pragma unroll
+          for (int c = 0; c < 4; ++c) nq[c] = zv(5, z + 4 - BS, c);
+#pragma unroll
+          for (int c = 0; c < 3; ++c) nq[4 + c] = zu(5, z + 4 - BS, c);
+        }
         if (hthr) {
 #pragma unroll
-          for (int c = 0; c < 4; ++c) hn[c] = hv ? vs * hv[c * hvfs + (z + 1) * hvzs] : T(0);
+          for (int c = 0; c < 4; ++c) hn[c] = hv[c * hvfs + (z + 1) * hvzs];
 #pragma unroll
           for (int c = 0; c < 3; ++c) hn[4 + c] = hu[c * hufs + (z + 1) * huzs];
         }
+      }
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        sv[c] = sib[sicol + z * sizs + c * (int)a.Lsi.fstride];
+        if (NEXT) lv[c] = lb[pcol + z * pzs + c * (int)a.Lp.fstride];
       }
       lds_barrier();
       const T v[4] = {q[0][3], q[1][3], q[2][3], q[3][3]};
@@ -670,63 +691,19 @@ void adj_stage_kernel(AdjStage<T> a) {
           }
           acc[c] += ih * pr + (nu * ih2) * lap;
           acc[d] -= v[c] * (ih * du);
-          // keep the LDS reads of a field with its arithmetic (hoisted
-          // together they spill)
-          __builtin_amdgcn_sched_barrier(0);
         }
         T dp = T(0);
 #pragma unroll
         for (int m = 0; m < 3; ++m) dp += am[m] * (at(3, m + 1) - at(3, -1 - m));
         acc[d] += c0sq * (ih * dp);
         acc[3] += ih * dv;
-        __builtin_amdgcn_sched_barrier(0);
       }
       acc[3] -= cg * v[3];
-      const int qi = (z * BS + y) * BS + x;
-      if (p.sponge || masked) {
-        const double xg = (double)(meta[2] * BS + x) * h, yg = (double)(meta[3] * BS + y) * h,
-                     zg = (double)(meta[4] * BS + z) * h;
-        if (p.sponge) {
-          const T sp = T(sponge_eval(p, a.Ldom, xg, yg, zg) / p.c_sp);
+      bad += T(0) * (v[0] + v[1] + v[2]);
 #pragma unroll
-          for (int c = 0; c < 4; ++c) acc[c] -= sp * v[c];
-        }
-        if (masked) {
-          double chi, dchi = 0.0, us[3], dsd[3] = {0, 0, 0};
-          if (p.mask == WACM_MASK_PLATE)
-            plate_adj_point(p, pm, xg, yg, zg, chi, dchi, us, dsd);
-          else
-            mask_eval(p, a.t, xg, yg, zg, chi, us);
-          double gal = 0.0, gad = 0.0;
-#pragma unroll
-          for (int c = 0; c < 3; ++c) {
-            const int64_t o = ((int64_t)slot * 3 + c) * B3 + qi;
-            acc[c] -= T(chi / p.c_eta) * v[c];
-            if (a.dusbar) a.dusbar[o] += chi / p.c_eta * (double)v[c];
-            const double e = a.dus ? (double)a.dus[o] : 0.0;
-            gal += -dchi / p.c_eta * ((double)q[4 + c][3] - us[c] - e) * (double)v[c];
-            gad += chi / p.c_eta * dsd[c] * (double)v[c];
-          }
-#pragma unroll
-          for (int k = 0; k < 3; ++k) th[k] += gal * pm.dal[k] + gad * pm.dad[k];
-        }
-      }
-      if (p.mask && !masked) {
-        // 0 times a value that is not finite is not 0
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-          th[c] += 0.0 * (double)v[c];
-          if (a.dusbar && !isfinite(v[c])) a.dusbar[((int64_t)slot * 3 + c) * B3 + qi] += 0.0 * v[c];
-        }
-      }
-      {
-        const int lo = pcol + z * a.Lp.P * a.Lp.P, co = ccol + z * BS * BS;
-        const int sio = sicol + z * a.Lsi.P * a.Lsi.P, soo = socol + z * a.Lso.P * a.Lso.P;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          sob[soo + c * (int)a.Lso.fstride] = sib[sio + c * (int)a.Lsi.fstride] + acc[c];
-          if (a.kn) kob[co + c * B3] = a.lamw * lb[lo + c * (int)a.Lp.fstride] + a.kw * acc[c];
-        }
+      for (int c = 0; c < 4; ++c) {
+        sob[socol + z * sozs + c * (int)a.Lso.fstride] = sv[c] + acc[c];
+        if (NEXT) kob[ccol + z * BS * BS + c * B3] = a.lamw * lv[c] + a.kw * acc[c];
       }
       if (z + 1 < BS) {
         T(*nb_)[W * WY] = slab[(z + 1) & 1];
@@ -734,28 +711,133 @@ void adj_stage_kernel(AdjStage<T> a) {
         for (int c = 0; c < 7; ++c) nb_[c][cidx] = q[c][4];
         if (hthr) {
 #pragma unroll
-          for (int c = 0; c < 7; ++c) nb_[c][hli] = hn[c];
+          for (int c = 0; c < 7; ++c) nb_[c][hli] = c < 4 ? (hnone ? T(0) : vs * hn[c]) : hn[c];
         }
+        const bool none = zhi && z + 4 >= BS;
 #pragma unroll
         for (int c = 0; c < 7; ++c) {
 #pragma unroll
           for (int mm = 0; mm < 6; ++mm) q[c][mm] = q[c][mm + 1];
-          q[c][6] = nq[c];
+          q[c][6] = c < 4 ? (none ? T(0) : vs * nq[c]) : nq[c];
+        }
+      }
+    }
+    if (a.p.mask) {
+      // where the mask is 0 its terms are 0 times kb: not 0 if kb is not finite
+      for (int o = 32; o > 0; o >>= 1) bad += __shfl_xor(bad, o, 64);
+      if ((tid & 63) == 0) red[tid >> 6] = bad;
+      lds_barrier();
+      if (tid == 0) {
+        T s = red[0];
+        for (int w = 1; w < NT / 64; ++w) s += red[w];
+        a.bad[item] = (double)s;
+      }
+    }
+  }
+}
+
+// The pointwise terms of the mask and the sponge, in the blocks they reach:
+// B_c -= chi/C_eta kb_c + sponge kb_c added to the running sum and, weighted,
+// to the next rhs adjoint; the gradients with respect to dus and theta.  Bound
+// by the latency of its loads (21 per point), so a block's planes are dealt to
+// BS / 4 workgroups; a slab needs the plate's factors of its own planes only.
+// Points where every term is 0 are passed over.  NTY: work items of the stage
+// kernel per block.
+constexpr int ADJ_PZ = 4;  // planes per work item
+template <typename T, int BS, int NTY>
+__global__ __launch_bounds__(NT_GEN) void adj_pen_kernel(AdjStage<T> a) {
+  constexpr int B3 = BS * BS * BS, NZ = BS / ADJ_PZ, NQ = ADJ_PZ * BS * BS;
+  __shared__ PlateAdjTab<BS> ptab;
+  __shared__ double red[3][NT_GEN / 64];
+  const wacm_params& p = a.p;
+  const PlateAdjTime pm = plate_adj_time(p, a.t);
+  for (int64_t w = blockIdx.x; w < a.nb * NZ; w += gridDim.x) {
+    const int64_t ib = w / NZ;
+    const int z0 = (int)(w - ib * NZ) * ADJ_PZ;
+    const int32_t* m = a.tab[ib].meta;
+    const int slot = m[0];
+    const int reach = pen_reach(p, a.Ldom, BS, m, pm.ca, pm.sa);  // uniform
+    const bool masked = (reach & 1) != 0, sponged = (reach & 2) != 0;
+    double poison = 0.0;
+    if (p.mask)
+      for (int t = 0; t < NTY; ++t) poison += a.bad[ib * NTY + t];
+    const bool bad = !isfinite(poison);
+    double th[3] = {poison, poison, poison};
+    if (threadIdx.x != 0) th[0] = th[1] = th[2] = 0.0;
+    T* __restrict__ sob = a.sout;
+    T* __restrict__ ko = a.kn + (int64_t)slot * a.Lc.bstride;
+    double* __restrict__ db = a.dusbar + (int64_t)slot * 3 * B3;
+    const T* __restrict__ du = a.dus + (int64_t)slot * 3 * B3;
+    if (reach || bad) {
+      const double h = a.Ldom / (double(int64_t(1) << m[1]) * BS);
+      const bool plate = masked && p.mask == WACM_MASK_PLATE;
+      __syncthreads();  // the last item's factors and partials are free
+      if (plate) plate_adj_tab_fill<BS>(p, pm, m, h, z0, z0 + ADJ_PZ, ptab);
+      __syncthreads();
+      for (int qq = threadIdx.x; qq < NQ; qq += NT_GEN) {
+        const int q = z0 * BS * BS + qq;
+        const int i = q % BS, j = (q / BS) % BS, k = q / (BS * BS);
+        const double xg = (double)(m[2] * BS + i) * h, yg = (double)(m[3] * BS + j) * h,
+                     zg = (double)(m[4] * BS + k) * h;
+        const T sp = sponged ? T(sponge_eval(p, a.Ldom, xg, yg, zg) / p.c_sp) : T(0);
+        double chi = 0.0, dchi = 0.0, us[3] = {0, 0, 0}, dsd[3] = {0, 0, 0};
+        if (plate)
+          plate_adj_tab_point<BS>(p, pm, ptab, i, j, k, xg, zg, chi, dchi, us, dsd);
+        else if (masked)
+          chi = sphere_chi(p, xg, yg, zg);
+        // 0 times a value that is not finite is not 0
+        if (sp == T(0) && chi == 0.0 && dchi == 0.0 && !bad) continue;
+        const int64_t ov = point_in(a.Lv, BS, slot, i, j, k);
+        const int64_t ou = point_in(a.Lu, BS, slot, i, j, k);
+        T* so = sob + point_in(a.Lso, BS, slot, i, j, k);
+        T v[4], u[3], e[3], s0[4], k0[4], acc[4];
+        double d0[3];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          v[c] = a.vs * a.v[ov + c * a.Lv.fstride];
+          s0[c] = so[c * a.Lso.fstride];
+          k0[c] = a.kn ? ko[q + c * B3] : T(0);
+          acc[c] = -sp * v[c];
+        }
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+          u[c] = a.u[ou + c * a.Lu.fstride];
+          e[c] = a.dus ? du[c * B3 + q] : T(0);
+          d0[c] = a.dusbar ? db[c * B3 + q] : 0.0;
+        }
+        if (p.mask) {
+          const double ce = chi / p.c_eta, de = dchi / p.c_eta;
+          double gal = 0.0, gad = 0.0;
+#pragma unroll
+          for (int c = 0; c < 3; ++c) {
+            acc[c] -= T(ce) * v[c];
+            if (a.dusbar) db[c * B3 + q] = d0[c] + ce * (double)v[c];
+            gal += -de * ((double)u[c] - us[c] - (double)e[c]) * (double)v[c];
+            gad += ce * dsd[c] * (double)v[c];
+          }
+          for (int k2 = 0; k2 < 3; ++k2) th[k2] += gal * pm.dal[k2] + gad * pm.dad[k2];
+        }
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          so[c * a.Lso.fstride] = s0[c] + acc[c];
+          if (a.kn) ko[q + c * B3] = k0[c] + a.kw * acc[c];
         }
       }
     }
     if (p.mask) {
+      if (masked || bad) {
 #pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        double s = th[k];
-        for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-        if ((tid & 63) == 0) red[k][tid >> 6] = s;
+        for (int k = 0; k < 3; ++k) {
+          for (int o = 32; o > 0; o >>= 1) th[k] += __shfl_xor(th[k], o, 64);
+          if ((threadIdx.x & 63) == 0) red[k][threadIdx.x >> 6] = th[k];
+        }
+        __syncthreads();
       }
-      __syncthreads();
-      if (tid < 3) {
-        double s = red[tid][0];
-        for (int w = 1; w < NT / 64; ++w) s += red[tid][w];
-        a.part[item * 3 + tid] = s;
+      if (threadIdx.x < 3) {
+        double s = 0.0;
+        if (masked || bad)
+          for (int t = 0; t < NT_GEN / 64; ++t) s += red[threadIdx.x][t];
+        a.part[w * 3 + threadIdx.x] = s;
       }
     }
   }
@@ -930,8 +1012,7 @@ static Layout pool_L(const wacm_grid* g) {
   return L;
 }
 
-static unsigned grid_n(int64_t n) {
-  int64_t cap = 2048;
+static unsigned grid_n(int64_t n, int64_t cap = 2048) {
   return (unsigned)std::max<int64_t>(1, std::min<int64_t>(n, cap));
 }
 
@@ -1006,7 +1087,19 @@ static hipError_t force_adj_t(const wacm_grid* g, const wacm_params* p, double t
   if (g->nb == 0 || !p->mask) return hipSuccess;
   AdjArgs<T> a = adj_args<T>(g, p, t, U, nullptr, Ub, dusbar, dus);
   a.weight = weight;
-  force_adj_kernel<T><<<grid_n(g->nb), NT_GEN, 0, st>>>(a);
+  switch (g->d.bs) {
+    case 16:
+      force_adj_kernel<T, 16><<<grid_n(g->nb), NT_GEN, 0, st>>>(a);
+      break;
+    case 24:
+      force_adj_kernel<T, 24><<<grid_n(g->nb), NT_GEN, 0, st>>>(a);
+      break;
+    case 32:
+      force_adj_kernel<T, 32><<<grid_n(g->nb), NT_GEN, 0, st>>>(a);
+      break;
+    default:
+      return hipErrorInvalidValue;
+  }
   theta_finalize<<<1, NT_GEN, 0, st>>>(g->d_part, g->nb, dtheta);
   return hipGetLastError();
 }
@@ -1023,12 +1116,14 @@ hipError_t launch_force_adj(const wacm_grid* g, const wacm_params* p, double t, 
 
 // Work buffer of one adjoint step (within the 8 pool registers of
 // wacm_adj_work_bytes): the stage inputs Y2, Y3, Y4 (x-split), two rhs
-// adjoints and the running sum (compact), the face halos of the stage input
-// and the face buffer (FP64).
+// adjoints and the running sum (compact), the face halos of the stage input,
+// the face buffer (FP64) and the reduction partials: per slot 24 bs^3 values
+// in the registers and at most 217 bs^2 (FP32) in the rest, of the 32 (bs +
+// 2 ng)^3, ng >= 3, of the pool registers.
 template <typename T>
 struct AdjWork {
   T *y[3], *k[2], *sum, *hb;
-  double* fb;
+  double *fb, *bad, *part;
 };
 template <typename T>
 static AdjWork<T> adj_work(const wacm_grid* g, void* work) {
@@ -1041,16 +1136,19 @@ static AdjWork<T> adj_work(const wacm_grid* g, void* work) {
   r.sum = (T*)(w + 5 * reg);
   r.hb = (T*)(w + 6 * reg);
   r.fb = (double*)(w + 6 * reg + hb);
+  r.bad = r.fb + cap * 72 * bs * bs;
+  r.part = r.bad + cap * 4;  // at most 4 stage items per block
   return r;
 }
 
-template <typename T, int BS, int TY>
-static hipError_t adj_stage_launch(const wacm_grid* g, const AdjStage<T>& a, double* fb,
-                                   hipStream_t st) {
+// the stage itself, grid of as many workgroups as are resident
+template <typename T, int BS, int TY, bool NEXT>
+static void adj_stage_main(const AdjStage<T>& a, hipStream_t st) {
   static const int resident = [] {
     int n = 0, dev = 0, cus = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, adj_stage_kernel<T, BS, TY>, BS * TY, 0) !=
-            hipSuccess || n < 1)
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, adj_stage_kernel<T, BS, TY, NEXT>,
+                                                     BS * TY, 0) != hipSuccess ||
+        n < 1)
       n = 1;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
@@ -1058,13 +1156,28 @@ static hipError_t adj_stage_launch(const wacm_grid* g, const AdjStage<T>& a, dou
       cus = 256;
     return n * cus;
   }();
+  const int64_t items = a.nb * (BS / TY);
+  adj_stage_kernel<T, BS, TY, NEXT>
+      <<<(unsigned)std::min<int64_t>(items, resident), BS * TY, 0, st>>>(a);
+}
+
+// one stage backwards
+template <typename T, int BS, int TY>
+static hipError_t adj_stage_launch(const wacm_grid* g, const AdjStage<T>& a, double* fb,
+                                   double* dtheta, hipStream_t st) {
   const AdjPlan& pl = g->plan[1];
   if (g->n_cface > 0)
     adj_face_kernel<T, BS><<<grid_n(g->n_cface), NT_GEN, 0, st>>>(g->d_tab, g->d_cface,
                                                                   g->n_cface, a, fb);
-  const int64_t items = a.nb * (BS / TY);
-  adj_stage_kernel<T, BS, TY>
-      <<<(unsigned)std::min<int64_t>(items, resident), BS * TY, 0, st>>>(a);
+  if (a.kn)
+    adj_stage_main<T, BS, TY, true>(a, st);
+  else
+    adj_stage_main<T, BS, TY, false>(a, st);
+  if (a.p.mask || a.p.sponge) {
+    const int64_t n = a.nb * (BS / ADJ_PZ);
+    adj_pen_kernel<T, BS, BS / TY><<<grid_n(n, 8192), NT_GEN, 0, st>>>(a);
+    if (a.p.mask) theta_finalize<<<1, NT_GEN, 0, st>>>(a.part, n, dtheta);
+  }
   if (pl.nrows > 0)
     adj_gather_kernel<T><<<grid_n((pl.nrows + NT_GEN - 1) / NT_GEN), NT_GEN, 0, st>>>(
         pl.d_dst, pl.d_ptr, pl.d_src, pl.nrows, BS, fb, a);
@@ -1076,8 +1189,9 @@ static hipError_t adj_stage_launch(const wacm_grid* g, const AdjStage<T>& a, dou
 //   kb_4 = dt/6 lam, kb_3 = dt/3 lam + dt B_4, kb_2 = dt/3 lam + dt/2 B_3,
 //   kb_1 = dt/6 lam + dt/2 B_2, with B_s = S^T J_rhs(U_s)^T kb_s, and
 //   lam_n = lam + B_4 + B_3 + B_2 + B_1.
-// Each stage is three kernels: what the faces next to other levels return
-// (from kb and the input), the stage itself, and the gather of the former.
+// Each stage is four kernels: what the faces next to other levels return
+// (from kb and the input), the stage itself, the mask's and sponge's pointwise
+// terms, and the gather of the former.
 // 1632 blocks of 16^3 (plate), FP32: 17.2 -> 4.5 ms per step.
 template <typename T>
 static hipError_t rk4_adj_t(const wacm_grid* g, const wacm_params* p, double t, double dt,
@@ -1112,7 +1226,8 @@ static hipError_t rk4_adj_t(const wacm_grid* g, const wacm_params* p, double t, 
   a.p = *p;
   a.dus = dus;
   a.dusbar = dusbar;
-  a.part = g->d_part;
+  a.bad = w.bad;
+  a.part = w.part;
   for (int s = 3; s >= 0; --s) {
     a.u = in[s];
     a.Lu = s == 0 ? L : Lx;
@@ -1128,27 +1243,20 @@ static hipError_t rk4_adj_t(const wacm_grid* g, const wacm_params* p, double t, 
     a.lamw = s == 0 ? T(0) : T(lamw[s - 1]);
     a.kw = T(cs[s] * dt);
     if ((e = launch_nlface(g, a.u, a.Lu, w.hb, st)) != hipSuccess) return e;
-    int64_t items = g->nb;
     switch (g->d.bs) {
       case 16:
-        e = adj_stage_launch<T, 16, 16>(g, a, w.fb, st);
+        e = adj_stage_launch<T, 16, 16>(g, a, w.fb, dtheta, st);
         break;
       case 24:
-        e = adj_stage_launch<T, 24, 8>(g, a, w.fb, st);
-        items *= 3;
+        e = adj_stage_launch<T, 24, 8>(g, a, w.fb, dtheta, st);
         break;
       case 32:
-        e = adj_stage_launch<T, 32, 8>(g, a, w.fb, st);
-        items *= 4;
+        e = adj_stage_launch<T, 32, 8>(g, a, w.fb, dtheta, st);
         break;
       default:
         e = hipErrorInvalidValue;
     }
     if (e != hipSuccess) return e;
-    if (p->mask) {
-      theta_finalize<<<1, NT_GEN, 0, st>>>(g->d_part, items, dtheta);
-      if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
   }
   return hipSuccess;
 }

@@ -910,12 +910,20 @@ __global__ __launch_bounds__(NT_GEN) void diag_kernel(const Tab* __restrict__ ta
                                                       wacm_params p, double t,
                                                       double* __restrict__ part) {
   __shared__ double red[NDIAG][NT_GEN];
+  __shared__ PlateTab<bs> ptab;
   constexpr int n3 = bs * bs * bs;
+  const MaskTime mt = mask_time(p, t);
   for (int64_t ib = blockIdx.x; ib < nb; ib += gridDim.x) {
     const int32_t* m = tab[ib].meta;
     const int slot = m[0], J = m[1];
     const double h = Ldom / (double(int64_t(1) << J) * bs);
     const T* b = U + (int64_t)slot * L.bstride;
+    const bool masked = (pen_reach(p, Ldom, bs, m, mt.ca, mt.sa) & 1) != 0;
+    const bool plate = masked && p.mask == WACM_MASK_PLATE;
+    if (plate) {  // uniform; the last block's reduction has ended
+      plate_tab_fill<bs>(p, mt, m, h, ptab);
+      __syncthreads();
+    }
     double acc[NDIAG] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
     for (int q = threadIdx.x; q < n3; q += NT_GEN) {
       const int i = q % bs, j = (q / bs) % bs, k = q / (bs * bs);
@@ -926,13 +934,23 @@ __global__ __launch_bounds__(NT_GEN) void diag_kernel(const Tab* __restrict__ ta
       const double m2 = u[0] * u[0] + u[1] * u[1] + u[2] * u[2];
       acc[0] = fmax(acc[0], m2);
       for (int c = 0; c < 4; ++c) acc[1 + c] = fmax(acc[1 + c], fabs(u[c]));
-      if (p.mask) {
-        double chi, us[3];
-        mask_eval(p, t, (double)(m[2] * bs + i) * h, (double)(m[3] * bs + j) * h,
-                  (double)(m[4] * bs + k) * h, chi, us);
+      if (masked) {
+        const double xg = (double)(m[2] * bs + i) * h, yg = (double)(m[3] * bs + j) * h,
+                     zg = (double)(m[4] * bs + k) * h;
+        double chi, us[3] = {0.0, 0.0, 0.0};
+        if (plate) {
+          chi = plate_tab_chi<bs>(p, ptab, i, j, k);
+          us[0] = mt.ad * (zg - p.x_le[2]);
+          us[2] = -mt.ad * (xg - p.x_le[0]);
+        } else {
+          chi = sphere_chi(p, xg, yg, zg);
+        }
         if (dus)
           for (int d = 0; d < 3; ++d) us[d] += (double)dus[((int64_t)slot * 3 + d) * n3 + q];
         for (int d = 0; d < 3; ++d) acc[5 + d] += chi * (u[d] - us[d]);
+      } else if (p.mask) {
+        // chi is 0; 0 times a value that is not finite is not
+        for (int d = 0; d < 3; ++d) acc[5 + d] += 0.0 * u[d];
       }
       acc[8] += m2;
     }
@@ -1028,6 +1046,7 @@ __global__ __launch_bounds__(BS* BS) void detail_kernel(const Tab* __restrict__ 
   constexpr int NT = BS * BS;
   __shared__ T xp[2][4][S * BS];
   __shared__ double red[10][NT / 64];
+  __shared__ PlateTab<BS> ptab;
   const T w0 = T(DDW0), w1 = T(DDW1);
   const int tid = threadIdx.x;
   const int i = tid % BS, j = tid / BS;
@@ -1041,17 +1060,21 @@ __global__ __launch_bounds__(BS* BS) void detail_kernel(const Tab* __restrict__ 
   };
   double cmin = 1e300, cmax = -1e300;
   if (p.mask) {
-    wacm_params pm = p;
-    pm.sponge = 0;
-    if (pen_far(pm, Ldom, BS, m, pitch_window(p, t, t))) {
+    const MaskTime mt = mask_time(p, t);
+    if (!(pen_reach(p, Ldom, BS, m, mt.ca, mt.sa) & 1)) {
       cmin = cmax = 0.0;  // the mask is exactly 0 on the whole block
     } else {
-      const MaskTime mt = mask_time(p, t);
       const double h = Ldom / (double(int64_t(1) << m[1]) * BS);
+      const bool plate = p.mask == WACM_MASK_PLATE;
+      if (plate) {
+        plate_tab_fill<BS>(p, mt, m, h, ptab);
+        __syncthreads();
+      }
       for (int k = 0; k < BS; ++k) {
-        double chi, us[3];
-        mask_point(p, mt, (double)(m[2] * BS + i) * h, (double)(m[3] * BS + j) * h,
-                   (double)(m[4] * BS + k) * h, chi, us);
+        const double chi = plate ? plate_tab_chi<BS>(p, ptab, i, j, k)
+                                 : sphere_chi(p, (double)(m[2] * BS + i) * h,
+                                              (double)(m[3] * BS + j) * h,
+                                              (double)(m[4] * BS + k) * h);
         cmin = fmin(cmin, chi);
         cmax = fmax(cmax, chi);
       }

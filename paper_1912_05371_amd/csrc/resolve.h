@@ -335,15 +335,15 @@ WACM_HD inline PitchWindow pitch_window(const wacm_params& p, double t0, double 
 // every interior point (at every time, or at every time of the window), so
 // the penalization terms of the rhs vanish exactly there and the
 // unpenalized stage kernel gives the same values.  Conservative tests, with
-// a margin of 40 w beyond the body where every tanh of the smoothed mask
-// (Sec. 2.2) is exactly +-1 in FP64; with clipping (chi < 1e-8 set to 0)
+// a margin of 20 w beyond the body where every tanh of the smoothed mask
+// (Sec. 2.2) is exactly +-1 in FP64 (1 - tanh 20 < 9e-18); with clipping (chi < 1e-8 set to 0)
 // 12 w suffice: beyond it one tanh factor of the mask stays below 4e-11.
 //  - sphere: the distance from the centre to the block's point box exceeds
-//    R + 40 w;
+//    R + 20 w;
 //  - plate, any angle: either the block's y points miss the span widened by
-//    40 w, or their distance from the pitch axis (x and z relative to x_le; a
+//    20 w, or their distance from the pitch axis (x and z relative to x_le; a
 //    rotation about the axis keeps it) exceeds the farthest corner of the
-//    chord x thickness rectangle widened by 40 w;
+//    chord x thickness rectangle widened by 20 w;
 //  - plate, angles of a window: or the body-frame chord or thickness
 //    coordinate of every point of the box, at every angle of the window,
 //    misses the widened rectangle's range: bounded by its value at the box
@@ -362,7 +362,7 @@ WACM_HD inline bool pen_far(const wacm_params& p, double L, int bs, const int32_
   if (p.sponge)
     for (int d = 0; d < 3; ++d)
       if (!(lo[d] >= p.l_sp && hi[d] <= L - p.l_sp)) return false;
-  const double mg = (p.clip ? 12.0 : 40.0) * p.w;
+  const double mg = (p.clip ? 12.0 : 20.0) * p.w;
   if (p.mask == WACM_MASK_SPHERE) {
     double s = 0.0;
     for (int d = 0; d < 3; ++d) {

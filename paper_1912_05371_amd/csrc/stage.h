@@ -2,6 +2,8 @@
 // with a depth-3 halo: the fused rhs + RK stage and its adjoint.
 #pragma once
 
+#include <type_traits>
+
 #include "resolve.h"
 #include "wacm_internal.h"
 
@@ -46,6 +48,130 @@ struct BlockIter {
     }
   }
 };
+
+// The plate's mask on a block, by factors.  In the body frame the box's x and
+// z coordinates depend on (x, z) of the point alone and its y coordinate on y
+// alone, so a block has BS^2 + BS factor values for its BS^3 points: a
+// workgroup evaluates them once into LDS (4 tanh per thread of a whole block
+// instead of 6 per point, FP64 tanh being what bounded the kernels with a
+// mask) and forms chi = f0 f1 f2 per point, in mask_point's order.
+template <int BS>
+struct PlateTab {
+  double f0[BS * BS], f2[BS * BS];  // [z][x]
+  double f1[BS];
+};
+struct NoTab {};
+
+// tanh of FP64 is +-1 exactly from |x| = 20 on (1 - tanh x < 9e-18, a
+// twelfth of the last place); whole waves often lie there
+__device__ __forceinline__ double tanh_sat(double x) {
+  double r = copysign(1.0, x);
+  if (!(fabs(x) >= 20.0)) r = tanh(x);
+  return r;
+}
+
+// the sphere's mask at a point, as mask_point evaluates it
+__device__ __forceinline__ double sphere_chi(const wacm_params& p, double x, double y, double z) {
+  const double dx = x - p.sph_c[0], dy = y - p.sph_c[1], dz = z - p.sph_c[2];
+  const double d = sqrt(dx * dx + dy * dy + dz * dz) - p.sph_r;
+  const double chi = 0.5 * (1.0 - tanh_sat(d / p.w));
+  return p.clip && chi < 1e-8 ? 0.0 : chi;
+}
+
+__device__ __forceinline__ double box_factor(double b, double lo, double hi, double w) {
+  return 0.5 * (tanh_sat((b - lo) / w) - tanh_sat((b - hi) / w));
+}
+
+template <int BS>
+__device__ __forceinline__ void plate_tab_fill(const wacm_params& p, const MaskTime& mt,
+                                               const int32_t* meta, double h, PlateTab<BS>& t) {
+  for (int q = threadIdx.x; q < BS * BS; q += blockDim.x) {
+    const int x = q % BS, z = q / BS;
+    const double rx = (double)(meta[2] * BS + x) * h - p.x_le[0];
+    const double rz = (double)(meta[4] * BS + z) * h - p.x_le[2];
+    t.f0[q] = box_factor(mt.ca * rx - mt.sa * rz, p.lo[0], p.hi[0], p.w);
+    t.f2[q] = box_factor(mt.sa * rx + mt.ca * rz, p.lo[2], p.hi[2], p.w);
+  }
+  for (int y = threadIdx.x; y < BS; y += blockDim.x)
+    t.f1[y] = box_factor((double)(meta[3] * BS + y) * h - p.x_le[1], p.lo[1], p.hi[1], p.w);
+}
+
+template <int BS>
+__device__ __forceinline__ double plate_tab_chi(const wacm_params& p, const PlateTab<BS>& t,
+                                                int x, int y, int z) {
+  double chi = t.f0[z * BS + x];
+  chi *= t.f1[y];
+  chi *= t.f2[z * BS + x];
+  return p.clip && chi < 1e-8 ? 0.0 : chi;
+}
+
+// The same with each factor's derivative in its body coordinate (adjoint).
+template <int BS>
+struct PlateAdjTab {
+  double f0[BS * BS], f2[BS * BS], g0[BS * BS], g2[BS * BS];  // [z][x]
+  double f1[BS];
+};
+
+__device__ __forceinline__ void box_factor_adj(double b, double lo, double hi, double w,
+                                               double& f, double& g) {
+  const double ta = tanh_sat((b - lo) / w), tb = tanh_sat((b - hi) / w);
+  f = 0.5 * (ta - tb);
+  g = 0.5 * ((1.0 - ta * ta) - (1.0 - tb * tb)) / w;
+}
+
+template <int BS>
+__device__ __forceinline__ void plate_adj_tab_fill(const wacm_params& p, const PlateAdjTime& m,
+                                                   const int32_t* meta, double h, int z0, int z1,
+                                                   PlateAdjTab<BS>& t) {
+  for (int q = z0 * BS + threadIdx.x; q < z1 * BS; q += blockDim.x) {  // planes z0..z1-1
+    const int x = q % BS, z = q / BS;
+    const double rx = (double)(meta[2] * BS + x) * h - p.x_le[0];
+    const double rz = (double)(meta[4] * BS + z) * h - p.x_le[2];
+    box_factor_adj(m.ca * rx - m.sa * rz, p.lo[0], p.hi[0], p.w, t.f0[q], t.g0[q]);
+    box_factor_adj(m.sa * rx + m.ca * rz, p.lo[2], p.hi[2], p.w, t.f2[q], t.g2[q]);
+  }
+  for (int y = threadIdx.x; y < BS; y += blockDim.x)
+    t.f1[y] = box_factor((double)(meta[3] * BS + y) * h - p.x_le[1], p.lo[1], p.hi[1], p.w);
+}
+
+// chi, its derivative in the pitch angle (the body frame turns about y: d b0 =
+// -b2, d b2 = b0) and the solid velocity with its derivative in the pitch rate
+template <int BS>
+__device__ __forceinline__ void plate_adj_tab_point(const wacm_params& p, const PlateAdjTime& m,
+                                                    const PlateAdjTab<BS>& t, int x, int y, int z,
+                                                    double xg, double zg, double& chi,
+                                                    double& dchi, double us[3], double dusd[3]) {
+  const int q = z * BS + x;
+  const double rx = xg - p.x_le[0], rz = zg - p.x_le[2];
+  const double b0 = m.ca * rx - m.sa * rz, b2 = m.sa * rx + m.ca * rz;
+  const double f0 = t.f0[q], f1 = t.f1[y], f2 = t.f2[q];
+  chi = f0 * f1 * f2;
+  dchi = t.g0[q] * -b2 * f1 * f2 + f0 * f1 * t.g2[q] * b0;
+  if (p.clip && chi < 1e-8) {
+    chi = 0.0;
+    dchi = 0.0;
+  }
+  us[0] = m.ad * rz;
+  us[1] = 0.0;
+  us[2] = -m.ad * rx;
+  dusd[0] = rz;
+  dusd[1] = 0.0;
+  dusd[2] = -rx;
+}
+
+// Whether the mask (bit 0) and the sponge (bit 1) reach a block at the time
+// whose pitch angle has cosine ca and sine sa: elsewhere they are exactly 0
+// at every point (pen_far).
+__device__ __forceinline__ int pen_reach(const wacm_params& p, double L, int bs,
+                                         const int32_t* meta, double ca, double sa) {
+  wacm_params q = p;
+  q.sponge = 0;
+  int r = p.mask && !pen_far(q, L, bs, meta, PitchWindow{ca, sa, 1e-9, true}) ? 1 : 0;
+  q.mask = 0;
+  q.sponge = p.sponge;
+  if (p.sponge && !pen_far(q, L, bs, meta, PitchWindow{ca, sa, 1e-9, true})) r |= 2;
+  return r;
+}
 
 // Where the depth-3 halo of one face of the current block lives: element
 // (field c, depth d away from the face, tangential t0 < t1 by axis order) is
