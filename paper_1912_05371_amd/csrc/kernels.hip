@@ -4,6 +4,7 @@
 // registers in the same padded layout or compact (bs^3 per field), and the
 // per-block neighbour tables (Tab) built on the host.  All kernels are
 // memory-bound stencils: no MFMA; wave64 reductions; LDS slabs.
+#include <algorithm>
 #include <cmath>
 #include <mutex>
 
@@ -12,22 +13,6 @@
 #include "wacm_internal.h"
 
 namespace wacm {
-
-template <typename T>
-__device__ __forceinline__ T wave_max(T v) {
-  for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
-  return v;
-}
-// |u|^2 in FP64 with one fixed operation order: the maximum fused into the
-// last RK4 stage and the stand-alone reduction agree bit for bit.
-__device__ __forceinline__ double speed2(double u, double v, double w) {
-  return __builtin_fma(w, w, __builtin_fma(v, v, u * u));
-}
-template <typename T>
-__device__ __forceinline__ T wave_min(T v) {
-  for (int o = 32; o > 0; o >>= 1) v = fmin(v, __shfl_xor(v, o, 64));
-  return v;
-}
 
 // --------------------------------------------------------------------------
 // ghost synchronisation
@@ -250,434 +235,6 @@ __global__ __launch_bounds__(NT_GEN) void sync_coarser_kernel(const Tab* __restr
 // --------------------------------------------------------------------------
 // fused rhs + RK4 stage (Sec. 2.2-2.3)
 // --------------------------------------------------------------------------
-template <typename T>
-struct StageArgs {
-  const Tab* tab;
-  int64_t nb;
-  const T* in;  // stage input register
-  Layout Lin;
-  const T* hb;  // halo buffer of faces next to other levels [slot][6][4][3][bs][bs]
-  T* un;        // U^n register (the pool)
-  Layout Lun;
-  T* acc;  // accumulator (compact)
-  Layout Lacc;
-  T* out;  // next stage input, or dU for the rhs-only mode
-  Layout Lout;
-  const T* dus;  // extra solid velocity [slot][3][bs^3] or null
-  const double* t_dev;  // step time and size on the device, or null:
-  const double* dt_dev;  // t_host and dt_host
-  double* umax_part;  // stage 4: per work item max |u|^2 of the new U^n, or null
-  // optional block list: the blocks of this launch are blist[off + i],
-  // i < bcnt[bsel], off = bsel ? bcnt[0] : 0 (the list holds the blocks
-  // without penalization first, then the others; null: every block)
-  const int32_t* blist;
-  const int32_t* bcnt;
-  int bsel;
-  double t_host;
-  double dt_host;
-  double kscale;  // MODE 3: out = U^n + kscale dt k (1; 1/2 gives stage 2 without W)
-  double L;
-  int xcd_map;  // 1: give each XCD a contiguous run of work items
-  int* queue;   // xcd_map 2: per-XCD work counters (QSTRIDE apart), zero at launch
-  int nt;       // 1: non-temporal loads/stores of the streaming operands
-  wacm_params p;
-};
-
-// Dynamic per-XCD work queues (xcd_map 2): the Morton-ordered items are cut
-// into 8 contiguous chunks, one per XCD; workgroup w (on XCD w % 8) takes the
-// next item of its own chunk from that chunk's counter, so the tiles of one
-// block and neighbouring blocks run together on one L2, and when its chunk is
-// empty it takes items from the following chunks, so no XCD idles while
-// another still has work.  Each counter increment that finds a chunk empty
-// moves on to the next chunk: at most 8 misses per workgroup, so every
-// workgroup ends.  Thread 0 only.
-constexpr int QSTRIDE = 32;  // ints between counters: one 128-byte line each
-__device__ __forceinline__ int queue_take(int* ctr, int& q, int chunk, int n, int v) {
-  for (int miss = 0;;) {
-    const int lo = q * chunk;
-    const int hi = lo + chunk < n ? lo + chunk : n;
-    if (lo + v < hi) return lo + v;
-    if (++miss == 8) return n;
-    q = (q + 1) & 7;
-    v = atomicAdd(ctr + q * QSTRIDE, 1);
-  }
-}
-
-__global__ void queue_clear(int* ctr) {
-  if (threadIdx.x < 8 * QSTRIDE) ctr[threadIdx.x] = 0;
-}
-
-// MODE 0: dU = rhs(U) with U's own ghost layers.  MODE s = 1..4: classical
-// RK4 stage s with registers U^n, W and the stage inputs Y_s:
-//   s1: out = Y2 = U^n + dt/2 k1                    (input = U^n)
-//   s2: out = Y3 = U^n + dt/2 k2,  W = (U^n + Y2)/3 + dt/3 k2
-//   s3: out = Y4 = U^n + dt k3
-//   s4: U^{n+1} = W + Y4/3 + dt/6 k4
-// Since dt k1 = 2 (Y2 - U^n) and dt k3 = Y4 - U^n, the update
-// U^n + dt/6 (k1 + 2 k2 + 2 k3 + k4) equals W + Y4/3 + dt/6 k4 with
-// W = 2/3 U^n + dt/6 k1 + dt/3 k2: only stage 2 writes a second register and
-// stages 3 and 4 read one besides their input (same values up to rounding of
-// U^n's size).
-// PEN: penalization/sponge terms present.  PREF: load the epilogue operands
-// (U^n, acc) before the barrier instead of after the rhs.  Work items are
-// tiles of TY rows of a block's (x,y) columns (TY = BS: the whole block), one
-// persistent workgroup per item at a time, one thread per column marching in
-// z: z-neighbours in a register queue, the x/y cross of the current plane in a
-// double-buffered LDS slab, the next plane's loads issued before the barrier.
-// Rows between tiles of one block are read from the block itself.
-// Occupancy: FP64 tiles are held to 2 waves per SIMD, FP32 tiles to 3; a
-// whole bs-16 block (4 waves) to 2 per SIMD, which keeps two workgroups per
-// CU for the penalized FP64 variant at the cost of a few spills (measured
-// faster than one workgroup per CU without spills).
-// MODEX = MODE (0 rhs only, 1..4 RK stage) or 10 + MODE: the RK stage with
-// every register in the padded pool layout, same-level halos read from the
-// neighbours' interiors and the others from the input's own synchronised
-// ghost layers (the lifted-wavelet step).
-template <typename T, int BS, int TY, int MODEX, bool PEN, bool PREF>
-__global__ __launch_bounds__(BS* TY) __attribute__((amdgpu_waves_per_eu(TY == BS ? (BS == 16 ? 2 : 1) : (sizeof(T) == 8 ? 2 : 3))))
-void stage_kernel(StageArgs<T> a) {
-  constexpr int H = 3, W = BS + 2 * H, WY = TY + 2 * H, NT = BS * TY;
-  constexpr int NTY = BS / TY, NH = 6 * TY + 6 * BS;
-  static_assert(NH <= NT || TY == BS, "halo points per plane exceed the threads");
-  constexpr int MODE = MODEX % 10;
-  constexpr bool OWNG = MODEX >= 10;
-  constexpr int HALO = OWNG ? HALO_MIX : (MODE == 0 ? HALO_OWN : HALO_NB);
-  // the stage registers between stages are x-split; U^n is the pool or, from
-  // the second step of a multi-step call on, an x-split register too
-  const bool xin = !OWNG && (MODE >= 2 || (MODE == 1 && a.Lin.xs != 0));
-  const bool xun = MODE >= 2 && a.Lun.xs != 0;
-  constexpr bool XOUT = !OWNG && MODE >= 1 && MODE <= 3;
-  __shared__ T slab[2][4][W * WY];
-  __shared__ FaceDesc<T> fds[6];
-  __shared__ int32_t meta[5];
-  __shared__ double red[NT / 64];
-  __shared__ int qitem;
-  const int tid = threadIdx.x;
-  const int x = tid % BS, yl = tid / BS;
-  const T a1 = T(TW1), a2 = T(TW2), a3 = T(TW3);
-  const T c2a = T(D2A), c2b = T(D2B), c2c = T(D2C);
-  double tc = a.t_host, dt = 0.0;
-  if (MODE != 0) {
-    if (a.t_dev) tc = *a.t_dev;
-    dt = a.dt_dev ? *a.dt_dev : a.dt_host;
-  }
-  const T nu = T(a.p.nu), c0sq = T(a.p.c0 * a.p.c0), cg = T(a.p.c_gamma);
-  const T fA = T(MODE == 4 ? dt / 6.0 : dt / 3.0);  // k weight of W (s2) and of U^{n+1} (s4)
-  // the stage time and what of the mask depends on it alone
-  const double ts = tc + (MODE == 2 || MODE == 3 ? 0.5 * dt : (MODE == 4 ? dt : 0.0));
-  const MaskTime mt = PEN && a.p.mask ? mask_time(a.p, ts) : MaskTime{1.0, 0.0, 0.0};
-  const T fB = T(MODE == 3 ? a.kscale * dt : 0.5 * dt);
-  const int fin = (int)a.Lin.fstride, Pi = a.Lin.P;
-  const int cidx = (yl + H) * W + (x + H);
-  // this thread's halo point of every plane (threads < NH): x-faces of the
-  // tile's rows, then the 3 rows below and above the tile
-  const bool hthr = tid < NH;
-  int hkind = 0, hd = 0, hs = 0, hli = 0;  // hkind: 0..3 face x-,x+,below,above
-  if (hthr) {
-    if (tid < 6 * TY) {
-      hkind = tid / (3 * TY);
-      const int rem = tid - hkind * 3 * TY;
-      hd = rem / TY;
-      hs = rem - hd * TY;
-      const int hx = hkind == 0 ? -1 - hd : BS + hd;
-      hli = (hs + H) * W + (hx + H);
-    } else {
-      const int q = tid - 6 * TY;
-      hkind = 2 + q / (3 * BS);
-      const int rem = q - (hkind - 2) * 3 * BS;
-      hd = rem / BS;
-      hs = rem - hd * BS;
-      const int hyl = hkind == 2 ? -1 - hd : TY + hd;
-      hli = (hyl + H) * W + (hs + H);
-    }
-  }
-  // plane steps of this thread's column
-  const int zs = xin ? xsplit_zstride(BS, x) : Pi * Pi;
-  const int azs = a.Lacc.P * a.Lacc.P, afs = (int)a.Lacc.fstride;
-  const int uzs = xun ? xsplit_zstride(BS, x) : a.Lun.P * a.Lun.P, ufs = (int)a.Lun.fstride;
-  const int ozs = XOUT ? xsplit_zstride(BS, x) : a.Lout.P * a.Lout.P;
-  const int ofs = (int)a.Lout.fstride;
-
-  // work items: static (round-robin or contiguous per XCD) or from the
-  // per-XCD queues, whose next item thread 0 requests while the current one
-  // is processed and publishes in qitem before the loop's first barrier
-  int64_t nblk = a.nb, boff = 0;
-  if (a.blist) {
-    boff = a.bsel ? a.bcnt[0] : 0;
-    nblk = a.bcnt[a.bsel];
-  }
-  const int64_t nitems = nblk * NTY;
-  const bool dyn = a.queue != nullptr;
-  BlockIter it(nitems, a.xcd_map);
-  int qh = blockIdx.x & 7, qpend = 0;
-  const int qchunk = (int)((nitems + 7) / 8);
-  if (dyn && tid == 0) qitem = queue_take(a.queue, qh, qchunk, (int)nitems,
-                                          atomicAdd(a.queue + qh * QSTRIDE, 1));
-  for (;;) {
-    lds_barrier();
-    const int64_t item = dyn ? (int64_t)__builtin_amdgcn_readfirstlane(qitem) : it.ib;
-    if (item >= (dyn ? nitems : it.end)) break;
-    if (!dyn) it.ib += it.step;
-    const int64_t il = item / NTY;
-    const int64_t ibk = a.blist ? a.blist[boff + il] : il;
-    const int y0 = (int)(item - il * NTY) * TY;
-    const int y = y0 + yl;
-    if (tid < 6) fds[tid] = face_desc<T, BS, HALO>(a.tab[ibk], a.in, a.Lin, a.hb, tid, xin);
-    if (tid < 5) meta[tid] = a.tab[ibk].meta[tid];
-    lds_barrier();
-    if (dyn && tid == 0) qpend = atomicAdd(a.queue + qh * QSTRIDE, 1);
-    // offsets of this thread's column in the input, accumulator and U^n
-    const int col = xin ? xsplit_offset(BS, x, y, 0)
-                        : (a.Lin.ng * Pi + (y + a.Lin.ng)) * Pi + (x + a.Lin.ng);
-    const int acol = (a.Lacc.ng * a.Lacc.P + (y + a.Lacc.ng)) * a.Lacc.P + (x + a.Lacc.ng);
-    const int ucol = xun ? xsplit_offset(BS, x, y, 0)
-                         : (a.Lun.ng * a.Lun.P + (y + a.Lun.ng)) * a.Lun.P + (x + a.Lun.ng);
-    const int ocol = XOUT ? xsplit_offset(BS, x, y, 0)
-                          : (a.Lout.ng * a.Lout.P + (y + a.Lout.ng)) * a.Lout.P + (x + a.Lout.ng);
-    // uniform over the workgroup: scalar registers
-    const int slot = __builtin_amdgcn_readfirstlane(meta[0]);
-    const int J = __builtin_amdgcn_readfirstlane(meta[1]);
-    const double hdd = a.L / (double(int64_t(1) << J) * BS);
-    const T ih = T(1.0 / hdd), ih2 = T(1.0 / (hdd * hdd));
-    const T* __restrict__ inb = a.in + (int64_t)slot * a.Lin.bstride + col;
-    T* accb = a.acc + (int64_t)slot * a.Lacc.bstride + acol;
-    T* unb = a.un + (int64_t)slot * a.Lun.bstride + ucol;
-    T* outb = a.out + (int64_t)slot * a.Lout.bstride + ocol;
-    // field c of this thread's column at depth d below (f = 4) or above
-    // (f = 5) the block; the descriptor is re-read from LDS at each use
-    auto zface = [&](int f, int d, int c) -> T {
-      const FaceDesc<T>& fz = fds[f];
-      if (xin && fz.mode == 1) return fz.ptr[c * fin + col + (f == 4 ? BS - 1 - d : d) * zs];
-      return fz.ptr[c * fz.fs + d * fz.sd + x * fz.s0 + y * fz.s1];
-    };
-    // this thread's halo point as an affine map in z: hp[c hfs + z hzs]
-    const T* hp = nullptr;
-    int hfs = 0, hzs = 0;
-    if (hthr) {
-      if (hkind < 2) {
-        const FaceDesc<T>& fh = fds[hkind];
-        hp = fh.ptr + hd * fh.sd + (y0 + hs) * fh.s0;
-        hfs = fh.fs;
-        hzs = fh.s1;
-      } else {
-        const int hy = hkind == 2 ? y0 - 1 - hd : y0 + TY + hd;
-        if (hy < 0 || hy >= BS) {
-          const FaceDesc<T>& fh = fds[hy < 0 ? 2 : 3];
-          if (xin && fh.mode == 1) {
-            hp = fh.ptr + xsplit_offset(BS, hs, hy < 0 ? BS + hy : hy - BS, 0);
-            hfs = fin;
-            hzs = xsplit_zstride(BS, hs);
-          } else {
-            hp = fh.ptr + (hy < 0 ? -1 - hy : hy - BS) * fh.sd + hs * fh.s0;
-            hfs = fh.fs;
-            hzs = fh.s1;
-          }
-        } else if (xin) {
-          hp = a.in + (int64_t)slot * a.Lin.bstride + xsplit_offset(BS, hs, hy, 0);
-          hfs = fin;
-          hzs = xsplit_zstride(BS, hs);
-        } else {
-          hp = a.in + (int64_t)slot * a.Lin.bstride +
-               (a.Lin.ng * Pi + (hy + a.Lin.ng)) * Pi + (hs + a.Lin.ng);
-          hfs = fin;
-          hzs = Pi * Pi;
-        }
-      }
-    }
-
-    double m2 = 0.0;  // stage 4: max |u|^2 of this thread's new points
-    // mask, solid velocity and sponge of this thread's point of the next
-    // plane, evaluated at the end of the previous plane where fewer values
-    // are live
-    T pchi = T(0), psp = T(0), pus[3] = {T(0), T(0), T(0)};
-    auto pen_at = [&](int zz) {
-      const double xg = (double)(meta[2] * BS + x) * hdd, yg = (double)(meta[3] * BS + y) * hdd,
-                   zg = (double)(meta[4] * BS + zz) * hdd;
-      if (a.p.mask) {
-        double cd, u3[3];
-        mask_point(a.p, mt, xg, yg, zg, cd, u3);
-        pchi = T(cd);
-        pus[0] = T(u3[0]);
-        pus[1] = T(u3[1]);
-        pus[2] = T(u3[2]);
-      }
-      if (a.p.sponge) psp = T(sponge_eval(a.p, a.L, xg, yg, zg));
-    };
-    if (PEN) pen_at(0);
-    T q[4][7];
-#pragma unroll
-    for (int mm = 0; mm < 7; ++mm) {
-      const int z = mm - 3;
-#pragma unroll
-      for (int c = 0; c < 4; ++c)
-        q[c][mm] = z < 0 ? zface(4, -1 - z, c) : inb[c * fin + z * zs];
-    }
-    // plane 0 into slab 0
-#pragma unroll
-    for (int c = 0; c < 4; ++c) slab[0][c][cidx] = q[c][3];
-    if (hthr) {
-#pragma unroll
-      for (int c = 0; c < 4; ++c) slab[0][c][hli] = hp[c * hfs];
-    }
-
-    for (int z = 0; z < BS; ++z) {
-      T(*sb)[W * WY] = slab[z & 1];
-      // loads for the next plane: column value at z+4 and this thread's halo point
-      T nq[4], hnx[4];
-      if (z + 1 < BS) {
-        const int zz = z + 4;
-#pragma unroll
-        for (int c = 0; c < 4; ++c)
-          nq[c] = zz < BS ? inb[c * fin + zz * zs] : zface(5, zz - BS, c);
-        if (hthr) {
-#pragma unroll
-          for (int c = 0; c < 4; ++c) hnx[c] = hp[c * hfs + (z + 1) * hzs];
-        }
-      }
-      // epilogue operands of this point, loaded early if PREF
-      T unv[4], acv[4];
-      if (PREF) {
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          if (MODE == 2 || MODE == 3) unv[c] = ntload(unb + c * ufs + z * uzs, a.nt);
-          if (MODE == 4) acv[c] = ntload(accb + c * afs + z * azs, a.nt);
-        }
-      }
-      lds_barrier();
-
-      // rhs, accumulated field by field
-      const T u = q[0][3], v = q[1][3], w = q[2][3], pr = q[3][3];
-      T r[4], div = T(0);
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        const T* s = sb[c];
-        const T dx = (a1 * (s[cidx + 1] - s[cidx - 1]) + a2 * (s[cidx + 2] - s[cidx - 2]) +
-                      a3 * (s[cidx + 3] - s[cidx - 3])) *
-                     ih;
-        const T dy = (a1 * (s[cidx + W] - s[cidx - W]) + a2 * (s[cidx + 2 * W] - s[cidx - 2 * W]) +
-                      a3 * (s[cidx + 3 * W] - s[cidx - 3 * W])) *
-                     ih;
-        const T dz = (a1 * (q[c][4] - q[c][2]) + a2 * (q[c][5] - q[c][1]) +
-                      a3 * (q[c][6] - q[c][0])) *
-                     ih;
-        if (c < 3) {
-          const T lap = ((c2a * s[cidx - 2] + c2b * s[cidx - 1] + c2c * s[cidx] +
-                          c2b * s[cidx + 1] + c2a * s[cidx + 2]) +
-                         (c2a * s[cidx - 2 * W] + c2b * s[cidx - W] + c2c * s[cidx] +
-                          c2b * s[cidx + W] + c2a * s[cidx + 2 * W]) +
-                         (c2a * q[c][1] + c2b * q[c][2] + c2c * q[c][3] + c2b * q[c][4] +
-                          c2a * q[c][5])) *
-                        ih2;
-          r[c] = -(u * dx + v * dy + w * dz) + nu * lap;
-          div += c == 0 ? dx : (c == 1 ? dy : dz);
-        } else {
-          r[0] -= dx;
-          r[1] -= dy;
-          r[2] -= dz;
-        }
-      }
-      r[3] = -c0sq * div - cg * pr;
-      if (PEN) {
-        const wacm_params& p = a.p;
-        T chi = pchi, sp = psp, us[3] = {pus[0], pus[1], pus[2]};
-        if (a.dus) {
-          const T* du = a.dus + (int64_t)slot * 3 * BS * BS * BS + (z * BS + y) * BS + x;
-          us[0] += du[0];
-          us[1] += du[BS * BS * BS];
-          us[2] += du[2 * BS * BS * BS];
-        }
-        const T iceta = p.mask ? T(1.0 / p.c_eta) : T(0), icsp = p.sponge ? T(1.0 / p.c_sp) : T(0);
-        const T val[4] = {u, v, w, pr};
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-          if (p.mask) r[c] -= chi * iceta * (val[c] - us[c]);
-          if (p.sponge) r[c] -= sp * icsp * (val[c] - T(p.u_inf[c]));
-        }
-        if (p.sponge) r[3] -= sp * icsp * (pr - T(p.p_inf));
-      }
-
-      if (!PREF) {
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          if (MODE == 2 || MODE == 3) unv[c] = ntload(unb + c * ufs + z * uzs, a.nt);
-          if (MODE == 4) acv[c] = ntload(accb + c * afs + z * azs, a.nt);
-        }
-      }
-      if (MODE == 0) {
-#pragma unroll
-        for (int c = 0; c < 4; ++c) outb[c * ofs + z * ozs] = r[c];
-      } else if (MODE == 4) {
-        const T val[4] = {u, v, w, pr};
-        T nv[4];
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          nv[c] = acv[c] + val[c] * T(1.0 / 3.0) + fA * r[c];
-          ntstore(nv[c], unb + c * ufs + z * uzs, a.nt);
-        }
-        // The x-ghost columns of the row are cleared too, so that every cache
-        // line of the padded row is written whole: rows of partly written lines
-        // store far slower.  Ghost layers carry no state between steps.
-        const int gx = a.Lun.ng;
-        if (!xun && (x < gx || x >= BS - gx)) {
-          const int off = x < gx ? -gx : gx;
-#pragma unroll
-          for (int c = 0; c < 4; ++c) ntstore(T(0), unb + c * ufs + z * uzs + off, a.nt);
-        }
-        if (a.umax_part) m2 = fmax(m2, speed2(double(nv[0]), double(nv[1]), double(nv[2])));
-      } else {
-        const T val[4] = {u, v, w, pr};
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          const T u0 = MODE == 1 ? val[c] : unv[c];
-          // (U^n + Y2)/3 = 2/3 U^n + dt/6 k1, from the input Y2 = U^n + dt/2 k1
-          if (MODE == 2) ntstore((u0 + val[c]) * T(1.0 / 3.0) + fA * r[c], accb + c * afs + z * azs, a.nt);
-          outb[c * ofs + z * ozs] = u0 + fB * r[c];
-        }
-        // a padded output's rows are written whole as in stage 4 (the next
-        // stage's fill rewrites every ghost point that is read)
-        const int gx = a.Lout.ng;
-        if (OWNG && (x < gx || x >= BS - gx)) {
-          const int off = x < gx ? -gx : gx;
-#pragma unroll
-          for (int c = 0; c < 4; ++c) outb[c * ofs + z * ozs + off] = T(0);
-        }
-      }
-      if (z + 1 < BS) {
-        // plane z+1 into the other slab: it was last read before this
-        // plane's barrier, which every thread has passed
-        T(*nb_)[W * WY] = slab[(z + 1) & 1];
-#pragma unroll
-        for (int c = 0; c < 4; ++c) nb_[c][cidx] = q[c][4];
-        if (hthr) {
-#pragma unroll
-          for (int c = 0; c < 4; ++c) nb_[c][hli] = hnx[c];
-        }
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-#pragma unroll
-          for (int mm = 0; mm < 6; ++mm) q[c][mm] = q[c][mm + 1];
-          q[c][6] = nq[c];
-        }
-        if (PEN) pen_at(z + 1);
-      }
-    }
-    if (MODE == 4 && a.umax_part) {
-      // the work item's maximum, reduced in the workgroup; red is free again
-      // by the next item's writes (several barriers later)
-      m2 = wave_max(m2);
-      if ((tid & 63) == 0) red[tid >> 6] = m2;
-      lds_barrier();
-      if (tid == 0) {
-        double mx = red[0];
-#pragma unroll
-        for (int w = 1; w < NT / 64; ++w) mx = fmax(mx, red[w]);
-        a.umax_part[boff * NTY + item] = mx;
-      }
-    }
-    if (dyn && tid == 0) qitem = queue_take(a.queue, qh, qchunk, (int)nitems, qpend);
-  }
-}
-
 // Faces next to a coarser or finer leaf: the depth-3 face halo of the stage
 // input into the halo buffer the stage kernel reads.  A finer neighbour gives
 // its coincident point (decimation, Sec. 3.1).  A coarser neighbour gives the
@@ -1493,19 +1050,6 @@ static hipError_t pen_classify(const wacm_grid* g, const wacm_params* p, const d
 // --------------------------------------------------------------------------
 // launchers
 // --------------------------------------------------------------------------
-static int num_cus() {
-  static int cus = 0;
-  static std::once_flag once;
-  std::call_once(once, [] {
-    int dev = 0;
-    hipDeviceProp_t prop;
-    if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess)
-      cus = prop.multiProcessorCount;
-    if (cus <= 0) cus = 256;
-  });
-  return cus;
-}
-
 // Records an event pair around the launches in its scope when profiling is on.
 class ProfScope {
  public:
@@ -1736,87 +1280,6 @@ hipError_t launch_sync(const wacm_grid* g, void* U, hipStream_t st) {
   return g->d.dtype == WACM_F64 ? sync_t(g, (double*)U, st) : sync_t(g, (float*)U, st);
 }
 
-// resident workgroups per CU of a kernel (queried once per instantiation)
-template <typename K>
-static int resident_per_cu(K kernel, int threads) {
-  int n = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kernel, threads, 0) != hipSuccess || n < 1)
-    n = 1;
-  return n;
-}
-
-template <typename T, int BS, int TY, int MODE, bool PEN, bool PREF>
-static hipError_t stage_launch_t(const StageArgs<T>& a, int wg_per_cu, hipStream_t st) {
-  static const int resident =
-      resident_per_cu(stage_kernel<T, BS, TY, MODE, PEN, PREF>, BS * TY);
-  const int per_cu = wg_per_cu > 0 ? wg_per_cu : resident;
-  const int64_t items = a.nb * (BS / TY);
-  int64_t grid = (int64_t)per_cu * num_cus();
-  if (grid > items) grid = items;
-  if (grid < 1) grid = 1;
-  if (a.queue) {
-    queue_clear<<<1, 8 * QSTRIDE, 0, st>>>(a.queue);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  stage_kernel<T, BS, TY, MODE, PEN, PREF><<<(unsigned)grid, BS * TY, 0, st>>>(a);
-  return hipGetLastError();
-}
-
-// tile_rows 0: whole-block work items; 8: tiles of 8 rows (bs >= 24, where the
-// halo of a tile plane fits in one point per thread; smaller blocks use whole
-// blocks)
-template <typename T, int BS, int MODE, bool PEN, bool PREF>
-static hipError_t stage_launch_pp(const StageArgs<T>& a, const wacm_schedule& s,
-                                  hipStream_t st) {
-  if constexpr (BS >= 24) {
-    if (s.tile_rows == 8) return stage_launch_t<T, BS, 8, MODE, PEN, PREF>(a, s.wg_per_cu, st);
-  }
-  return stage_launch_t<T, BS, BS, MODE, PEN, PREF>(a, s.wg_per_cu, st);
-}
-
-// Schedule knobs: prefetch = 1 issues the epilogue loads before the plane's
-// barrier (more bytes in flight, more registers), 0 after the rhs; -1 picks
-// the default (early for FP32, late for FP64, whose 9-wave workgroup is at
-// its VGPR limit).
-template <typename T, int BS, int MODE>
-static hipError_t stage_launch(const StageArgs<T>& a, const wacm_schedule& s, hipStream_t st) {
-  const bool pen = a.p.mask || a.p.sponge || a.dus;
-  const bool pref = s.prefetch < 0 ? sizeof(T) == 4 : s.prefetch != 0;
-  if (pen && a.blist) {
-    // the blocks where the penalization vanishes take the unpenalized
-    // variant, the others the penalized one
-    StageArgs<T> f = a, n = a;
-    f.bsel = 0;
-    n.bsel = 1;
-    hipError_t e = pref ? stage_launch_pp<T, BS, MODE, false, true>(f, s, st)
-                        : stage_launch_pp<T, BS, MODE, false, false>(f, s, st);
-    if (e != hipSuccess) return e;
-    return pref ? stage_launch_pp<T, BS, MODE, true, true>(n, s, st)
-                : stage_launch_pp<T, BS, MODE, true, false>(n, s, st);
-  }
-  if (pen)
-    return pref ? stage_launch_pp<T, BS, MODE, true, true>(a, s, st)
-                : stage_launch_pp<T, BS, MODE, true, false>(a, s, st);
-  return pref ? stage_launch_pp<T, BS, MODE, false, true>(a, s, st)
-              : stage_launch_pp<T, BS, MODE, false, false>(a, s, st);
-}
-
-template <typename T, int MODE>
-static hipError_t stage_dispatch(int bs, const StageArgs<T>& a, const wacm_schedule& s,
-                                 hipStream_t st) {
-  switch (bs) {
-    case 16:
-      return stage_launch<T, 16, MODE>(a, s, st);
-    case 24:
-      return stage_launch<T, 24, MODE>(a, s, st);
-    case 32:
-      return stage_launch<T, 32, MODE>(a, s, st);
-    default:
-      return hipErrorInvalidValue;
-  }
-}
-
 template <typename T>
 static StageArgs<T> base_args(const wacm_grid* g, const wacm_params* p) {
   StageArgs<T> a{};
@@ -1837,14 +1300,6 @@ static StageArgs<T> base_args(const wacm_grid* g, const wacm_params* p) {
 // halos from the neighbours' interiors, the halos of faces next to another
 // level from the input's own ghost layers (filled before each stage), no
 // face-halo buffer.  Tiles of 8 rows; early epilogue loads for FP32.
-template <typename T, int BS, int S>
-static hipError_t stage_owng_bs(const StageArgs<T>& a, int wg_per_cu, hipStream_t st) {
-  constexpr bool PREF = sizeof(T) == 4;
-  return a.p.mask || a.p.sponge || a.dus
-             ? stage_launch_t<T, BS, 8, 10 + S, true, PREF>(a, wg_per_cu, st)
-             : stage_launch_t<T, BS, 8, 10 + S, false, PREF>(a, wg_per_cu, st);
-}
-
 template <typename T>
 static hipError_t stage_owng_t(const wacm_grid* g, const wacm_params* p, int s,
                                const double* t_dev, const double* dt_dev, const T* in, T* un,
@@ -1868,18 +1323,7 @@ static hipError_t stage_owng_t(const wacm_grid* g, const wacm_params* p, int s,
   a.dus = dus;
   a.t_dev = t_dev;
   a.dt_dev = dt_dev;
-  const int w = g->sched.wg_per_cu;
-  switch (g->d.bs * 10 + s) {
-    case 241: return stage_owng_bs<T, 24, 1>(a, w, st);
-    case 242: return stage_owng_bs<T, 24, 2>(a, w, st);
-    case 243: return stage_owng_bs<T, 24, 3>(a, w, st);
-    case 244: return stage_owng_bs<T, 24, 4>(a, w, st);
-    case 321: return stage_owng_bs<T, 32, 1>(a, w, st);
-    case 322: return stage_owng_bs<T, 32, 2>(a, w, st);
-    case 323: return stage_owng_bs<T, 32, 3>(a, w, st);
-    case 324: return stage_owng_bs<T, 32, 4>(a, w, st);
-    default: return hipErrorInvalidValue;
-  }
+  return stage_run<T>(10 + s, g->d.bs, a, g->sched, st);
 }
 
 hipError_t launch_stage_owng(const wacm_grid* g, const wacm_params* p, int s,
@@ -1907,7 +1351,7 @@ static hipError_t rhs_t(const wacm_grid* g, const wacm_params* p, double t, cons
   a.Lacc = pool_layout(g);
   a.dus = dus;
   a.t_host = t;
-  return stage_dispatch<T, 0>(g->d.bs, a, g->sched, st);
+  return stage_run<T>(0, g->d.bs, a, g->sched, st);
 }
 
 hipError_t launch_rhs(const wacm_grid* g, const wacm_params* p, double t, const void* U,
@@ -1944,12 +1388,6 @@ hipError_t launch_dt(const wacm_grid* g, const wacm_params* p, const void* U, do
                      hipStream_t st) {
   return g->d.dtype == WACM_F64 ? dt_t(g, p, (const double*)U, dt_dev, st)
                                 : dt_t(g, p, (const float*)U, dt_dev, st);
-}
-
-// stage work items of the current schedule (whole blocks or tiles of 8 rows)
-static int64_t stage_items(const wacm_grid* g) {
-  const int bs = g->d.bs;
-  return g->nb * ((g->sched.tile_rows == 8 && bs >= 24) ? bs / 8 : 1);
 }
 
 // nsteps classical RK4 steps.  With the CFL rule, the first step's dt comes
@@ -1997,8 +1435,7 @@ static hipError_t stage_input_t(const wacm_grid* g, const wacm_params* p, int s,
   a.kscale = s == 2 ? 0.5 : 1.0;
   if (g->n_cface > 0)
     if (hipError_t e = nlface_launch<T>(g, in, a.Lin, hb, st); e != hipSuccess) return e;
-  return s == 1 ? stage_dispatch<T, 1>(g->d.bs, a, g->sched, st)
-                : stage_dispatch<T, 3>(g->d.bs, a, g->sched, st);
+  return stage_run<T>(s == 1 ? 1 : 3, g->d.bs, a, g->sched, st);
 }
 
 hipError_t launch_stage_input(const wacm_grid* g, const wacm_params* p, int s, double t,
@@ -2043,7 +1480,7 @@ static hipError_t rk4_t(const wacm_grid* g, const wacm_params* p, double* t_dev,
   T* outs[4] = {ping, pong, ping, U};
   Layout lins[4] = {Lp, Ls, Ls, Ls};
   const double hmin = g->d.L / (double(int64_t(1) << g->jfine) * g->d.bs);
-  const int64_t items = stage_items(g);
+  int64_t nmax = 0;  // velocity maxima the last stage of the previous step left
   // blocks without penalization first (the adaptation lists are free
   // during a step: capacity entries of the list, then the 2 counts); a
   // pitching plate is classified per step, for the angles of that step
@@ -2065,7 +1502,7 @@ static hipError_t rk4_t(const wacm_grid* g, const wacm_params* p, double* t_dev,
       if (k == 0) {
         if ((e = dt_t<T>(g, p, U, dt_dev, st)) != hipSuccess) return e;
       } else {
-        dt_finalize<<<1, NT_GEN, 0, st>>>(g->d_part, items, *p, hmin, dt_dev);
+        dt_finalize<<<1, NT_GEN, 0, st>>>(g->d_part, nmax, *p, hmin, dt_dev);
         if ((e = hipGetLastError()) != hipSuccess) return e;
       }
     }
@@ -2084,6 +1521,7 @@ static hipError_t rk4_t(const wacm_grid* g, const wacm_params* p, double* t_dev,
       a.un = s == 3 ? unext : un;
       a.Lun = s == 3 ? Lnext : Lun;
       a.umax_part = (s == 3 && dt_mode == WACM_DT_CFL && k + 1 < nsteps) ? g->d_part : nullptr;
+      a.nmax = a.umax_part ? &nmax : nullptr;
       if (g->n_cface > 0) {
         ProfScope ps(g, 1, st);
         if ((e = nlface_launch<T>(g, a.in, a.Lin, hb, st)) != hipSuccess) return e;
@@ -2092,20 +1530,7 @@ static hipError_t rk4_t(const wacm_grid* g, const wacm_params* p, double* t_dev,
       if (s == 0 && split_step &&
           (e = pen_classify(g, p, t_dev, dt_dev, plist, pcnt, pflag, st)) != hipSuccess)
         return e;
-      switch (s) {
-        case 0:
-          e = stage_dispatch<T, 1>(g->d.bs, a, g->sched, st);
-          break;
-        case 1:
-          e = stage_dispatch<T, 2>(g->d.bs, a, g->sched, st);
-          break;
-        case 2:
-          e = stage_dispatch<T, 3>(g->d.bs, a, g->sched, st);
-          break;
-        default:
-          e = stage_dispatch<T, 4>(g->d.bs, a, g->sched, st);
-          break;
-      }
+      e = stage_run<T>(s + 1, g->d.bs, a, g->sched, st);
       if (e != hipSuccess) return e;
     }
     ProfScope ps(g, 3, st);

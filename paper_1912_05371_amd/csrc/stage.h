@@ -2,6 +2,7 @@
 // with a depth-3 halo: the fused rhs + RK stage and its adjoint.
 #pragma once
 
+#include <mutex>
 #include <type_traits>
 
 #include "resolve.h"
@@ -73,7 +74,7 @@ __device__ __forceinline__ double tanh_sat(double x) {
 // the sphere's mask at a point, as mask_point evaluates it
 __device__ __forceinline__ double sphere_chi(const wacm_params& p, double x, double y, double z) {
   const double dx = x - p.sph_c[0], dy = y - p.sph_c[1], dz = z - p.sph_c[2];
-  const double d = sqrt(dx * dx + dy * dy + dz * dz) - p.sph_r;
+  const double d = sqrt(fma(dx, dx, fma(dy, dy, dz * dz))) - p.sph_r;
   const double chi = 0.5 * (1.0 - tanh_sat(d / p.w));
   return p.clip && chi < 1e-8 ? 0.0 : chi;
 }
@@ -89,8 +90,8 @@ __device__ __forceinline__ void plate_tab_fill(const wacm_params& p, const MaskT
     const int x = q % BS, z = q / BS;
     const double rx = (double)(meta[2] * BS + x) * h - p.x_le[0];
     const double rz = (double)(meta[4] * BS + z) * h - p.x_le[2];
-    t.f0[q] = box_factor(mt.ca * rx - mt.sa * rz, p.lo[0], p.hi[0], p.w);
-    t.f2[q] = box_factor(mt.sa * rx + mt.ca * rz, p.lo[2], p.hi[2], p.w);
+    t.f0[q] = box_factor(fma(mt.ca, rx, -(mt.sa * rz)), p.lo[0], p.hi[0], p.w);
+    t.f2[q] = box_factor(fma(mt.sa, rx, mt.ca * rz), p.lo[2], p.hi[2], p.w);
   }
   for (int y = threadIdx.x; y < BS; y += blockDim.x)
     t.f1[y] = box_factor((double)(meta[3] * BS + y) * h - p.x_le[1], p.lo[1], p.hi[1], p.w);
@@ -246,6 +247,13 @@ __device__ __forceinline__ FaceDesc<T> face_desc(const Tab& tb, const T* in, con
   return fd;
 }
 
+// A value the compiler takes as it is (nothing is fused into its use).
+template <typename T>
+__device__ __forceinline__ T opaque(T v) {
+  asm("" : "+v"(v));
+  return v;
+}
+
 // Streaming operands (U^n, the accumulator) are touched once per stage: load
 // and store them non-temporally so the caches keep the stage input, whose
 // face layers neighbouring blocks read again.
@@ -260,5 +268,101 @@ __device__ __forceinline__ void ntstore(T v, T* p, int nt) {
   else
     *p = v;
 }
+
+
+template <typename T>
+__device__ __forceinline__ T wave_max(T v) {
+  for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
+  return v;
+}
+// |u|^2 in FP64 with one fixed operation order: the maximum fused into the
+// last RK4 stage and the stand-alone reduction agree bit for bit.
+__device__ __forceinline__ double speed2(double u, double v, double w) {
+  return __builtin_fma(w, w, __builtin_fma(v, v, u * u));
+}
+template <typename T>
+__device__ __forceinline__ T wave_min(T v) {
+  for (int o = 32; o > 0; o >>= 1) v = fmin(v, __shfl_xor(v, o, 64));
+  return v;
+}
+
+template <typename T>
+struct StageArgs {
+  const Tab* tab;
+  int64_t nb;
+  const T* in;  // stage input register
+  Layout Lin;
+  const T* hb;  // halo buffer of faces next to other levels [slot][6][4][3][bs][bs]
+  T* un;        // U^n register (the pool)
+  Layout Lun;
+  T* acc;  // accumulator (compact)
+  Layout Lacc;
+  T* out;  // next stage input, or dU for the rhs-only mode
+  Layout Lout;
+  const T* dus;  // extra solid velocity [slot][3][bs^3] or null
+  const double* t_dev;  // step time and size on the device, or null:
+  const double* dt_dev;  // t_host and dt_host
+  int64_t* nmax;      // host: where the launcher leaves the number of umax_part entries
+  double* umax_part;  // stage 4: per work item max |u|^2 of the new U^n, or null
+  // optional block list: the blocks of this launch are blist[off + i],
+  // i < bcnt[bsel], off = bsel ? bcnt[0] : 0 (the list holds the blocks
+  // without penalization first, then the others; null: every block)
+  const int32_t* blist;
+  const int32_t* bcnt;
+  int bsel;
+  double t_host;
+  double dt_host;
+  double kscale;  // MODE 3: out = U^n + kscale dt k (1; 1/2 gives stage 2 without W)
+  double L;
+  int xcd_map;  // 1: give each XCD a contiguous run of work items
+  int* queue;   // xcd_map 2: per-XCD work counters (QSTRIDE apart), zero at launch
+  int nt;       // 1: non-temporal loads/stores of the streaming operands
+  wacm_params p;
+};
+
+// Dynamic per-XCD work queues (xcd_map 2): the Morton-ordered items are cut
+// into 8 contiguous chunks, one per XCD; workgroup w (on XCD w % 8) takes the
+// next item of its own chunk from that chunk's counter, so the tiles of one
+// block and neighbouring blocks run together on one L2, and when its chunk is
+// empty it takes items from the following chunks, so no XCD idles while
+// another still has work.  Each counter increment that finds a chunk empty
+// moves on to the next chunk: at most 8 misses per workgroup, so every
+// workgroup ends.  Thread 0 only.
+constexpr int QSTRIDE = 32;  // ints between counters: one 128-byte line each
+__device__ __forceinline__ int queue_take(int* ctr, int& q, int chunk, int n, int v) {
+  for (int miss = 0;;) {
+    const int lo = q * chunk;
+    const int hi = lo + chunk < n ? lo + chunk : n;
+    if (lo + v < hi) return lo + v;
+    if (++miss == 8) return n;
+    q = (q + 1) & 7;
+    v = atomicAdd(ctr + q * QSTRIDE, 1);
+  }
+}
+
+[[maybe_unused]] static __global__ void queue_clear(int* ctr) {
+  if (threadIdx.x < 8 * QSTRIDE) ctr[threadIdx.x] = 0;
+}
+
+// compute units of the current device (asked once)
+inline int num_cus() {
+  static int cus = 0;
+  static std::once_flag once;
+  std::call_once(once, [] {
+    int dev = 0;
+    hipDeviceProp_t prop;
+    if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess)
+      cus = prop.multiProcessorCount;
+    if (cus <= 0) cus = 256;
+  });
+  return cus;
+}
+
+// One launch of the stage kernel (stage_kernel.h; instantiated per element type
+// in stage_f32.hip and stage_f64.hip): mode 0 rhs only, 1..4 RK stage, 10 + 1..4
+// RK stage on padded registers.
+template <typename T>
+hipError_t stage_run(int mode, int bs, const StageArgs<T>& a, const wacm_schedule& s,
+                     hipStream_t st);
 
 }  // namespace wacm

@@ -28,7 +28,7 @@ import sqlite3
 import sys
 
 HERE = os.path.dirname(os.path.abspath(__file__))
-STAGE_SOURCES = ("csrc/kernels.hip", "csrc/resolve.h", "csrc/stage.h", "csrc/wacm_internal.h")
+STAGE_SOURCES = ("csrc/stage_kernel.h", "csrc/resolve.h", "csrc/stage.h", "csrc/wacm_internal.h")
 
 
 def stage_source_sha1() -> str:
