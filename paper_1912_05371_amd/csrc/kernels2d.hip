@@ -15,6 +15,7 @@
 
 #include "resolve.h"
 #include "resolve2d.h"
+#include "stage.h"
 #include "wacm_internal.h"
 
 namespace wacm {
@@ -36,60 +37,95 @@ Lay pool_layout(const wacm_grid* g) {
   return L;
 }
 
-// every ghost point of every active block, all ng layers; one thread per
-// (block, ghost point), the 3 fields together
+// every ghost point of every active block, all ng layers: one workgroup per
+// block, whose table the points look up in LDS (from memory, one look-up after
+// the other bounded the fill)
 template <typename T>
 __global__ __launch_bounds__(NT_GEN) void sync2d_kernel(const Tab* __restrict__ tab, int64_t nb,
-                                                        T* __restrict__ U, Lay L, int bs) {
-  const int P = L.P, ng = L.ng;
-  const int nghost = P * P - bs * bs;
-  const int64_t total = nb * nghost;
-  for (int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; q < total;
-       q += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t ib = q / nghost;
-    int i, j;
-    ghost_point((int)(q - ib * nghost), bs, ng, i, j);
-    const Tab& t = tab[ib];
-    T* dst = U + (int64_t)t.meta[0] * L.bstride + (int64_t)(j + ng) * P + (i + ng);
-    for (int c = 0; c < 3; ++c) dst[c * L.fstride] = ghost_value(t, U, L, bs, c, i, j);
+                                                        T* U, Lay L, int bs) {
+  __shared__ Tab st;
+  const int P = L.P, ng = L.ng, nghost = P * P - bs * bs;
+  for (int64_t ib = blockIdx.x; ib < nb; ib += gridDim.x) {
+    __syncthreads();
+    load_tab(tab + ib, st);
+    __syncthreads();
+    T* dst = U + (int64_t)st.meta[0] * L.bstride;
+    for (int q = threadIdx.x; q < nghost; q += NT_GEN) {
+      int i, j;
+      ghost_point(q, bs, ng, i, j);
+      T v[3];
+      ghost_values<4>(st, U, L, bs, i, j, v);
+      for (int c = 0; c < 3; ++c) dst[c * L.fstride + (int64_t)(j + ng) * P + (i + ng)] = v[c];
+    }
   }
 }
 
-// Fused rhs + RK4 stage on the synchronised stage input `in` (own ghost
-// layers), one workgroup per block, one thread per point; the 3-deep halo
-// and the block in an LDS tile.  Registers (pool layout): U^n `un`, the
-// accumulator `acc`, the next stage input `out`.
+// Fused ghost fill + rhs + RK4 stage: one workgroup per block, one thread per
+// point; the block and the depth-3 halo of its four sides (what the stencils
+// read) in an LDS tile.  The halo is read from whichever leaves hold it, so a
+// stage is one launch and its input's ghost layers are never written: a grid of
+// a few hundred blocks is bounded by launches and by the latency of the chain
+// table -> halo -> stores (349 blocks of 16^2 FP64: 42 us per stage in two
+// launches -> 10 us).  MODE 0 reads the input's own ghost layers.  Registers
+// (pool layout): U^n `un`, the accumulator `acc`, the next stage input `out`.
 //   MODE 0: out = rhs(in)
 //   MODE 1: acc = U^n + dt/6 k;  out = U^n + dt/2 k
 //   MODE 2: acc += dt/3 k;       out = U^n + dt/2 k
 //   MODE 3: acc += dt/3 k;       out = U^n + dt k
-//   MODE 4: U^n = acc + dt/6 k   (out = un)
+//   MODE 4: U^n = acc + dt/6 k   (out = un); part: per block max |u|^2 of it
 template <typename T, int BS, int MODE>
 __global__ __launch_bounds__(BS* BS) void stage2d_kernel(const Tab* __restrict__ tab, int64_t nb,
                                                          const T* __restrict__ in, T* un, T* acc,
                                                          T* out, Lay L, double Ldom,
                                                          wacm_params p,
-                                                         const double* __restrict__ dt_dev) {
-  constexpr int W = BS + 6;
+                                                         const double* __restrict__ dt_dev,
+                                                         double* __restrict__ part) {
+  constexpr int W = BS + 6, NT = BS * BS, NH = 12 * BS;
+  constexpr int ROWS = BS == 16 ? 4 : 1;  // more than 256 threads leave no registers for 16 taps
   __shared__ T tile[3][W * W];
+  __shared__ Tab st;
+  __shared__ double red[NT / 64];
   const int tid = threadIdx.x, x = tid % BS, y = tid / BS;
   const double dt = MODE == 0 ? 0.0 : *dt_dev;
   const T a1 = T(TW1), a2 = T(TW2), a3 = T(TW3);
   const T c2a = T(D2A), c2b = T(D2B), c2c = T(D2C);
   const T nu = T(p.nu), c0sq = T(p.c0 * p.c0), cg = T(p.c_gamma);
+  const int ct = (y + 3) * W + (x + 3);
   for (int64_t ib = blockIdx.x; ib < nb; ib += gridDim.x) {
     const int slot = tab[ib].meta[0], J = tab[ib].meta[1];
     const double h = Ldom / (double(int64_t(1) << J) * BS);
     const T ih = T(1.0 / h), ih2 = T(1.0 / (h * h));
-    const T* src = in + (int64_t)slot * L.bstride;
-    __syncthreads();  // the previous block's tile is no longer read
-    for (int q = tid; q < W * W; q += BS * BS) {
-      const int tx = q % W, ty = q / W;
-      const int64_t o = (int64_t)(ty - 3 + L.ng) * L.P + (tx - 3 + L.ng);
-      for (int c = 0; c < 3; ++c) tile[c][q] = src[c * L.fstride + o];
+    const int64_t o = (int64_t)slot * L.bstride + (int64_t)(y + L.ng) * L.P + (x + L.ng);
+    // this point's values, in flight while the table arrives
+    T own[3], u0[3], a0[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      own[c] = in[o + c * L.fstride];
+      if (MODE == 2 || MODE == 3) u0[c] = un[o + c * L.fstride];
+      if (MODE >= 2) a0[c] = acc[o + c * L.fstride];
+    }
+    __syncthreads();  // the previous block's tile and table are no longer read
+    if (MODE != 0) {
+      load_tab(tab + ib, st);
+      __syncthreads();
+    }
+#pragma unroll
+    for (int c = 0; c < 3; ++c) tile[c][ct] = own[c];
+    for (int q = tid; q < NH; q += NT) {
+      // side 0..3 (x-, x+, y-, y+), depth, position along the side
+      const int side = q / (3 * BS), rem = q - side * 3 * BS, d = rem / BS, e = rem - d * BS;
+      const int n = (side & 1) ? BS + d : -1 - d;
+      const int i = side < 2 ? n : e, j = side < 2 ? e : n;
+      T v[3];
+      if (MODE == 0) {
+        const int64_t g = (int64_t)slot * L.bstride + (int64_t)(j + L.ng) * L.P + (i + L.ng);
+        for (int c = 0; c < 3; ++c) v[c] = in[g + c * L.fstride];
+      } else {
+        ghost_values<ROWS>(st, in, L, BS, i, j, v);
+      }
+      for (int c = 0; c < 3; ++c) tile[c][(j + 3) * W + (i + 3)] = v[c];
     }
     __syncthreads();
-    const int ct = (y + 3) * W + (x + 3);
     T dx[3], dy[3], lap[2];
     for (int c = 0; c < 3; ++c) {
       const T* s = tile[c];
@@ -106,25 +142,37 @@ __global__ __launch_bounds__(BS* BS) void stage2d_kernel(const Tab* __restrict__
                    c2a * s[ct + 2 * W])) *
                  ih2;
     }
-    const T u = tile[0][ct], v = tile[1][ct], pr = tile[2][ct];
+    const T u = own[0], v = own[1], pr = own[2];
     T r[3];
     r[0] = -(u * dx[0] + v * dy[0]) - dx[2] + nu * lap[0];
     r[1] = -(u * dx[1] + v * dy[1]) - dy[2] + nu * lap[1];
     r[2] = -c0sq * (dx[0] + dy[1]) - cg * pr;
-    const int64_t o = (int64_t)slot * L.bstride + (int64_t)(y + L.ng) * L.P + (x + L.ng);
+    T nv[3];
+#pragma unroll
     for (int c = 0; c < 3; ++c) {
       const int64_t oc = o + c * L.fstride;
       if (MODE == 0) {
         out[oc] = r[c];
       } else if (MODE == 1) {
-        const T u0 = un[oc];
-        acc[oc] = u0 + T(dt / 6.0) * r[c];
-        out[oc] = u0 + T(0.5 * dt) * r[c];
+        acc[oc] = own[c] + T(dt / 6.0) * r[c];
+        out[oc] = own[c] + T(0.5 * dt) * r[c];
       } else if (MODE == 2 || MODE == 3) {
-        acc[oc] = acc[oc] + T(dt / 3.0) * r[c];
-        out[oc] = un[oc] + T(MODE == 2 ? 0.5 * dt : dt) * r[c];
+        acc[oc] = a0[c] + T(dt / 3.0) * r[c];
+        out[oc] = u0[c] + T(MODE == 2 ? 0.5 * dt : dt) * r[c];
       } else {
-        un[oc] = acc[oc] + T(dt / 6.0) * r[c];
+        nv[c] = a0[c] + T(dt / 6.0) * r[c];
+        un[oc] = nv[c];
+      }
+    }
+    if (MODE == 4 && part) {
+      const double un0 = nv[0], un1 = nv[1];
+      double m = __builtin_fma(un1, un1, un0 * un0);
+      for (int s = 32; s > 0; s >>= 1) m = fmax(m, __shfl_xor(m, s, 64));
+      if ((tid & 63) == 0) red[tid >> 6] = m;
+      __syncthreads();
+      if (tid == 0) {
+        for (int w = 1; w < NT / 64; ++w) m = fmax(m, red[w]);
+        part[ib] = m;
       }
     }
   }
@@ -362,32 +410,30 @@ unsigned blocks_for(int64_t n, int per_cu = 8) {
 template <typename T>
 hipError_t sync_t(const wacm_grid* g, T* U, hipStream_t st) {
   if (g->nb == 0) return hipSuccess;
-  const Lay L = pool_layout(g);
-  const int64_t total = g->nb * (int64_t)(L.P * L.P - g->d.bs * g->d.bs);
-  sync2d_kernel<T><<<blocks_for((total + NT_GEN - 1) / NT_GEN, 16), NT_GEN, 0, st>>>(
-      g->d_tab, g->nb, U, L, g->d.bs);
+  sync2d_kernel<T><<<blocks_for(g->nb), NT_GEN, 0, st>>>(g->d_tab, g->nb, U, pool_layout(g),
+                                                         g->d.bs);
   return hipGetLastError();
 }
 
 template <typename T, int BS, int MODE>
 hipError_t stage_bs(const wacm_grid* g, const wacm_params* p, const T* in, T* un, T* acc, T* out,
-                    const double* dt_dev, hipStream_t st) {
+                    const double* dt_dev, double* part, hipStream_t st) {
   stage2d_kernel<T, BS, MODE><<<blocks_for(g->nb, 4), BS * BS, 0, st>>>(
-      g->d_tab, g->nb, in, un, acc, out, pool_layout(g), g->d.L, *p, dt_dev);
+      g->d_tab, g->nb, in, un, acc, out, pool_layout(g), g->d.L, *p, dt_dev, part);
   return hipGetLastError();
 }
 
 template <typename T, int MODE>
 hipError_t stage_t(const wacm_grid* g, const wacm_params* p, const T* in, T* un, T* acc, T* out,
-                   const double* dt_dev, hipStream_t st) {
+                   const double* dt_dev, double* part, hipStream_t st) {
   if (g->nb == 0) return hipSuccess;
   switch (g->d.bs) {
     case 16:
-      return stage_bs<T, 16, MODE>(g, p, in, un, acc, out, dt_dev, st);
+      return stage_bs<T, 16, MODE>(g, p, in, un, acc, out, dt_dev, part, st);
     case 24:
-      return stage_bs<T, 24, MODE>(g, p, in, un, acc, out, dt_dev, st);
+      return stage_bs<T, 24, MODE>(g, p, in, un, acc, out, dt_dev, part, st);
     case 32:
-      return stage_bs<T, 32, MODE>(g, p, in, un, acc, out, dt_dev, st);
+      return stage_bs<T, 32, MODE>(g, p, in, un, acc, out, dt_dev, part, st);
     default:
       return hipErrorInvalidValue;
   }
@@ -420,29 +466,21 @@ hipError_t rk4_t(const wacm_grid* g, const wacm_params* p, double* t_dev, double
   T* Yb = (T*)((char*)work + reg);
   T* acc = (T*)((char*)work + 2 * reg);
   hipError_t e;
+  const double hmin = g->d.L / (double(int64_t(1) << g->jfine) * g->d.bs);
   for (int64_t k = 0; k < nsteps; ++k) {
-    if (dt_mode == WACM_DT_CFL && (e = dt_t<T>(g, p, U, dt_dev, st)) != hipSuccess) return e;
-    T* ins[4] = {U, Ya, Yb, Ya};
-    T* outs[4] = {Ya, Yb, Ya, U};
-    for (int s = 0; s < 4; ++s) {
-      if ((e = sync_t<T>(g, ins[s], st)) != hipSuccess) return e;
-      switch (s) {
-        case 0:
-          e = stage_t<T, 1>(g, p, ins[s], U, acc, outs[s], dt_dev, st);
-          break;
-        case 1:
-          e = stage_t<T, 2>(g, p, ins[s], U, acc, outs[s], dt_dev, st);
-          break;
-        case 2:
-          e = stage_t<T, 3>(g, p, ins[s], U, acc, outs[s], dt_dev, st);
-          break;
-        default:
-          e = stage_t<T, 4>(g, p, ins[s], U, acc, outs[s], dt_dev, st);
-          break;
-      }
+    // from the second step on, the CFL maximum comes from the last stage
+    if (dt_mode == WACM_DT_CFL) {
+      e = k == 0 ? dt_t<T>(g, p, U, dt_dev, st)
+                 : finalize_dt(g->d_part, g->nb, *p, hmin, dt_dev, st);
       if (e != hipSuccess) return e;
     }
-    if ((e = add_dt_to_time(t_dev, dt_dev, st)) != hipSuccess) return e;
+    double* part = dt_mode == WACM_DT_CFL && k + 1 < nsteps ? g->d_part : nullptr;
+    if ((e = stage_t<T, 1>(g, p, U, U, acc, Ya, dt_dev, nullptr, st)) != hipSuccess ||
+        (e = stage_t<T, 2>(g, p, Ya, U, acc, Yb, dt_dev, nullptr, st)) != hipSuccess ||
+        (e = stage_t<T, 3>(g, p, Yb, U, acc, Ya, dt_dev, nullptr, st)) != hipSuccess ||
+        (e = stage_t<T, 4>(g, p, Ya, U, acc, U, dt_dev, part, st)) != hipSuccess ||
+        (e = add_dt_to_time(t_dev, dt_dev, st)) != hipSuccess)
+      return e;
   }
   return hipSuccess;
 }
@@ -486,9 +524,9 @@ hipError_t launch_rhs_2d(const wacm_grid* g, const wacm_params* p, const void* U
                          hipStream_t st) {
   if (g->d.dtype == WACM_F64)
     return d2::stage_t<double, 0>(g, p, (const double*)U, nullptr, nullptr, (double*)dU,
-                                  nullptr, st);
+                                  nullptr, nullptr, st);
   return d2::stage_t<float, 0>(g, p, (const float*)U, nullptr, nullptr, (float*)dU, nullptr,
-                               st);
+                               nullptr, st);
 }
 
 hipError_t launch_dt_2d(const wacm_grid* g, const wacm_params* p, const void* U, double* dt_dev,

@@ -77,29 +77,59 @@ __host__ __device__ inline int64_t lattice_offset(const Tab& t, const Lay& L, in
   return (int64_t)slot * L.bstride + (int64_t)(iy + L.ng) * L.P + (ix + L.ng);
 }
 
-// Ghost value of field c at block-local (i, j): the owner's lattice value, or
-// the DD4 prediction (weights (-1, 9, 9, -1)/16 at offsets -3, -1, 1, 3 on
-// each axis where the index is odd) from the coarse lattice when the owner is
-// coarser; summed y outer, x inner.
+// Ghost values of the 3 fields at block-local (i, j): the owner's lattice
+// values, or the DD4 prediction (weights (-1, 9, 9, -1)/16 at offsets -3, -1,
+// 1, 3 on each axis where the index is odd) from the coarse lattice when the
+// owner is coarser; summed y outer, x inner.
+template <int ROWS, typename T>
+__host__ __device__ void ghost_values(const Tab& t, const T* __restrict__ U, const Lay& L, int bs,
+                                      int i, int j, T out[3]) {
+  const int r = region_of(i, bs) + 3 * region_of(j, bs) + 9;
+  if (t.kind[r] >= 0) {
+    const int64_t o = lattice_offset(t, L, bs, i, j);
+    for (int c = 0; c < 3; ++c) out[c] = U[o + c * L.fstride];
+    return;
+  }
+  constexpr double W[4] = {DDW0, DDW1, DDW1, DDW0};
+  constexpr int O[4] = {-3, -1, 1, 3};
+  // the taps of ROWS rows are loaded before the first is used (an even axis
+  // has one tap, read 4 times): a loop over the taps would wait for each
+  const int nx = (i & 1) ? 4 : 1, ny = (j & 1) ? 4 : 1;
+  double v[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+  for (int b0 = 0; b0 < 4; b0 += ROWS) {
+    T u[ROWS][4][3];
+    if (b0 < ny) {
+#pragma unroll
+      for (int b = 0; b < ROWS; ++b)
+#pragma unroll
+        for (int a = 0; a < 4; ++a) {
+          const int64_t o = lattice_offset(t, L, bs, nx == 1 ? i : i + O[a],
+                                           ny == 1 ? j : j + O[b0 + b]);
+#pragma unroll
+          for (int c = 0; c < 3; ++c) u[b][a][c] = U[o + c * L.fstride];
+        }
+#pragma unroll
+      for (int b = 0; b < ROWS; ++b)
+#pragma unroll
+        for (int a = 0; a < 4; ++a)
+          if (a < nx && b0 + b < ny) {
+            const double w = (ny == 1 ? 1.0 : W[b0 + b]) * (nx == 1 ? 1.0 : W[a]);
+#pragma unroll
+            for (int c = 0; c < 3; ++c) v[c] += w * (double)u[b][a][c];
+          }
+    }
+  }
+  for (int c = 0; c < 3; ++c) out[c] = T(v[c]);
+}
+
+// field c of ghost_values
 template <typename T>
 __host__ __device__ T ghost_value(const Tab& t, const T* __restrict__ U, const Lay& L, int bs,
                                   int c, int i, int j) {
-  const int r = region_of(i, bs) + 3 * region_of(j, bs) + 9;
-  if (t.kind[r] >= 0) return U[lattice_offset(t, L, bs, i, j) + c * L.fstride];
-  constexpr double W[4] = {DDW0, DDW1, DDW1, DDW0};
-  constexpr int O[4] = {-3, -1, 1, 3};
-  const int nx = (i & 1) ? 4 : 1, ny = (j & 1) ? 4 : 1;
-  double v = 0.0;
-  for (int b = 0; b < ny; ++b) {
-    const int py = ny == 1 ? j : j + O[b];
-    const double wy = ny == 1 ? 1.0 : W[b];
-    for (int a = 0; a < nx; ++a) {
-      const int px = nx == 1 ? i : i + O[a];
-      const double wx = nx == 1 ? 1.0 : W[a];
-      v += (wy * wx) * (double)U[lattice_offset(t, L, bs, px, py) + c * L.fstride];
-    }
-  }
-  return T(v);
+  T v[3];
+  ghost_values<4>(t, U, L, bs, i, j, v);
+  return v[c];
 }
 
 }  // namespace d2
