@@ -580,19 +580,83 @@ __global__ __launch_bounds__(NT_GEN) void norm_finalize(const double* __restrict
   }
 }
 
+// The x and y passes of the tensor DD4 prediction, marching through the planes
+// of a lattice: 4 fields together, NT = BS^2 threads, one per (i, j) column.  A
+// plane's raw lattice values ([field][row][S], S points per row, SY rows) go to
+// LDS, then its x pass (raw -> X, BS points per row), then each thread's y pass
+// from X.  Raw values and X are double-buffered, so that a step does the x pass
+// of plane m, stores plane m + 1 and loads plane m + 2 before one LDS barrier.
+// Every X is formed once; threads take the even rows first, so that a wave's
+// rows mostly have one parity.  A point's even lattice neighbour at or below is
+// lattice index H + i / 2 (H points of halo below).
+template <typename T, int BS, int S, int H>
+struct PredictPlanes {
+  static constexpr int NT = BS * BS, S2 = S * S, NX = S * BS;
+  static constexpr int PR = (4 * S2 + NT - 1) / NT, PX = (4 * NX + NT - 1) / NT;
+  T (*raw)[4 * S2];
+  T (*xp)[4 * NX];
+  int tid, i, j;   // this thread's column
+  int lo[PR];      // element offset of its raw values in their plane, or -1
+  int xs[PX];      // lattice index its x-pass values start from, or -1
+  T rv[PR];
+  __device__ PredictPlanes(T (*r)[4 * S2], T (*x)[4 * NX], int P, int fs, int org, int step)
+      : raw(r), xp(x), tid(threadIdx.x) {
+    i = tid % BS;
+    const int jr = tid / BS;
+    j = jr < BS / 2 ? 2 * jr : 2 * (jr - BS / 2) + 1;
+#pragma unroll
+    for (int q = 0; q < PR; ++q) {
+      const int e = tid + q * NT, c = e / S2, k = e - c * S2;
+      lo[q] = e < 4 * S2 ? c * fs + org + step * ((k / S) * P + k % S) : -1;
+    }
+#pragma unroll
+    for (int q = 0; q < PX; ++q) {
+      const int e = tid + q * NT, c = e / NX, k = e - c * NX;
+      xs[q] = e < 4 * NX ? c * S2 + (k / BS) * S + H + (k % BS) / 2 : -1;
+    }
+  }
+  __device__ void load(const T* plane) {
+#pragma unroll
+    for (int q = 0; q < PR; ++q) rv[q] = lo[q] >= 0 ? plane[lo[q]] : T(0);
+  }
+  __device__ void store(int m) {
+#pragma unroll
+    for (int q = 0; q < PR; ++q)
+      if (lo[q] >= 0) raw[m & 1][tid + q * NT] = rv[q];
+  }
+  __device__ void xpass(int m) {
+    const T w0 = T(DDW0), w1 = T(DDW1);
+#pragma unroll
+    for (int q = 0; q < PX; ++q)
+      if (xs[q] >= 0) {
+        const T* r = raw[m & 1] + xs[q];
+        const T a = r[-1], b = r[0], c = r[1], d = r[2];
+        // NX and NT are even: every value of a thread has its column's parity
+        xp[m & 1][tid + q * NT] = (i & 1) ? w0 * a + w1 * b + w1 * c + w0 * d : b;
+      }
+  }
+  // P along x and y of plane m at this thread's column, field c
+  __device__ T ypass(int m, int c) const {
+    const T w0 = T(DDW0), w1 = T(DDW1);
+    const T* x = xp[m & 1] + c * NX + (H + j / 2) * BS + i;
+    if (!(j & 1)) return x[0];
+    return w0 * x[-BS] + w1 * x[0] + w1 * x[BS] + w0 * x[2 * BS];
+  }
+};
+
 // Wavelet details (Sec. 3.1) of one block: d = u - P R u at every interior
 // point with an odd index, P R u the tensor-product DD4 prediction from the
 // block's even lattice (ghost-synchronised pool), evaluated separably while
-// marching in z over the coarse planes k' = -2, 0, ..., bs + 2: the x pass
-// gives X(i, j', k') on the coarse rows (LDS, two buffers), the y pass
-// Y(i, j, k') of the thread's own column (one thread per column, the last 4
-// coarse planes in registers), the z pass the prediction of the fine plane k'
-// (even) and k' - 3 (odd).  All 4 fields at once: one barrier per coarse
-// plane.  One workgroup per block; per block and field the maxima of |u_c|
-// and |d_c| over the interior (part[8 ib + c], part[8 ib + 4 + c]), and the
-// mask range (0 without a mask, and for a block where the mask vanishes at
-// time t); thr_finalize turns them into the normalised detail maximum and the
-// coarsening flag (Sec. 3.3-3.5).
+// marching in z over the coarse planes k' = -2, 0, ..., bs + 2: x and y passes
+// through LDS (PredictPlanes), the last 4 coarse planes of the thread's column
+// in registers, z pass and comparison for the fine planes k' (even) and k' - 3
+// (odd), whose points are loaded a plane ahead.  One workgroup per block.
+// Bound: reading the block; it was the latency of each plane's own loads before
+// its barrier (4005 blocks of 24^3, FP64: 1059 -> 580 us).  Per block and field
+// the maxima of |u_c| and |d_c| over the interior (part[8 ib + c], part[8 ib +
+// 4 + c]), and the mask range (0 without a mask, and for a block where the mask
+// vanishes at time t); thr_finalize turns them into the normalised detail
+// maximum and the coarsening flag (Sec. 3.3-3.5).
 template <typename T, int BS>
 __global__ __launch_bounds__(BS* BS) void detail_kernel(const Tab* __restrict__ tab, int64_t nb,
                                                         const T* __restrict__ U, Layout L,
@@ -600,21 +664,32 @@ __global__ __launch_bounds__(BS* BS) void detail_kernel(const Tab* __restrict__ 
                                                         double* __restrict__ part,
                                                         double* __restrict__ mrange) {
   constexpr int S = BS / 2 + 3;  // even positions -2, 0, ..., bs+2
-  constexpr int NT = BS * BS;
-  __shared__ T xp[2][4][S * BS];
+  using PP = PredictPlanes<T, BS, S, 1>;
+  constexpr int NT = PP::NT;
+  __shared__ T raw[2][4 * PP::S2], xp[2][4 * PP::NX];
   __shared__ double red[10][NT / 64];
   __shared__ PlateTab<BS> ptab;
   const T w0 = T(DDW0), w1 = T(DDW1);
-  const int tid = threadIdx.x;
-  const int i = tid % BS, j = tid / BS;
-  const int P = L.P, ng = L.ng;
+  const int P = L.P, ng = L.ng, P2 = P * P, fs = (int)L.fstride;
   const int64_t ib = blockIdx.x;
   if (ib >= nb) return;  // whole workgroup
   const int32_t* m = tab[ib].meta;
   const T* b = U + (int64_t)m[0] * L.bstride;
-  auto at = [&](int c, int ii, int jj, int kk) -> T {
-    return b[c * L.fstride + ((int64_t)(kk + ng) * P + (jj + ng)) * P + (ii + ng)];
+  PP pp(raw, xp, P, fs, (ng - 2) * P + (ng - 2), 2);
+  const int tid = pp.tid, i = pp.i, j = pp.j;
+  const int col = (j + ng) * P + (i + ng);
+  auto plane = [&](int mm) { return b + (2 * mm - 2 + ng) * P2; };
+  T ue[4], uo[4];
+  auto load_fine = [&](int mm) {  // the fine planes that coarse plane mm completes
+    const int kc = 2 * mm - 2, ko = kc - 3;
+    if (kc >= 0 && kc < BS)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) ue[c] = b[c * fs + col + (kc + ng) * P2];
+    if (ko >= 0 && ko < BS)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) uo[c] = b[c * fs + col + (ko + ng) * P2];
   };
+  pp.load(plane(0));
   double cmin = 1e300, cmax = -1e300;
   if (p.mask) {
     const MaskTime mt = mask_time(p, t);
@@ -637,79 +712,61 @@ __global__ __launch_bounds__(BS* BS) void detail_kernel(const Tab* __restrict__ 
       }
     }
   }
-  double dmc[4] = {0, 0, 0, 0}, umc[4] = {0, 0, 0, 0};
+  pp.store(0);
+  pp.load(plane(1));
+  load_fine(0);
+  T dmc[4] = {T(0), T(0), T(0), T(0)}, umc[4] = {T(0), T(0), T(0), T(0)};
   T y0[4], y1[4], y2[4], y3[4];  // Y of the coarse planes mm, mm-1, mm-2, mm-3
 #pragma unroll
   for (int c = 0; c < 4; ++c) y0[c] = y1[c] = y2[c] = y3[c] = T(0);
   const bool oddij = ((i | j) & 1) != 0;
+  lds_barrier();
+#pragma unroll 1
   for (int mm = 0; mm < S; ++mm) {
     const int kc = 2 * mm - 2;  // coarse plane
     const int ko = kc - 3;      // odd fine plane whose prediction this plane completes
-    // this thread's points of the fine planes kc and ko, loaded before the
-    // x pass so that their latency overlaps it
-    T ue[4], uo[4];
     const bool he = kc >= 0 && kc < BS, ho = ko >= 0 && ko < BS;
+    pp.xpass(mm);
+    if (mm + 1 < S) pp.store(mm + 1);
+    T fe[4], fo[4];
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
-      ue[c] = he ? at(c, i, j, kc) : T(0);
-      uo[c] = ho ? at(c, i, j, ko) : T(0);
+      fe[c] = ue[c];
+      fo[c] = uo[c];
     }
-    // x pass on the coarse rows j' = 2 jj - 2 of plane kc; the buffer of
-    // plane mm - 2 is free: every thread has passed plane mm - 1's barrier
-    T(*xb)[S * BS] = xp[mm & 1];
-    for (int q = tid; q < S * BS; q += NT) {
-      const int jj = q / BS, ii = q - jj * BS, jc = 2 * jj - 2;
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        T v;
-        if ((ii & 1) == 0)
-          v = at(c, ii, jc, kc);
-        else
-          v = w0 * at(c, ii - 3, jc, kc) + w1 * at(c, ii - 1, jc, kc) +
-              w1 * at(c, ii + 1, jc, kc) + w0 * at(c, ii + 3, jc, kc);
-        xb[c][q] = v;
-      }
-    }
-    __syncthreads();
-    // y pass: Y(i, j) of plane kc for the thread's column
+    if (mm + 2 < S) pp.load(plane(mm + 2));
+    if (mm + 1 < S) load_fine(mm + 1);
+    lds_barrier();
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
       y3[c] = y2[c];
       y2[c] = y1[c];
       y1[c] = y0[c];
-      if ((j & 1) == 0) {
-        y0[c] = xb[c][(j / 2 + 1) * BS + i];
-      } else {
-        const int jj = (j - 3) / 2 + 1;  // coarse row of j - 3
-        y0[c] = w0 * xb[c][jj * BS + i] + w1 * xb[c][(jj + 1) * BS + i] +
-                w1 * xb[c][(jj + 2) * BS + i] + w0 * xb[c][(jj + 3) * BS + i];
-      }
+      y0[c] = pp.ypass(mm, c);
     }
     // z pass: the even fine plane kc and the odd fine plane kc - 3 (taps
     // kc-6, kc-4, kc-2, kc = coarse planes mm-3 .. mm)
     if (he) {
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
-        const T u = ue[c];
-        umc[c] = fmax(umc[c], fabs((double)u));
-        if (oddij) dmc[c] = fmax(dmc[c], fabs((double)(u - y0[c])));
+        umc[c] = fmax(umc[c], fabs(fe[c]));
+        if (oddij) dmc[c] = fmax(dmc[c], fabs(fe[c] - y0[c]));
       }
     }
     if (ho) {
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
-        const T u = uo[c];
         const T pr = w0 * y3[c] + w1 * y2[c] + w1 * y1[c] + w0 * y0[c];
-        umc[c] = fmax(umc[c], fabs((double)u));
-        dmc[c] = fmax(dmc[c], fabs((double)(u - pr)));
+        umc[c] = fmax(umc[c], fabs(fo[c]));
+        dmc[c] = fmax(dmc[c], fabs(fo[c] - pr));
       }
     }
   }
   double v[10];
 #pragma unroll
   for (int c = 0; c < 4; ++c) {
-    v[c] = wave_max(umc[c]);
-    v[4 + c] = wave_max(dmc[c]);
+    v[c] = (double)wave_max(umc[c]);
+    v[4 + c] = (double)wave_max(dmc[c]);
   }
   v[8] = wave_min(cmin);
   v[9] = wave_max(cmax);
@@ -744,6 +801,7 @@ __global__ __launch_bounds__(1024) void thr_finalize(const Tab* __restrict__ tab
   __shared__ double inv[4];
   const int tid = threadIdx.x;
   double mx[4] = {0, 0, 0, 0};
+#pragma unroll 4
   for (int64_t q = tid; q < nb; q += blockDim.x)
 #pragma unroll
     for (int c = 0; c < 4; ++c) mx[c] = fmax(mx[c], part[q * 8 + c]);
@@ -873,72 +931,67 @@ __global__ __launch_bounds__(NT_GEN) void filter_kernel(const Tab* __restrict__ 
 // point Q = off + (i, j, k), off = octant offset (0 or bs per axis); even Q
 // copy the parent point Q/2, odd Q use the DD4 taps (Q-3)/2 .. (Q+3)/2 (the
 // parent's ghost layers included).  Separable and z-marching as in
-// detail_kernel: for each parent plane an x pass on the parent rows and a y
-// pass into a ring of 4 planes in LDS, then the z pass writes the child
-// planes the ring completes.
+// detail_kernel, 4 fields together, one workgroup per child: x and y passes of
+// each parent plane through LDS, a ring of 4 planes per column in registers, z
+// pass for the child planes the ring completes.  Bound: the child's writes
+// (5216 children of 16^3, FP64: 635 -> 470 us; with one field at a time each
+// plane waited for its loads behind 3 barriers, and rows were written in part).
 template <typename T, int BS>
-__global__ __launch_bounds__(NT_GEN) void prolong_kernel(const int32_t* __restrict__ list,
-                                                         int64_t n, T* __restrict__ U, Layout L) {
-  constexpr int S = BS / 2 + 4;  // parent points per axis: off/2 - 2 .. off/2 + bs/2 + 1
-  constexpr int B2 = BS * BS;
-  __shared__ T xp[S * BS];
-  __shared__ T yr[4][B2];
+__global__ __launch_bounds__(BS* BS) void prolong_kernel(const int32_t* __restrict__ list,
+                                                         int64_t n, T* U, Layout L) {
+  constexpr int S = BS / 2 + 4;  // parent points off/2 - 2 .. off/2 + bs/2 + 1
+  using PP = PredictPlanes<T, BS, S, 2>;
+  __shared__ T raw[2][4 * PP::S2], xp[2][4 * PP::NX];
   const T w0 = T(DDW0), w1 = T(DDW1);
-  const int tid = threadIdx.x, P = L.P, ng = L.ng;
+  const int P = L.P, ng = L.ng, P2 = P * P, fs = (int)L.fstride;
   for (int64_t w = blockIdx.x; w < n; w += gridDim.x) {
     const int32_t ps = list[3 * w], cs = list[3 * w + 1], oct = list[3 * w + 2];
     const int h0 = (oct & 1) * (BS / 2) - 2, h1 = ((oct >> 1) & 1) * (BS / 2) - 2,
               h2 = ((oct >> 2) & 1) * (BS / 2) - 2;  // first parent index per axis
-    const T* par = U + (int64_t)ps * L.bstride;
-    T* ch = U + (int64_t)cs * L.bstride;
-    auto pidx = [&](int i, int j, int k) -> int64_t {
-      return ((int64_t)(k + ng) * P + (j + ng)) * P + (i + ng);
-    };
-    for (int c = 0; c < 4; ++c) {
-      const T* pc = par + c * L.fstride;
-      T* cc = ch + c * L.fstride;
-      for (int mm = 0; mm < S; ++mm) {
-        const int kz = h2 + mm;  // parent plane
-        __syncthreads();
-        // x pass: xp[jj][i] for the parent rows j = h1 + jj; child i has
-        // Q = 2 (h0 + 2) + i, even -> parent point Q/2, odd -> taps
-        for (int q = tid; q < S * BS; q += NT_GEN) {
-          const int jj = q / BS, i = q - jj * BS;
-          const int64_t row = pidx(0, h1 + jj, kz);
-          const int base = h0 + 2 + (i >> 1);  // parent index of Q/2 (even Q)
-          T v;
-          if ((i & 1) == 0)
-            v = pc[row + base];
-          else  // taps (Q-3)/2 .. (Q+3)/2 = base-1 .. base+2
-            v = w0 * pc[row + base - 1] + w1 * pc[row + base] + w1 * pc[row + base + 1] +
-                w0 * pc[row + base + 2];
-          xp[q] = v;
-        }
-        __syncthreads();
-        T* yo = yr[mm & 3];
-        for (int q = tid; q < B2; q += NT_GEN) {
-          const int j = q / BS, i = q - j * BS;
-          const int jj = 2 + (j >> 1);  // row of Q/2 in xp
-          T v;
-          if ((j & 1) == 0)
-            v = xp[jj * BS + i];
-          else
-            v = w0 * xp[(jj - 1) * BS + i] + w1 * xp[jj * BS + i] + w1 * xp[(jj + 1) * BS + i] +
-                w0 * xp[(jj + 2) * BS + i];
-          yo[q] = v;
-        }
-        __syncthreads();
-        // z pass: child plane k even uses plane mm = 2 + k/2; k odd uses
-        // planes 1 + (k-1)/2 .. 4 + (k-1)/2, complete when mm = 4 + (k-1)/2
-        const int ke = 2 * (mm - 2), ko = 2 * (mm - 4) + 1;
-        for (int q = tid; q < B2; q += NT_GEN) {
-          const int j = q / BS, i = q - j * BS;
-          if (ke >= 0 && ke < BS) cc[pidx(i, j, ke)] = yo[q];
-          if (ko >= 0 && ko < BS)
-            cc[pidx(i, j, ko)] = w0 * yr[(mm + 1) & 3][q] + w1 * yr[(mm + 2) & 3][q] +
-                                 w1 * yr[(mm + 3) & 3][q] + w0 * yo[q];
-        }
+    const T* __restrict__ par = U + (int64_t)ps * L.bstride;
+    T* __restrict__ ch = U + (int64_t)cs * L.bstride;
+    PP pp(raw, xp, P, fs, (h1 + ng) * P + (h0 + ng), 1);
+    const int col = (pp.j + ng) * P + (pp.i + ng);
+    // the x-ghost columns of each row are cleared too, so that whole cache
+    // lines are written (a child's ghost layers carry no values yet)
+    const int gx = pp.i < ng ? -ng : (pp.i >= BS - ng ? ng : 0);
+    auto plane = [&](int mm) { return par + (h2 + mm + ng) * P2; };
+    pp.load(plane(0));
+    T y0[4], y1[4], y2[4], y3[4];  // parent planes mm, mm-1, mm-2, mm-3
+#pragma unroll
+    for (int c = 0; c < 4; ++c) y0[c] = y1[c] = y2[c] = y3[c] = T(0);
+    lds_barrier();  // the last child's planes are no longer read
+    pp.store(0);
+    pp.load(plane(1));
+    lds_barrier();
+#pragma unroll 1
+    for (int mm = 0; mm < S; ++mm) {
+      pp.xpass(mm);
+      if (mm + 1 < S) pp.store(mm + 1);
+      if (mm + 2 < S) pp.load(plane(mm + 2));
+      lds_barrier();
+      // z pass: child plane k even uses plane mm = 2 + k/2; k odd uses planes
+      // 1 + (k-1)/2 .. 4 + (k-1)/2, complete when mm = 4 + (k-1)/2
+      const int ke = 2 * (mm - 2), ko = 2 * (mm - 4) + 1;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        y3[c] = y2[c];
+        y2[c] = y1[c];
+        y1[c] = y0[c];
+        y0[c] = pp.ypass(mm, c);
       }
+      if (ke >= 0 && ke < BS)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          ch[c * fs + col + (ke + ng) * P2] = y0[c];
+          if (gx) ch[c * fs + col + gx + (ke + ng) * P2] = T(0);
+        }
+      if (ko >= 0 && ko < BS)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          ch[c * fs + col + (ko + ng) * P2] = w0 * y3[c] + w1 * y2[c] + w1 * y1[c] + w0 * y0[c];
+          if (gx) ch[c * fs + col + gx + (ko + ng) * P2] = T(0);
+        }
     }
   }
 }
@@ -1647,13 +1700,13 @@ static hipError_t prolong_t(const wacm_grid* g, T* U, int64_t n, hipStream_t st)
   const unsigned grid = grid_for(n, 8);
   switch (g->d.bs) {
     case 16:
-      prolong_kernel<T, 16><<<grid, NT_GEN, 0, st>>>(g->d_list, n, U, pool_layout(g));
+      prolong_kernel<T, 16><<<grid, 256, 0, st>>>(g->d_list, n, U, pool_layout(g));
       break;
     case 24:
-      prolong_kernel<T, 24><<<grid, NT_GEN, 0, st>>>(g->d_list, n, U, pool_layout(g));
+      prolong_kernel<T, 24><<<grid, 576, 0, st>>>(g->d_list, n, U, pool_layout(g));
       break;
     case 32:
-      prolong_kernel<T, 32><<<grid, NT_GEN, 0, st>>>(g->d_list, n, U, pool_layout(g));
+      prolong_kernel<T, 32><<<grid, 1024, 0, st>>>(g->d_list, n, U, pool_layout(g));
       break;
     default:
       return hipErrorInvalidValue;
