@@ -120,12 +120,15 @@ typedef struct {
  * block (bs^2 threads), 8 a tile of 8 rows of the block's columns (8 bs
  * threads, smaller workgroups, more of them per CU); pen_split: 2 runs the
  * blocks where the penalization and sponge terms vanish at every point (far
- * from the mask by 40 smoothing widths, 12 with clipping, and outside the
+ * from the mask by 20 smoothing widths, 12 with clipping, and outside the
  * sponge) through the unpenalized variant and the others through the
  * penalized one, 1 does so when it pays (at least 2048 active blocks and,
  * for a static mask or sponge, at least 512 without penalization), 0 runs
  * every block through the penalized one when a mask, sponge or dus is
- * present.  Results are the same bit for bit.  Default {0, 1, -1, 1, 0, 1}. */
+ * present.  Results are the same bit for bit.  Default {0, 1, -1, 1, 0, 1};
+ * as long as no schedule is set on a grid the library departs from it by size
+ * and type (tiles of 8 rows and early loads for FP64 blocks of 24^3 and more;
+ * work counters, in the call's own work buffer, for large grids). */
 typedef struct {
   int32_t wg_per_cu;
   int32_t xcd_map;

@@ -280,6 +280,7 @@ int wacm_set_schedule(wacm_grid* g, const wacm_schedule* s) {
       (s->tile_rows != 0 && s->tile_rows != 8) || (s->pen_split < 0 || s->pen_split > 2))
     return fail(WACM_E_INVAL, "schedule value out of range");
   g->sched = *s;
+  g->sched_set = true;
   return WACM_OK;
 }
 

@@ -1184,13 +1184,12 @@ static unsigned grid_for(int64_t n, int per_cu) {
   return (unsigned)(n < cap ? (n > 0 ? n : 1) : cap);
 }
 
-// The face-halo kernel follows the stage kernel's XCD mapping: with xcd_map
-// 2 it takes its faces from the second set of work counters.
+// The face-halo kernel follows the stage kernel's XCD mapping: with work
+// counters (q) it takes its faces from a second set of them.
 template <typename T>
 static hipError_t nlface_launch(const wacm_grid* g, const T* in, const Layout& Lin, T* hb,
-                                hipStream_t st) {
+                                int* q, hipStream_t st) {
   const unsigned grid = grid_for(g->n_cface, 8);
-  int* q = g->sched.xcd_map == 2 ? g->d_queue + 8 * QSTRIDE : nullptr;
   if (q) {
     queue_clear<<<1, 8 * QSTRIDE, 0, st>>>(q);
     hipError_t e = hipGetLastError();
@@ -1331,6 +1330,46 @@ hipError_t launch_sync_lifted_stage(const wacm_grid* g, void* U, const int32_t* 
 
 hipError_t launch_sync(const wacm_grid* g, void* U, hipStream_t st) {
   return g->d.dtype == WACM_F64 ? sync_t(g, (double*)U, st) : sync_t(g, (float*)U, st);
+}
+
+// The second set of work counters, for the face-halo kernel.
+template <typename T>
+static int* face_queue(const StageArgs<T>& a) {
+  return a.queue ? a.queue + 8 * QSTRIDE : nullptr;
+}
+
+// The RK stages' schedule: the caller's, or if none was set on the grid the
+// default one with, for FP64 blocks of 24^3 and more, tiles of 8 rows and early
+// epilogue loads (ms per step, whole blocks -> tiles: 24^3 1.10 -> 1.07 at 603
+// blocks, 10.30 -> 9.40 at 6000; 32^3 8.91 -> 5.17 at 1520, where a whole
+// block's 16 waves leave 128 registers and spill).  FP32 keeps whole blocks
+// below the size of large_grid (24^3, 2024 blocks: 1.90 against 1.95).
+static wacm_schedule stage_schedule(const wacm_grid* g) {
+  wacm_schedule s = g->sched;
+  if (!g->sched_set && g->d.dtype == WACM_F64 && g->d.bs >= 24) {
+    s.tile_rows = 8;
+    s.prefetch = 1;
+  }
+  return s;
+}
+
+// Whether a grid without a schedule of its own takes tiles from work counters:
+// from 4096 blocks of 24^3 on (ms per step at 6000 blocks, static -> counters:
+// FP64 9.40 -> 9.20, FP32 whole blocks 5.48 -> 5.30; at 20028 blocks FP64 31.4 ->
+// 30.0; no gain at 2024 blocks, for 16^3, or for FP32 32^3).
+static bool large_grid(const wacm_grid* g) {
+  const int bs = g->d.bs;
+  return !g->sched_set && (bs == 24 || (bs == 32 && g->d.dtype == WACM_F64)) &&
+         g->nb * (int64_t)(bs * bs * bs) >= (int64_t)4096 * 24 * 24 * 24;
+}
+
+// Room for a call's own work counters in its work buffer: the halo of a face
+// next to a leaf of the same level is read in place and never stored.  -1: none.
+static int64_t spare_face(const wacm_grid* g) {
+  for (const Tab& t : g->h_tab)
+    for (int f = 0; f < 6; ++f)
+      if (t.kind[FACE_REGION[f]] == 0) return (int64_t)t.meta[0] * 6 + f;
+  return -1;
 }
 
 template <typename T>
@@ -1487,8 +1526,9 @@ static hipError_t stage_input_t(const wacm_grid* g, const wacm_params* p, int s,
   a.dt_host = dt;
   a.kscale = s == 2 ? 0.5 : 1.0;
   if (g->n_cface > 0)
-    if (hipError_t e = nlface_launch<T>(g, in, a.Lin, hb, st); e != hipSuccess) return e;
-  return stage_run<T>(s == 1 ? 1 : 3, g->d.bs, a, g->sched, st);
+    if (hipError_t e = nlface_launch<T>(g, in, a.Lin, hb, face_queue(a), st); e != hipSuccess)
+      return e;
+  return stage_run<T>(s == 1 ? 1 : 3, g->d.bs, a, stage_schedule(g), st);
 }
 
 hipError_t launch_stage_input(const wacm_grid* g, const wacm_params* p, int s, double t,
@@ -1504,8 +1544,10 @@ hipError_t launch_stage_input(const wacm_grid* g, const wacm_params* p, int s, d
 hipError_t launch_nlface(const wacm_grid* g, const void* in, const Layout& Lin, void* hb,
                          hipStream_t st) {
   if (g->n_cface == 0) return hipSuccess;
-  return g->d.dtype == WACM_F64 ? nlface_launch<double>(g, (const double*)in, Lin, (double*)hb, st)
-                                : nlface_launch<float>(g, (const float*)in, Lin, (float*)hb, st);
+  int* q = g->sched.xcd_map == 2 ? g->d_queue + 8 * QSTRIDE : nullptr;
+  return g->d.dtype == WACM_F64
+             ? nlface_launch<double>(g, (const double*)in, Lin, (double*)hb, q, st)
+             : nlface_launch<float>(g, (const float*)in, Lin, (float*)hb, q, st);
 }
 
 template <typename T>
@@ -1532,6 +1574,14 @@ static hipError_t rk4_t(const wacm_grid* g, const wacm_params* p, double* t_dev,
   T* ins[4] = {U, ping, pong, ping};
   T* outs[4] = {ping, pong, ping, U};
   Layout lins[4] = {Lp, Ls, Ls, Ls};
+  wacm_schedule sched = stage_schedule(g);
+  if (large_grid(g))
+    if (const int64_t f = spare_face(g); f >= 0) {
+      // counters of this call alone: calls on one grid may overlap in time
+      a.queue = reinterpret_cast<int*>(hb + f * 12 * g->d.bs * g->d.bs);
+      a.xcd_map = 2;
+      sched.tile_rows = 8;
+    }
   const double hmin = g->d.L / (double(int64_t(1) << g->jfine) * g->d.bs);
   int64_t nmax = 0;  // velocity maxima the last stage of the previous step left
   // blocks without penalization first (the adaptation lists are free
@@ -1577,13 +1627,13 @@ static hipError_t rk4_t(const wacm_grid* g, const wacm_params* p, double* t_dev,
       a.nmax = a.umax_part ? &nmax : nullptr;
       if (g->n_cface > 0) {
         ProfScope ps(g, 1, st);
-        if ((e = nlface_launch<T>(g, a.in, a.Lin, hb, st)) != hipSuccess) return e;
+        if ((e = nlface_launch<T>(g, a.in, a.Lin, hb, face_queue(a), st)) != hipSuccess) return e;
       }
       ProfScope ps(g, 2, st);
       if (s == 0 && split_step &&
           (e = pen_classify(g, p, t_dev, dt_dev, plist, pcnt, pflag, st)) != hipSuccess)
         return e;
-      e = stage_run<T>(s + 1, g->d.bs, a, g->sched, st);
+      e = stage_run<T>(s + 1, g->d.bs, a, sched, st);
       if (e != hipSuccess) return e;
     }
     ProfScope ps(g, 3, st);
