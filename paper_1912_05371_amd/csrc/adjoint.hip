@@ -503,8 +503,7 @@ void adj_stage_kernel(AdjStage<T> a) {
   __shared__ T red[NT / 64];
   const int tid = threadIdx.x, x = tid % BS, yl = tid / BS;
   const T am[3] = {T(TW1), T(TW2), T(TW3)};
-  const T c2a = T(D2A), c2b = T(D2B), c2c = T(D2C);
-  const T nu = T(a.p.nu), c0sq = T(a.p.c0 * a.p.c0), cg = T(a.p.c_gamma), vs = a.vs;
+  const T c0sq = T(a.p.c0 * a.p.c0), cg = T(a.p.c_gamma), vs = a.vs;
   const bool xin = a.Lu.xs != 0;
   const int cidx = (yl + H) * W + (x + H);
   // this thread's halo point of every plane: x faces of the tile's rows, then
@@ -556,6 +555,10 @@ void adj_stage_kernel(AdjStage<T> a) {
     const bool zhi = __builtin_amdgcn_readfirstlane(meta[7]) != 0;
     const double h = a.Ldom / (double(int64_t(1) << J) * BS);
     const T ih = T(1.0 / h), ih2 = T(1.0 / (h * h));
+    // weights of rhs_adj_kernel, rounded as there: an FP32 weight's rounding
+    // is an error of every point alike, which the gradients would add up
+    const T ah[3] = {am[0] * ih, am[1] * ih, am[2] * ih};
+    const T w2[3] = {T(a.p.nu * D2C) * ih2, T(a.p.nu * D2B) * ih2, T(a.p.nu * D2A) * ih2};
     // uniform block origins; this thread's column offsets and plane steps
     const T* ub = a.u + (int64_t)slot * a.Lu.bstride;
     const T* vb = a.v + (int64_t)slot * a.Lv.bstride;
@@ -680,30 +683,30 @@ void adj_stage_kernel(AdjStage<T> a) {
         T dv = T(0);  // D1_d kb_d
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
-          T pr = T(0), lap = c2c * v[c], du = T(0);
+          T pr = w2[0] * v[c], du = T(0);
 #pragma unroll
           for (int m = 0; m < 3; ++m) {
             const T vp = at(c, m + 1), vm = at(c, -1 - m);
-            pr += am[m] * (vp * up[m] - vm * um[m]);
-            if (m < 2) lap += (m == 0 ? c2b : c2a) * (vp + vm);
-            if (c == d) dv += am[m] * (vp - vm);
+            pr += ah[m] * (vp * up[m] - vm * um[m]);
+            if (m < 2) pr += w2[m + 1] * (vp + vm);
+            if (c == d) dv += ah[m] * (vp - vm);
             du += am[m] * (c == d ? up[m] - um[m] : at(4 + c, m + 1) - at(4 + c, -1 - m));
           }
-          acc[c] += ih * pr + (nu * ih2) * lap;
+          acc[c] += pr;
           acc[d] -= v[c] * (ih * du);
         }
         T dp = T(0);
 #pragma unroll
-        for (int m = 0; m < 3; ++m) dp += am[m] * (at(3, m + 1) - at(3, -1 - m));
-        acc[d] += c0sq * (ih * dp);
-        acc[3] += ih * dv;
+        for (int m = 0; m < 3; ++m) dp += (c0sq * ah[m]) * (at(3, m + 1) - at(3, -1 - m));
+        acc[d] += dp;
+        acc[3] += dv;
       }
       acc[3] -= cg * v[3];
       bad += T(0) * (v[0] + v[1] + v[2]);
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
         sob[socol + z * sozs + c * (int)a.Lso.fstride] = sv[c] + acc[c];
-        if (NEXT) kob[ccol + z * BS * BS + c * B3] = a.lamw * lv[c] + a.kw * acc[c];
+        if (NEXT) kob[ccol + z * BS * BS + c * B3] = fma(a.kw, acc[c], a.lamw * lv[c]);
       }
       if (z + 1 < BS) {
         T(*nb_)[W * WY] = slab[(z + 1) & 1];
@@ -820,7 +823,7 @@ __global__ __launch_bounds__(NT_GEN) void adj_pen_kernel(AdjStage<T> a) {
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
           so[c * a.Lso.fstride] = s0[c] + acc[c];
-          if (a.kn) ko[q + c * B3] = k0[c] + a.kw * acc[c];
+          if (a.kn) ko[q + c * B3] = fma(a.kw, acc[c], k0[c]);
         }
       }
     }
@@ -863,8 +866,8 @@ __global__ __launch_bounds__(NT_GEN) void adj_face_kernel(const Tab* __restrict_
   constexpr double W4[4] = {DDW0, DDW1, DDW1, DDW0};
   const int tid = threadIdx.x;
   const T am[3] = {T(TW1), T(TW2), T(TW3)};
-  const T w2[3] = {T(D2C), T(D2B), T(D2A)};
-  const T nu = T(a.p.nu), c0sq = T(a.p.c0 * a.p.c0);
+  const T w2[3] = {T(a.p.nu * D2C), T(a.p.nu * D2B), T(a.p.nu * D2A)};
+  const T c0sq = T(a.p.c0 * a.p.c0);
   for (int64_t wk = blockIdx.x; wk < n; wk += gridDim.x) {
     const Tab& tb = tab[cf[2 * wk]];
     const int f = cf[2 * wk + 1], axis = f >> 1, side = f & 1;
@@ -912,8 +915,8 @@ __global__ __launch_bounds__(NT_GEN) void adj_face_kernel(const Tab* __restrict_
               const T w = am[m] * ih * sg;
               if (c < 3) {
                 s += w * (v[k][c][e] * un[k][e]);
-                if (c == axis) s += c0sq * (w * v[k][3][e]);
-                if (m < 2) s += (nu * w2[m + 1] * ih2) * v[k][c][e];
+                if (c == axis) s += (c0sq * w) * v[k][3][e];
+                if (m < 2) s += (w2[m + 1] * ih2) * v[k][c][e];
               } else {
                 s += w * (axis == 0 ? v[k][0][e] : (axis == 1 ? v[k][1][e] : v[k][2][e]));
               }

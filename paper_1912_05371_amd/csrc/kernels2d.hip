@@ -89,6 +89,9 @@ __global__ __launch_bounds__(BS* BS) void stage2d_kernel(const Tab* __restrict__
   const double dt = MODE == 0 ? 0.0 : *dt_dev;
   const T a1 = T(TW1), a2 = T(TW2), a3 = T(TW3);
   const T c2a = T(D2A), c2b = T(D2B), c2c = T(D2C);
+  auto lap1 = [&](T m2, T m1, T c0, T p1, T p2) {
+    return fma(c2a, p2, fma(c2b, p1, fma(c2c, c0, fma(c2b, m1, c2a * m2))));
+  };
   const T nu = T(p.nu), c0sq = T(p.c0 * p.c0), cg = T(p.c_gamma);
   const int ct = (y + 3) * W + (x + 3);
   for (int64_t ib = blockIdx.x; ib < nb; ib += gridDim.x) {
@@ -126,27 +129,27 @@ __global__ __launch_bounds__(BS* BS) void stage2d_kernel(const Tab* __restrict__
       for (int c = 0; c < 3; ++c) tile[c][(j + 3) * W + (i + 3)] = v[c];
     }
     __syncthreads();
-    T dx[3], dy[3], lap[2];
+    // in explicit multiply-adds, so that every stage and type rounds alike
+    T dx[3], dy[3], lap[2];  // the first derivatives still without 1/h
+#pragma unroll
     for (int c = 0; c < 3; ++c) {
       const T* s = tile[c];
-      dx[c] = (a1 * (s[ct + 1] - s[ct - 1]) + a2 * (s[ct + 2] - s[ct - 2]) +
-               a3 * (s[ct + 3] - s[ct - 3])) *
-              ih;
-      dy[c] = (a1 * (s[ct + W] - s[ct - W]) + a2 * (s[ct + 2 * W] - s[ct - 2 * W]) +
-               a3 * (s[ct + 3 * W] - s[ct - 3 * W])) *
-              ih;
+      dx[c] = fma(a3, s[ct + 3] - s[ct - 3],
+                  fma(a1, s[ct + 1] - s[ct - 1], a2 * (s[ct + 2] - s[ct - 2])));
+      dy[c] = fma(a3, s[ct + 3 * W] - s[ct - 3 * W],
+                  fma(a1, s[ct + W] - s[ct - W], a2 * (s[ct + 2 * W] - s[ct - 2 * W])));
       if (c < 2)
-        lap[c] = ((c2a * s[ct - 2] + c2b * s[ct - 1] + c2c * s[ct] + c2b * s[ct + 1] +
-                   c2a * s[ct + 2]) +
-                  (c2a * s[ct - 2 * W] + c2b * s[ct - W] + c2c * s[ct] + c2b * s[ct + W] +
-                   c2a * s[ct + 2 * W])) *
-                 ih2;
+        lap[c] = lap1(s[ct - 2], s[ct - 1], s[ct], s[ct + 1], s[ct + 2]) +
+                 lap1(s[ct - 2 * W], s[ct - W], s[ct], s[ct + W], s[ct + 2 * W]);
     }
     const T u = own[0], v = own[1], pr = own[2];
     T r[3];
-    r[0] = -(u * dx[0] + v * dy[0]) - dx[2] + nu * lap[0];
-    r[1] = -(u * dx[1] + v * dy[1]) - dy[2] + nu * lap[1];
-    r[2] = -c0sq * (dx[0] + dy[1]) - cg * pr;
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      const T conv = fma(u, dx[c] * ih, v * (dy[c] * ih));
+      r[c] = fma(lap[c] * ih2, nu, fma(c == 0 ? -dx[2] : -dy[2], ih, -conv));
+    }
+    r[2] = fma(-c0sq, fma(dy[1], ih, dx[0] * ih), -cg * pr);
     T nv[3];
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
@@ -154,13 +157,13 @@ __global__ __launch_bounds__(BS* BS) void stage2d_kernel(const Tab* __restrict__
       if (MODE == 0) {
         out[oc] = r[c];
       } else if (MODE == 1) {
-        acc[oc] = own[c] + T(dt / 6.0) * r[c];
-        out[oc] = own[c] + T(0.5 * dt) * r[c];
+        acc[oc] = fma(r[c], T(dt / 6.0), own[c]);
+        out[oc] = fma(r[c], T(0.5 * dt), own[c]);
       } else if (MODE == 2 || MODE == 3) {
-        acc[oc] = a0[c] + T(dt / 3.0) * r[c];
-        out[oc] = u0[c] + T(MODE == 2 ? 0.5 * dt : dt) * r[c];
+        acc[oc] = fma(r[c], T(dt / 3.0), a0[c]);
+        out[oc] = fma(r[c], T(MODE == 2 ? 0.5 * dt : dt), u0[c]);
       } else {
-        nv[c] = a0[c] + T(dt / 6.0) * r[c];
+        nv[c] = fma(r[c], T(dt / 6.0), a0[c]);
         un[oc] = nv[c];
       }
     }
