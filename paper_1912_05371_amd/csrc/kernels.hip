@@ -116,9 +116,15 @@ __global__ __launch_bounds__(NT_GEN) void sync_lattice_kernel(const Tab* __restr
 // one work item per (block, region).  The region's box of ghost points is
 // predicted separably: the even lattice box around it (read from whichever
 // leaves hold it) is gathered for all 4 fields at once into registers, then,
-// one field at a time through LDS, predicted along x, y and z and written.
-// The same tensor-product DD4 values as the point-wise fill, summed in
-// another order.  Requires ng <= SC_MAXG (checked by the launcher).
+// one field at a time, predicted along x through LDS, in pairs of an even and
+// an odd point that share the lattice values, and along y and z by one thread
+// per column (i, j), which marches along z with the last 4 lattice layers in
+// registers and writes the ghost points.  The same tensor-product DD4 values
+// as the point-wise fill, summed in another order.  Requires ng <= SC_MAXG
+// (checked by the launcher).  Bound: its ghost layers lie in partly written
+// cache lines; it moves 1.25 GB in 411 us on 2000 blocks of 24^3, FP64 (561 us
+// with a pass per axis through LDS and hardware divisions), 304 us on 1500
+// blocks of 32^3, FP32 (481 before).
 constexpr int SC_MAXG = 6;
 template <int BS>
 struct SyncCoarseDims {
@@ -126,8 +132,16 @@ struct SyncCoarseDims {
   static constexpr int MG = SC_MAXG;         // lattice points along a ghost axis, ng <= 6
   static constexpr int NSRC = MG * S * S;    // largest lattice box (a face region)
   static constexpr int NA = MG * S * BS;     // largest x-pass box
-  static constexpr int NB = MG * BS * BS;    // largest y-pass box
 };
+
+// p / d for p d < 2^32, d > 1: the box edges are known at run time only, and a
+// division of the hardware's instruction set costs some 25 operations.
+struct FastDiv {
+  uint32_t inv;
+  __device__ explicit FastDiv(int d) : inv(0xffffffffu / (uint32_t)d + 1u) {}
+  __device__ int operator()(int p) const { return (int)__umulhi((uint32_t)p, inv); }
+};
+
 template <typename T, int BS>
 __global__ __launch_bounds__(NT_GEN) void sync_coarser_kernel(const Tab* __restrict__ tab,
                                                               const int32_t* __restrict__ cr,
@@ -136,11 +150,14 @@ __global__ __launch_bounds__(NT_GEN) void sync_coarser_kernel(const Tab* __restr
   using D = SyncCoarseDims<BS>;
   constexpr int PER = (D::NSRC + NT_GEN - 1) / NT_GEN;
   __shared__ Tab st;
-  __shared__ T buf0[D::NSRC > D::NB ? D::NSRC : D::NB];  // lattice, then the y pass
-  __shared__ T buf1[D::NA];                               // x pass
+  __shared__ T buf0[D::NSRC];  // lattice box of one field
+  __shared__ T buf1[D::NA];    // after the x pass: [az][ay][i]
   const T w0 = T(DDW0), w1 = T(DDW1);
   const int tid = threadIdx.x, ng = L.ng, P = L.P;
-  const int64_t fs = L.fstride;
+  const int64_t fs = L.fstride, zs = (int64_t)P * P;
+  auto odd = [&](T a0, T a1, T a2, T a3) {
+    return fma(w0, a3, fma(w1, a2, fma(w1, a1, w0 * a0)));
+  };
   for (int64_t wk = blockIdx.x; wk < n; wk += gridDim.x) {
     const int32_t ib = cr[2 * wk], r = cr[2 * wk + 1];
     __syncthreads();
@@ -159,17 +176,27 @@ __global__ __launch_bounds__(NT_GEN) void sync_coarser_kernel(const Tab* __restr
       m[d] = (hi + ((hi & 1) ? 3 : 2) - e0[d]) / 2 + 1;
     }
     const int nsrc = m[0] * m[1] * m[2];
+    const FastDiv by_m0(m[0]), by_m1(m[1]), by_n0(nn[0]);
     T v[PER][4];
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
       const int p = tid + q * NT_GEN;
       if (p < nsrc) {
-        const int ax = p % m[0], rest = p / m[0], ay = rest % m[1], az = rest / m[1];
+        const int rest = by_m0(p), ax = p - rest * m[0];
+        const int az = by_m1(rest), ay = rest - az * m[1];
         const int64_t o = point_offset(st, BS, L, e0[0] + 2 * ax, e0[1] + 2 * ay, e0[2] + 2 * az);
 #pragma unroll
         for (int c = 0; c < 4; ++c) v[q][c] = U[o + c * fs];
       }
     }
+    // pairs (2t, 2t + 1) along x: the lattice values a .. a + 3 with a = t - 1
+    // - e0/2 give the even point (a + 1) and the odd one
+    const int t0 = lo[0] >> 1, npx = ((lo[0] + nn[0] - 1) >> 1) - t0 + 1;
+    const FastDiv by_npx(npx);
+    const int nxp = m[2] * m[1] * npx, hi0 = lo[0] + nn[0] - 1;
+    // a z axis along the interior is marched in two runs: more threads
+    const int ncol = nn[1] * nn[0], nrun = rd[2] == 1 ? 2 : 1, len = nn[2] / nrun;
+    const int rowz = m[1] * nn[0];
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
 #pragma unroll
@@ -177,57 +204,42 @@ __global__ __launch_bounds__(NT_GEN) void sync_coarser_kernel(const Tab* __restr
         const int p = tid + q * NT_GEN;
         if (p < nsrc) buf0[p] = v[q][c];
       }
-      __syncthreads();
-      // x pass: buf1[az][ay][i], i over the box
-      for (int p = tid; p < m[2] * m[1] * nn[0]; p += NT_GEN) {
-        const int ii = p % nn[0], row = p / nn[0];
-        const int i = lo[0] + ii;
-        const T* s = buf0 + row * m[0];
-        T val;
-        if ((i & 1) == 0) {
-          val = s[(i - e0[0]) / 2];
-        } else {
-          const int a = (i - 3 - e0[0]) / 2;
-          val = w0 * s[a] + w1 * s[a + 1] + w1 * s[a + 2] + w0 * s[a + 3];
-        }
-        buf1[p] = val;
+      lds_barrier();
+      for (int p = tid; p < nxp; p += NT_GEN) {
+        const int row = by_npx(p), t = t0 + (p - row * npx), i = 2 * t;
+        const T* s = buf0 + row * m[0] + (t - 1 - e0[0] / 2);
+        T* o = buf1 + row * nn[0] + (i - lo[0]);
+        if (i >= lo[0]) o[0] = s[1];
+        if (i < hi0) o[1] = odd(s[0], s[1], s[2], s[3]);
       }
-      __syncthreads();
-      // y pass: buf0[az][j][i]
-      for (int p = tid; p < m[2] * nn[1] * nn[0]; p += NT_GEN) {
-        const int ii = p % nn[0], rest = p / nn[0], jj = rest % nn[1], az = rest / nn[1];
-        const int j = lo[1] + jj;
-        const T* s = buf1 + az * m[1] * nn[0] + ii;
-        T val;
-        if ((j & 1) == 0) {
-          val = s[((j - e0[1]) / 2) * nn[0]];
-        } else {
-          const int a = (j - 3 - e0[1]) / 2;
-          val = w0 * s[a * nn[0]] + w1 * s[(a + 1) * nn[0]] + w1 * s[(a + 2) * nn[0]] +
-                w0 * s[(a + 3) * nn[0]];
+      lds_barrier();
+      for (int p = tid; p < nrun * ncol; p += NT_GEN) {
+        const int run = p >= ncol ? 1 : 0, col = p - run * ncol;
+        const int jj = by_n0(col), ii = col - jj * nn[0], j = lo[1] + jj;
+        const bool je = (j & 1) == 0;
+        const T* sy = buf1 + ((je ? j : j - 3) - e0[1]) / 2 * nn[0] + ii;
+        auto y = [&](int az) -> T {  // after the y pass, at lattice layer az
+          const T* q = sy + az * rowz;
+          if (je) return q[0];
+          return odd(q[0], q[nn[0]], q[2 * nn[0]], q[3 * nn[0]]);
+        };
+        const int kA = lo[2] + run * len, kB = kA + len;
+        T* out = dst + c * fs + (int64_t)(j + ng) * P + (lo[0] + ii + ng);
+        int az = (kA >> 1) - 1 - e0[2] / 2;
+        T a0 = y(az), a1 = y(az + 1), a2 = y(az + 2);
+        for (int k = kA & ~1; k < kB; k += 2) {
+          T* ok = out + (k + ng) * zs;
+          if (k >= kA) ok[0] = a1;
+          if (k + 1 < kB) {
+            const T a3 = y(az + 3);
+            ok[zs] = odd(a0, a1, a2, a3);
+            a0 = a1;
+            a1 = a2;
+            a2 = a3;
+            ++az;
+          }
         }
-        buf0[p] = val;
       }
-      __syncthreads();
-      // z pass into the ghost points
-      const int plane = nn[1] * nn[0];
-      for (int p = tid; p < nn[2] * plane; p += NT_GEN) {
-        const int kk = p / plane, q2 = p - kk * plane;
-        const int k = lo[2] + kk;
-        const T* s = buf0 + q2;
-        T val;
-        if ((k & 1) == 0) {
-          val = s[((k - e0[2]) / 2) * plane];
-        } else {
-          const int a = (k - 3 - e0[2]) / 2;
-          val = w0 * s[a * plane] + w1 * s[(a + 1) * plane] + w1 * s[(a + 2) * plane] +
-                w0 * s[(a + 3) * plane];
-        }
-        const int jj = q2 / nn[0], ii = q2 - jj * nn[0];
-        const int64_t o = ((int64_t)(k + ng) * P + (lo[1] + jj + ng)) * P + (lo[0] + ii + ng);
-        dst[o + c * fs] = val;
-      }
-      __syncthreads();
     }
   }
 }
@@ -1233,9 +1245,12 @@ static WorkParts work_parts(const wacm_grid* g) {
 
 size_t work_bytes(const wacm_grid* g) { return work_parts(g).total; }
 
+// Many workgroups of few regions each: faces, edges and corners differ 16-fold
+// in work, and what a fixed share of them leaves uneven costs 18% (8 workgroups
+// per CU: 486 us and 370 us in place of the figures above).
 template <typename T, int BS>
 static void sync_coarser_launch(const wacm_grid* g, T* U, hipStream_t st) {
-  sync_coarser_kernel<T, BS><<<grid_for(g->n_cregion, 8), NT_GEN, 0, st>>>(
+  sync_coarser_kernel<T, BS><<<grid_for(g->n_cregion, 64), NT_GEN, 0, st>>>(
       g->d_tab, g->d_cregion, g->n_cregion, U, pool_layout(g));
 }
 
