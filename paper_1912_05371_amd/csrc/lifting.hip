@@ -14,6 +14,7 @@
 #include <hip/hip_runtime.h>
 
 #include "resolve.h"
+#include "stage.h"
 #include "wacm_internal.h"
 
 namespace wacm {
@@ -29,11 +30,7 @@ constexpr double LIFT_TAP[13] = {-1.0 / 512,  0.0,         18.0 / 512,  -16.0 / 
 // ghost phase write into a staging buffer (4 fields, [c][dz][dy][dx], at 4 *
 // base values), so that no item reads a ghost value another item rewrites;
 // items of a merge write the parent's interior directly (parent slots are
-// fresh).  Each output is a z-march over the 13 fine planes around it: for
-// every fine plane an x pass on the fine rows into LDS, a y pass per output
-// column into a register ring of the last 13 planes, and the z pass once the
-// ring holds an output's 13 planes.  A workgroup takes NF of the 4 fields of
-// an item at a time (one work unit).
+// fresh).
 //
 // mode 0: `items` holds 12 int32 per item (dst slot, i0, j0, k0, nx, ny, nz,
 //         src slot, fx0, fy0, fz0, base); outputs to `out` at 4 * base.
@@ -41,134 +38,217 @@ constexpr double LIFT_TAP[13] = {-1.0 / 512,  0.0,         18.0 / 512,  -16.0 / 
 //         child slots, unused); item w is octant w % 8 of parent w / 8, a box
 //         of (bs/2)^3 outputs at the octant's offset, centred on the child's
 //         even points from (0, 0, 0); outputs into U at the parent.
-template <typename T, int BS, int NF, bool INPLACE>
+struct LiftItem {
+  int dslot, i0, j0, k0, nx, ny, nz, sslot, fx0, fy0, fz0;
+  int64_t base;
+};
+
+template <int BS, int NF>
+struct LiftDims {
+  static constexpr int NM = BS / 2;           // largest box edge
+  static constexpr int NROW = 2 * NM + 11;    // fine points a box needs along an axis
+  static constexpr int NPT = NROW * NROW;     // fine points of a plane
+  static constexpr int PER = (NPT + NT_GEN - 1) / NT_GEN;
+  static constexpr int XC = 4;                // outputs of the x pass per task
+  static constexpr int XI = (NF * NROW * (NM / XC) + NT_GEN - 1) / NT_GEN;
+  static_assert(NM % XC == 0, "whole chunks");
+};
+
+// v += h[q] w[q] over the nonzero taps, in their order
+template <typename T>
+__device__ __forceinline__ T lift_taps(const T* w) {
+  T v = T(0);
+#pragma unroll
+  for (int q = 0; q < 13; ++q)
+    if (q != 1 && q != 11) v = fma(T(LIFT_TAP[q]), w[q], v);
+  return v;
+}
+
+// One item: a march over its fine z planes.  Per plane: the points, loaded
+// into registers one plane ahead, go to LDS; x pass in chunks of 4 outputs,
+// whose tap windows overlap; y pass in chunks of YC outputs, each thread
+// keeping its columns for the whole march; the z pass adds the plane to the
+// sums of the at most 7 outputs that it belongs to.  Two barriers per plane,
+// which wait for LDS only; where a thread's points, tasks and columns lie is
+// found once per item.
+template <typename T, int BS, int NF, bool INPLACE, int YC>
+__device__ __forceinline__ void lift_march(const LiftItem& m, int c0, const T* U, const Layout& L,
+                                           T* out, int mode, const Tab& ft, T* raw, T* xq) {
+  using D = LiftDims<BS, NF>;
+  constexpr int NM = D::NM, PER = D::PER, XC = D::XC, XI = D::XI;
+  const int tid = threadIdx.x;
+  const int nrow = 2 * m.ny + 11, ncol = 2 * m.nx + 11, nplane = 2 * m.nz + 11;
+  const int npt = nrow * ncol, nxc = (m.nx + XC - 1) / XC, nxt = NF * nrow * nxc;
+  // x tasks: where the window starts in raw and the outputs in xq; the latter
+  // negative past the last task, the outputs present in the low 3 bits
+  int xs[XI], xd[XI];
+#pragma unroll
+  for (int k = 0; k < XI; ++k) {
+    const int t = tid + k * NT_GEN, row = t / nxc, ch = t - row * nxc;  // row: of all fields
+    const int c = row / nrow;
+    xs[k] = row * ncol + 2 * XC * ch;
+    const int left = m.nx - XC * ch;
+    xd[k] = t < nxt ? ((c * D::NROW + row - c * nrow) * NM + XC * ch) * 8 + (left < XC ? left : XC)
+                    : -1;
+  }
+  // this thread's columns: YC outputs along y of one field and dx
+  const int nyc = (m.ny + YC - 1) / YC;
+  const int yt = tid / m.nx, dx = tid - yt * m.nx, yfld = yt / nyc, dy0 = (yt - yfld * nyc) * YC;
+  const bool own = yfld < NF;
+  const T* yq = xq + (own ? (yfld * D::NROW + 2 * dy0) * NM + dx : 0);
+  T acc[YC][7];
+#pragma unroll
+  for (int e = 0; e < YC; ++e)
+#pragma unroll
+    for (int j = 0; j < 7; ++j) acc[e][j] = T(0);
+  const T* src = U + c0 * L.fstride;
+  const int64_t zs = (int64_t)L.P * L.P;
+  const T* ptr[PER];
+  T v[PER][NF];
+  // Addresses of this thread's points in plane z.  INPLACE: values of the
+  // finer leaf's ghost regions whose level-J box is a leaf are read from that
+  // leaf's interior (the same values its ghost fill would copy there); the
+  // other ghost regions from its array.
+  auto locate = [&](int z) {
+    const int rz = z < 0 ? 0 : (z < BS ? 1 : 2);
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+      int p = tid + k * NT_GEN;
+      p = p < npt ? p : 0;
+      const int yf = p / ncol, x = m.fx0 - 6 + (p - yf * ncol), y = m.fy0 - 6 + yf;
+      int64_t slot = m.sslot;
+      int sx = 0, sy = 0, sz = 0;
+      if constexpr (INPLACE) {
+        const int rx = x < 0 ? 0 : (x < BS ? 1 : 2), ry = y < 0 ? 0 : (y < BS ? 1 : 2);
+        const int r = rx + 3 * ry + 9 * rz;
+        if (r != 13 && ft.kind[r] == 0) {
+          slot = ft.slot[r][0];
+          sx = (1 - rx) * BS, sy = (1 - ry) * BS, sz = (1 - rz) * BS;
+        }
+      }
+      ptr[k] = src + slot * L.bstride +
+               ((int64_t)(z + sz + L.ng) * L.P + (y + sy + L.ng)) * L.P + (x + sx + L.ng);
+    }
+  };
+  auto load = [&]() {
+#pragma unroll
+    for (int k = 0; k < PER; ++k)
+#pragma unroll
+      for (int c = 0; c < NF; ++c) v[k][c] = ptr[k][c * L.fstride];
+  };
+  locate(m.fz0 - 6);
+  load();
+  for (int zf = 0; zf < nplane; ++zf) {
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+      const int p = tid + k * NT_GEN;
+      if (p < npt)
+#pragma unroll
+        for (int c = 0; c < NF; ++c) raw[c * npt + p] = v[k][c];
+    }
+    lds_barrier();
+    if (zf + 1 < nplane) {
+      const int z = m.fz0 - 5 + zf;
+      if (INPLACE && (z == 0 || z == BS)) {
+        locate(z);
+      } else {
+#pragma unroll
+        for (int k = 0; k < PER; ++k) ptr[k] += zs;
+      }
+      load();
+    }
+#pragma unroll
+    for (int k = 0; k < XI; ++k)
+      if (xd[k] >= 0) {
+        T w[2 * (XC - 1) + 13];
+#pragma unroll
+        for (int q = 0; q < 2 * (XC - 1) + 13; ++q) w[q] = raw[xs[k] + q];
+        T* o = xq + (xd[k] >> 3);
+        const int no = xd[k] & 7;
+#pragma unroll
+        for (int e = 0; e < XC; ++e) {
+          const T s = lift_taps(w + 2 * e);
+          if (e < no) o[e] = s;
+        }
+      }
+    lds_barrier();
+    if (own) {
+      T w[2 * (YC - 1) + 13], s[YC];
+#pragma unroll
+      for (int q = 0; q < 2 * (YC - 1) + 13; ++q) w[q] = yq[q * NM];
+#pragma unroll
+      for (int e = 0; e < YC; ++e) s[e] = lift_taps(w + 2 * e);
+      if ((zf & 1) == 0) {
+        // the outputs zf/2 - 6 .. zf/2, of which the first is complete
+        const int k = zf / 2 - 6;
+#pragma unroll
+        for (int e = 0; e < YC; ++e) {
+#pragma unroll
+          for (int j = 0; j < 7; ++j) acc[e][j] = fma(T(LIFT_TAP[12 - 2 * j]), s[e], acc[e][j]);
+          if (k >= 0 && dy0 + e < m.ny) {
+            const int cf = c0 + yfld, dy = dy0 + e;
+            if (mode == 0)
+              out[m.base + ((int64_t)(cf * m.nz + k) * m.ny + dy) * m.nx + dx] = acc[e][0];
+            else
+              out[(int64_t)m.dslot * L.bstride + cf * L.fstride +
+                  ((int64_t)(m.k0 + k + L.ng) * L.P + (m.j0 + dy + L.ng)) * L.P +
+                  (m.i0 + dx + L.ng)] = acc[e][0];
+          }
+#pragma unroll
+          for (int j = 0; j < 6; ++j) acc[e][j] = acc[e][j + 1];
+          acc[e][6] = T(0);
+        }
+      } else {
+#pragma unroll
+        for (int e = 0; e < YC; ++e)
+#pragma unroll
+          for (int j = 1; j < 5; ++j) acc[e][j] = fma(T(LIFT_TAP[11 - 2 * j]), s[e], acc[e][j]);
+      }
+    }
+  }
+}
+
+// A work unit is a pair of fields of an item: all 4 at once make the units too
+// few and too unequal for the chip (587 us against 448, the bound being the
+// memory latency of each plane), one alone halves the loads in flight (497).
+// Before, the x pass loaded its 11 taps per output from memory: 668 us; all on
+// 2000 blocks of 24^3, FP64, where it fetches 1.1 GB.  Boxes thin along x or y
+// give every output column a thread of its own.
+template <typename T, int BS, bool INPLACE>
 __global__ __launch_bounds__(NT_GEN) void lift_box_kernel(const int32_t* __restrict__ items,
                                                           int64_t n, const T* U, Layout L,
                                                           T* out, int mode,
                                                           const Tab* __restrict__ tab,
                                                           const int32_t* __restrict__ stab) {
-  constexpr int NM = BS / 2;           // largest box edge
-  constexpr int NROW = 2 * NM + 11;    // fine rows a box needs
-  constexpr int NU = 4 / NF;           // work units per item
-  __shared__ T xq[NF][NROW * NM];      // x pass of the current fine plane
+  constexpr int NF = 2, NM = BS / 2, YC = 2;
+  using D = LiftDims<BS, NF>;
+  static_assert(NF * NM * (NM / YC) <= NT_GEN && NM % YC == 0, "one thread per chunk of columns");
+  // a fine plane (a chunk's unused outputs read up to 6 values past it)
+  __shared__ T raw[NF * D::NPT + 8];
+  __shared__ T xq[NF * D::NROW * NM];  // its x pass
   __shared__ Tab ft;                   // the finer leaf's table (in-place reads)
-  __shared__ int64_t rowo[3][NROW];    // per fine row of the plane: offsets of x = 0
-  const int tid = threadIdx.x;
-  // INPLACE (mode 0): values of the finer leaf's ghost regions whose level-J
-  // box is a leaf are read from that leaf's interior (the same values its
-  // ghost fill would copy there); the other ghost regions from its array
-  constexpr bool inplace = INPLACE;
-  T h[13];
-#pragma unroll
-  for (int q = 0; q < 13; ++q) h[q] = T(LIFT_TAP[q]);
-  for (int64_t u = blockIdx.x; u < n * NU; u += gridDim.x) {
-    const int64_t w = u / NU;
-    const int c0 = (int)(u - w * NU) * NF;  // first field of this unit
-    int dslot, i0, j0, k0, nx, ny, nz, sslot, fx0, fy0, fz0;
-    int64_t base = 0;
+  for (int64_t u = blockIdx.x; u < 2 * n; u += gridDim.x) {
+    const int64_t w = u >> 1;
+    LiftItem m;
     if (mode == 0) {
       const int32_t* e = items + 12 * w;
-      dslot = e[0], i0 = e[1], j0 = e[2], k0 = e[3], nx = e[4], ny = e[5], nz = e[6];
-      sslot = e[7], fx0 = e[8], fy0 = e[9], fz0 = e[10];
-      base = (int64_t)e[11] * 4;
+      m = {e[0], e[1], e[2], e[3], e[4], e[5], e[6], e[7], e[8], e[9], e[10], (int64_t)e[11] * 4};
     } else {
       const int32_t* e = items + 10 * (w >> 3);
       const int oc = (int)(w & 7);
-      dslot = e[0];
-      sslot = e[1 + oc];
-      i0 = (oc & 1) * NM, j0 = ((oc >> 1) & 1) * NM, k0 = (oc >> 2) * NM;
-      nx = ny = nz = NM;
-      fx0 = fy0 = fz0 = 0;
+      m = {e[0], (oc & 1) * NM, ((oc >> 1) & 1) * NM, (oc >> 2) * NM, NM, NM, NM,
+           e[1 + oc], 0, 0, 0, 0};
     }
-    const T* src = U + c0 * L.fstride;
-    if (inplace) {
-      __syncthreads();  // ft is free again
-      const int32_t* ts = reinterpret_cast<const int32_t*>(tab + stab[sslot]);
-      int32_t* td = reinterpret_cast<int32_t*>(&ft);
-      for (int q = tid; q < (int)(sizeof(Tab) / 4); q += NT_GEN) td[q] = ts[q];
+    __syncthreads();  // the last unit's tables and planes are free again
+    if constexpr (INPLACE) {
+      load_tab(tab + stab[m.sslot], ft);
       __syncthreads();
     }
-    const int nrow = 2 * ny + 11, nplane = 2 * nz + 11, nxp = nrow * nx;
-    const bool own = tid < nx * ny;
-    const int dx = own ? tid % nx : 0, dy = own ? tid / nx : 0;
-    T ring[NF][13];
-#pragma unroll
-    for (int c = 0; c < NF; ++c)
-#pragma unroll
-      for (int q = 0; q < 13; ++q) ring[c][q] = T(0);
-    for (int zf = 0; zf < nplane; ++zf) {
-      const int z = fz0 - 6 + zf;
-      // element offsets of each fine row's point x = 0 for x < 0, 0 <= x < bs
-      // and x >= bs (the three regions along x); the last plane's x pass,
-      // which read them, ended before its second barrier
-      if (inplace && tid < 3 * nrow) {
-        const int rx = tid / nrow, yf = tid - rx * nrow;
-        const int y = fy0 - 6 + yf;
-        int64_t o = (int64_t)sslot * L.bstride + ((int64_t)(z + L.ng) * L.P + (y + L.ng)) * L.P + L.ng;
-        const int ry = y < 0 ? 0 : (y < BS ? 1 : 2), rz = z < 0 ? 0 : (z < BS ? 1 : 2);
-        const int r = rx + 3 * ry + 9 * rz;
-        if (r != 13 && ft.kind[r] == 0) {
-          const int sy = ry == 0 ? BS : (ry == 2 ? -BS : 0);
-          const int sz = rz == 0 ? BS : (rz == 2 ? -BS : 0);
-          o = (int64_t)ft.slot[r][0] * L.bstride +
-              ((int64_t)(z + sz + L.ng) * L.P + (y + sy + L.ng)) * L.P + L.ng +
-              (rx == 0 ? BS : (rx == 2 ? -BS : 0));
-        }
-        rowo[rx][yf] = o;
-      }
-      __syncthreads();  // xq is free again, rowo is written
-      for (int it = tid; it < NF * nxp; it += NT_GEN) {
-        const int c = it / nxp, rem = it - c * nxp;
-        const int yf = rem / nx, ox = rem - yf * nx;
-        const T* sc = src + c * L.fstride;
-        const int x0 = fx0 + 2 * ox - 6;  // the taps' window is x0..x0+12
-        T v = T(0);
-        if constexpr (inplace) {
-          const int64_t r0 = rowo[0][yf], r1 = rowo[1][yf], r2 = rowo[2][yf];
-#pragma unroll
-          for (int q = 0; q < 13; ++q)
-            if (q != 1 && q != 11) {
-              const int x = x0 + q;
-              v += h[q] * sc[(x < 0 ? r0 : (x < BS ? r1 : r2)) + x];
-            }
-        } else {
-          const int y = fy0 - 6 + yf;
-          const T* row = sc + (int64_t)sslot * L.bstride +
-                         ((int64_t)(z + L.ng) * L.P + (y + L.ng)) * L.P + L.ng + x0;
-#pragma unroll
-          for (int q = 0; q < 13; ++q)
-            if (q != 1 && q != 11) v += h[q] * row[q];
-        }
-        xq[c][yf * NM + ox] = v;
-      }
-      __syncthreads();
-      if (own) {
-        const bool emit = zf >= 12 && ((zf - 12) & 1) == 0;
-        const int k = (zf - 12) >> 1;
-#pragma unroll
-        for (int c = 0; c < NF; ++c) {
-          T v = T(0);
-#pragma unroll
-          for (int q = 0; q < 13; ++q)
-            if (q != 1 && q != 11) v += h[q] * xq[c][(2 * dy + q) * NM + dx];
-#pragma unroll
-          for (int q = 0; q < 12; ++q) ring[c][q] = ring[c][q + 1];
-          ring[c][12] = v;
-          if (emit) {
-            T o = T(0);
-#pragma unroll
-            for (int q = 0; q < 13; ++q)
-              if (q != 1 && q != 11) o += h[q] * ring[c][q];
-            const int cf = c0 + c;
-            if (mode == 0)
-              out[base + ((int64_t)(cf * nz + k) * ny + dy) * nx + dx] = o;
-            else
-              out[(int64_t)dslot * L.bstride + cf * L.fstride +
-                  ((int64_t)(k0 + k + L.ng) * L.P + (j0 + dy + L.ng)) * L.P + (i0 + dx + L.ng)] = o;
-          }
-        }
-      }
-    }
+    const int c0 = NF * (int)(u & 1);
+    if (NF * m.nx * m.ny <= NT_GEN)
+      lift_march<T, BS, NF, INPLACE, 1>(m, c0, U, L, out, mode, ft, raw, xq);
+    else
+      lift_march<T, BS, NF, INPLACE, YC>(m, c0, U, L, out, mode, ft, raw, xq);
   }
 }
 
@@ -202,21 +282,18 @@ static Layout lift_layout(const wacm_grid* g) {
 }
 
 static unsigned lift_grid(int64_t n) {
-  const int64_t cap = 2048;
+  const int64_t cap = 16384;
   return (unsigned)(n < cap ? (n > 0 ? n : 1) : cap);
 }
 
-// two fields per work unit: measured a little faster than one or four (the
-// kernel is bound by its gathers, not by its occupancy)
 template <typename T, int BS>
 static hipError_t lift_box_t(const wacm_grid* g, const int32_t* items, int64_t n, T* U, T* out,
                              int mode, bool inplace, hipStream_t st) {
-  constexpr int NF = 2;
   if (inplace)
-    lift_box_kernel<T, BS, NF, true><<<lift_grid(n * (4 / NF)), NT_GEN, 0, st>>>(
+    lift_box_kernel<T, BS, true><<<lift_grid(2 * n), NT_GEN, 0, st>>>(
         items, n, U, lift_layout(g), out, mode, g->d_tab, lift_slot_tab(g));
   else
-    lift_box_kernel<T, BS, NF, false><<<lift_grid(n * (4 / NF)), NT_GEN, 0, st>>>(
+    lift_box_kernel<T, BS, false><<<lift_grid(2 * n), NT_GEN, 0, st>>>(
         items, n, U, lift_layout(g), out, mode, nullptr, nullptr);
   return hipGetLastError();
 }
