@@ -250,35 +250,44 @@ __global__ __launch_bounds__(NT_GEN) void sync_coarser_kernel(const Tab* __restr
 // Faces next to a coarser or finer leaf: the depth-3 face halo of the stage
 // input into the halo buffer the stage kernel reads.  A finer neighbour gives
 // its coincident point (decimation, Sec. 3.1).  A coarser neighbour gives the
-// tensor-product DD4 prediction (Sec. 3.1), computed separably: the coarse
-// lattice box around the face (even local indices, read from whichever leaves
-// hold them) is gathered once, then predicted along the normal and the two
-// tangential axes in turn, one field at a time through LDS.  The loads of all
-// 4 fields are issued together into registers before the first field's
-// passes, so one memory latency per face is exposed instead of four.  With
-// `queue` (schedule xcd_map 2) the faces, listed in the blocks' Morton order,
-// are taken from per-XCD work counters like the stage kernel's items, so the
-// faces of sister blocks, which read the same coarse data, meet in one L2.
-// FP32: held to 4 waves per SIMD (a few spilled registers; 0.64 -> 0.60 ms
-// per launch on the 20k-block octree); FP64 keeps its registers (2 waves:
-// held to 4 it spills ~70 and slows down).
+// tensor-product DD4 prediction (Sec. 3.1), computed separably: each thread
+// gathers the 4 or 5 coarse values along the normal at its tangential lattice
+// position (even local indices, read from whichever leaves hold them) for all
+// 4 fields at once, so that one memory latency per face is exposed, and
+// predicts along the normal in registers; then t0 through LDS in pairs of an
+// even and an odd point, and t1 by one thread per column with the last 4
+// lattice values in registers.  Two barriers for NF fields, which wait for LDS
+// only.  With `queue` (schedule xcd_map 2) the faces, listed in the blocks'
+// Morton order, are taken from per-XCD work counters like the stage kernel's
+// items, so the faces of sister blocks, which read the same coarse data, meet
+// in one L2.
+// Bound: the gather's latency and scattered lines.  On 20000 blocks of 24^3,
+// FP64, 0.73 ms per launch (0.97 with a pass per axis, field and barrier pair
+// through LDS); 5000 such blocks, FP32, 140 us (178 before).  FP32 takes all
+// fields at a time and is held to 4 waves per SIMD (3 at bs 32: two fields and
+// 4 waves spill, 131 against 94 us on 1500 blocks); FP64 keeps its registers
+// (2 waves: held to 4 it spills ~70 and slows down).
 template <typename T, int BS>
-__global__ __launch_bounds__(NT_GEN) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 1)))
+__global__ __launch_bounds__(NT_GEN) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? (BS == 32 ? 3 : 4) : 1)))
 void nlface_kernel(const Tab* __restrict__ tab,
                                                         const int32_t* __restrict__ cf, int64_t n,
                                                         const T* __restrict__ in, Layout Lin,
                                                         T* __restrict__ hb, int* queue) {
   constexpr int S = BS / 2 + 3;   // tangential coarse positions -2, 0, ..., bs+2
-  constexpr int NSRC = 5 * S * S;  // at most 5 coarse points along the normal
-  constexpr int PER = (NSRC + NT_GEN - 1) / NT_GEN;
+  constexpr int PER = (S * S + NT_GEN - 1) / NT_GEN;
   constexpr int B2 = BS * BS;
   constexpr int NFINE = (3 * B2 + NT_GEN - 1) / NT_GEN;
+  constexpr int NF = sizeof(T) == 4 ? 4 : 2;  // fields at a time
+  // columns of the last pass are halved where that fills the threads better
+  constexpr int RUNS = NF * 3 * BS > NT_GEN || 2 * NF * 3 * BS <= NT_GEN ? 2 : 1;
   __shared__ Tab st;
-  __shared__ T src[NSRC];
-  __shared__ T pa[3 * S * S];
-  __shared__ T pb[3 * S * BS];
+  __shared__ T pa[NF * 3 * S * S];
+  __shared__ T pb[NF * 3 * S * BS];
   __shared__ int qitem;
   const T w0 = T(DDW0), w1 = T(DDW1);
+  auto odd = [&](T a0, T a1, T a2, T a3) {
+    return fma(w0, a3, fma(w1, a2, fma(w1, a1, w0 * a0)));
+  };
   const int64_t fs = Lin.fstride;
   const int tid = threadIdx.x;
   const bool dyn = queue != nullptr;
@@ -334,76 +343,68 @@ void nlface_kernel(const Tab* __restrict__ tab,
     // -1 - d (side 0); the even positions their stencils use run from n0 in
     // steps of 2: side 1 [bs-2, bs+4] (4 points), side 0 [-6, 2] (5 points)
     const int n0 = side ? BS - 2 : -6;
-    const int NN = side ? 4 : 5;
-    const int nsrc = NN * S * S;
-    T v[PER][4];
+    T v[PER][4][5];
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
-      const int p = tid + k * NT_GEN;
-      if (p < nsrc) {
-        const int m = p / (S * S), qq = p - m * S * S;
+      const int qq = tid + k * NT_GEN;
+      if (qq < S * S) {
         int li[3];
-        li[axis] = n0 + 2 * m;
         li[ua] = 2 * (qq % S) - 2;
         li[ub] = 2 * (qq / S) - 2;
-        const int64_t o = point_offset(st, BS, Lin, li[0], li[1], li[2]);
 #pragma unroll
-        for (int c = 0; c < 4; ++c) v[k][c] = in[o + c * fs];
+        for (int m = 0; m < 5; ++m) {
+          if (m == 4 && side) break;
+          li[axis] = n0 + 2 * m;
+          const int64_t o = point_offset(st, BS, Lin, li[0], li[1], li[2]);
+#pragma unroll
+          for (int c = 0; c < 4; ++c) v[k][c][m] = in[o + c * fs];
+        }
       }
     }
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
+    for (int c0 = 0; c0 < 4; c0 += NF) {
+      // along the normal: pa[c][d][t1'][t0']
 #pragma unroll
       for (int k = 0; k < PER; ++k) {
-        const int p = tid + k * NT_GEN;
-        if (p < nsrc) src[p] = v[k][c];
-      }
-      __syncthreads();
-      // along the normal: pa[d][t1'][t0']
-      for (int p = tid; p < 3 * S * S; p += NT_GEN) {
-        const int d = p / (S * S), qq = p - d * S * S;
-        const int g = side ? BS + d : -1 - d;
-        T val;
-        if ((g & 1) == 0) {
-          val = src[((g - n0) / 2) * S * S + qq];
-        } else {
-          const int m = (g - 3 - n0) / 2;  // taps g-3, g-1, g+1, g+3
-          val = w0 * src[m * S * S + qq] + w1 * src[(m + 1) * S * S + qq] +
-                w1 * src[(m + 2) * S * S + qq] + w0 * src[(m + 3) * S * S + qq];
+        const int qq = tid + k * NT_GEN;
+        if (qq < S * S) {
+#pragma unroll
+          for (int c = 0; c < NF; ++c) {
+            const T* s = v[k][c0 + c];
+            T* o = pa + c * 3 * S * S + qq;
+            const T low = odd(s[0], s[1], s[2], s[3]);
+            o[0] = side ? s[1] : odd(s[1], s[2], s[3], s[4]);
+            o[S * S] = side ? low : s[2];
+            o[2 * S * S] = side ? s[2] : low;
+          }
         }
-        pa[p] = val;
       }
-      __syncthreads();
-      // along t0: pb[d][t1'][t0], t0 in [0, bs)
-      for (int p = tid; p < 3 * S * BS; p += NT_GEN) {
-        const int t0 = p % BS, rest = p / BS;  // rest = d * S + t1'
-        const T* row = pa + rest * S;
-        T val;
-        if ((t0 & 1) == 0) {
-          val = row[t0 / 2 + 1];
-        } else {
-          const int m = (t0 - 3) / 2 + 1;  // coarse index of t0-3
-          val = w0 * row[m] + w1 * row[m + 1] + w1 * row[m + 2] + w0 * row[m + 3];
+      lds_barrier();
+      // along t0 in pairs (even, odd): pb[c][d][t1'][t0], t0 in [0, bs)
+      for (int p = tid; p < NF * 3 * S * (BS / 2); p += NT_GEN) {
+        const int t = p % (BS / 2), row = p / (BS / 2);
+        const T* s = pa + row * S + t;
+        pb[row * BS + 2 * t] = s[1];
+        pb[row * BS + 2 * t + 1] = odd(s[0], s[1], s[2], s[3]);
+      }
+      lds_barrier();
+      // along t1, one thread per column or half a column: out[c][d][t1][t0]
+      for (int p = tid; p < RUNS * NF * 3 * BS; p += NT_GEN) {
+        const int t0 = p % BS, rest = p / BS, run = rest / (NF * 3), cd = rest - run * (NF * 3);
+        const int u0 = run * (BS / 2 / RUNS);
+        const T* s = pb + (cd * S + u0) * BS + t0;
+        T* o = hbf + (c0 * 3 + cd) * B2 + 2 * u0 * BS + t0;
+        T a0 = s[0], a1 = s[BS], a2 = s[2 * BS];
+#pragma unroll
+        for (int u = 0; u < BS / 2 / RUNS; ++u) {
+          const T a3 = s[(u + 3) * BS];
+          o[2 * u * BS] = a1;
+          o[(2 * u + 1) * BS] = odd(a0, a1, a2, a3);
+          a0 = a1;
+          a1 = a2;
+          a2 = a3;
         }
-        pb[p] = val;
       }
-      __syncthreads();
-      // along t1: out[d][t1][t0]
-      for (int p = tid; p < 3 * B2; p += NT_GEN) {
-        const int d = p / B2, qq = p - d * B2;
-        const int t0 = qq % BS, t1 = qq / BS;
-        const T* colp = pb + d * S * BS + t0;
-        T val;
-        if ((t1 & 1) == 0) {
-          val = colp[(t1 / 2 + 1) * BS];
-        } else {
-          const int m = (t1 - 3) / 2 + 1;
-          val = w0 * colp[m * BS] + w1 * colp[(m + 1) * BS] + w1 * colp[(m + 2) * BS] +
-                w0 * colp[(m + 3) * BS];
-        }
-        hbf[(int64_t)(c * 3) * B2 + p] = val;
-      }
-      __syncthreads();
     }
     if (dyn && tid == 0) qitem = queue_take(queue, qh, qchunk, (int)n, qpend);
   }
