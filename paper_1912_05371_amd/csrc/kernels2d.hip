@@ -21,7 +21,7 @@
 namespace wacm {
 
 hipError_t finalize_dt(const double* part, int64_t n, const wacm_params& p, double hmin,
-                       double* dt_dev, hipStream_t st);
+                       double* dt_dev, double* t_dev, hipStream_t st);
 hipError_t finalize_diag(const double* part, int64_t n, double* out, hipStream_t st);
 hipError_t finalize_norm(const double* part, int64_t n, double* norm, hipStream_t st);
 hipError_t add_dt_to_time(double* t_dev, const double* dt_dev, hipStream_t st);
@@ -451,7 +451,7 @@ hipError_t dt_t(const wacm_grid* g, const wacm_params* p, const T* U, double* dt
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const double hmin = g->d.L / (double(int64_t(1) << g->jfine) * g->d.bs);
-  return finalize_dt(g->d_part, g->nb, *p, hmin, dt_dev, st);
+  return finalize_dt(g->d_part, g->nb, *p, hmin, dt_dev, nullptr, st);
 }
 
 size_t work_bytes(const wacm_grid* g) {
@@ -474,16 +474,17 @@ hipError_t rk4_t(const wacm_grid* g, const wacm_params* p, double* t_dev, double
     // from the second step on, the CFL maximum comes from the last stage
     if (dt_mode == WACM_DT_CFL) {
       e = k == 0 ? dt_t<T>(g, p, U, dt_dev, st)
-                 : finalize_dt(g->d_part, g->nb, *p, hmin, dt_dev, st);
+                 : finalize_dt(g->d_part, g->nb, *p, hmin, dt_dev, t_dev, st);
       if (e != hipSuccess) return e;
     }
     double* part = dt_mode == WACM_DT_CFL && k + 1 < nsteps ? g->d_part : nullptr;
     if ((e = stage_t<T, 1>(g, p, U, U, acc, Ya, dt_dev, nullptr, st)) != hipSuccess ||
         (e = stage_t<T, 2>(g, p, Ya, U, acc, Yb, dt_dev, nullptr, st)) != hipSuccess ||
         (e = stage_t<T, 3>(g, p, Yb, U, acc, Ya, dt_dev, nullptr, st)) != hipSuccess ||
-        (e = stage_t<T, 4>(g, p, Ya, U, acc, U, dt_dev, part, st)) != hipSuccess ||
-        (e = add_dt_to_time(t_dev, dt_dev, st)) != hipSuccess)
+        (e = stage_t<T, 4>(g, p, Ya, U, acc, U, dt_dev, part, st)) != hipSuccess)
       return e;
+    if (part) continue;  // the next step's finalize_dt advances the time
+    if ((e = add_dt_to_time(t_dev, dt_dev, st)) != hipSuccess) return e;
   }
   return hipSuccess;
 }
