@@ -102,3 +102,27 @@ def test_schedule_of_a_large_grid_without_one_set(prec):
         got.append((U[:len(lev), :, 4:28, 4:28, 4:28].clone(), t.item(), dt.item()))
         del U, g
     assert torch.equal(got[0][0], got[1][0]) and got[0][1:] == got[1][1:]
+
+
+@pytest.mark.parametrize("bs,ng,prec", [(16, 3, "f64"), (24, 4, "f32"), (32, 5, "f64")])
+def test_filtered_steps_need_the_lattice_ghosts_alone(bs, ng, prec):
+    from paper_1912_05371_amd import adaptive
+    c = cases.random_octree(bs=bs, ng=ng, target=40, j0=1, jmax=3, seed=bs)
+    g = wacm.Grid.from_case(c, dtype=DT[prec])
+    U = np.random.default_rng(ng).standard_normal((c.nb, 4, c.P, c.P, c.P))
+    prm = cases.params(nu=1e-3, c0=5.0, c_gamma=1.0)
+    i = slice(ng, ng + bs)
+    got = []
+    for whole in (False, True):
+        A = to_pool(g, U, fill=float("nan"))
+        A[:, :, :ng] = A[:, :, ng + bs:] = float("nan")
+        t, dt = (torch.full((1,), v, dtype=torch.float64, device="cuda") for v in (0.0, 1e-5))
+        if whole:
+            for _ in range(2):
+                g.rk4_step(prm, t, dt, A, g.work(), dt_mode=wacm.DT_FIXED)
+                g.sync_ghosts(A)
+                g.filter_blocks(A, -1)
+        else:
+            adaptive.filtered_steps(g, prm, A, g.work(), t, dt, 2, -1, dt_mode=wacm.DT_FIXED)
+        got.append(A[:c.nb, :, i, i, i].clone())
+    assert torch.isfinite(got[0]).all() and torch.equal(got[0], got[1])
