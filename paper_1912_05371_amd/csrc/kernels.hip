@@ -444,8 +444,8 @@ __global__ __launch_bounds__(NT_GEN) void maxu_kernel(const Tab* __restrict__ ta
 }
 
 // CFL step from the maxima.  With t, the time first advances by the step that
-// *dt_out still holds: between two steps of one call this is one launch for
-// two (4.6 us each, a tenth of a step on small grids).
+// *dt_out still holds: between two steps of one call one launch instead of two
+// (349 blocks of 16^2, five steps: 219.5 -> 214.0 us).
 __global__ __launch_bounds__(NT_GEN) void dt_finalize(const double* __restrict__ part, int64_t nb,
                                                       wacm_params p, double hmin,
                                                       double* dt_out, double* t) {
