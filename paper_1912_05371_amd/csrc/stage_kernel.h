@@ -149,7 +149,7 @@ void stage_kernel(StageArgs<T> a) {
     const int slot = __builtin_amdgcn_readfirstlane(meta[0]);
     const int J = __builtin_amdgcn_readfirstlane(meta[1]);
     const double hdd = a.L / (double(int64_t(1) << J) * BS);
-    const T ih = T(1.0 / hdd), ih2 = T(1.0 / (hdd * hdd)), nu2 = nu * ih2;
+    const T ih = T(1.0 / hdd), ih2 = T(1.0 / (hdd * hdd));
     const T* __restrict__ inb = a.in + (int64_t)slot * a.Lin.bstride + col;
     T* accb = a.acc + (int64_t)slot * a.Lacc.bstride + acol;
     T* unb = a.un + (int64_t)slot * a.Lun.bstride + ucol;
@@ -280,62 +280,38 @@ void stage_kernel(StageArgs<T> a) {
 
       // rhs, accumulated field by field, in explicit fused multiply-adds: the
       // compiler would contract the variants of this kernel differently, and
-      // every schedule has to give the same bits.  In FP64, where the vector
-      // units bound the kernel, the Laplacian adds the six equal distances
-      // first and 1/h and nu / h^2 are applied to sums: 20 operations fewer
-      // per point.  In FP32 memory bounds it; there the terms keep the plain
-      // order, one axis after the other.
+      // every schedule has to give the same bits.  The Laplacian is summed one
+      // axis after the other: with the six equal distances first (20 FP64
+      // operations fewer per point, 2% of a step of 20000 blocks of 24^3) its
+      // partial sums are three times as large, and the rhs of a flow that
+      // viscosity dominates is 1.7 times as far from its 64-bit value.
       const T u = q[0][3], v = q[1][3], w = q[2][3], pr = q[3][3];
       T r[4], div = T(0);
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
         const T* s = sb[c];
-        if constexpr (sizeof(T) == 8) {
-          const T dx = fma(a1, s[cidx + 1] - s[cidx - 1],
-                           fma(a2, s[cidx + 2] - s[cidx - 2], a3 * (s[cidx + 3] - s[cidx - 3])));
-          const T dy = fma(a1, s[cidx + W] - s[cidx - W],
-                           fma(a2, s[cidx + 2 * W] - s[cidx - 2 * W],
-                               a3 * (s[cidx + 3 * W] - s[cidx - 3 * W])));
-          const T dz =
-              fma(a1, q[c][4] - q[c][2], fma(a2, q[c][5] - q[c][1], a3 * (q[c][6] - q[c][0])));
-          if (c < 3) {
-            const T far2 = (s[cidx - 2] + s[cidx + 2]) + (s[cidx - 2 * W] + s[cidx + 2 * W]) +
-                           (q[c][1] + q[c][5]);
-            const T near2 = (s[cidx - 1] + s[cidx + 1]) + (s[cidx - W] + s[cidx + W]) +
-                            (q[c][2] + q[c][4]);
-            const T lap = fma(c2a, far2, fma(c2b, near2, T(3) * c2c * q[c][3]));
-            const T conv = fma(u, dx, fma(v, dy, w * dz));
-            r[c] = fma(nu2, lap, -ih * conv);
-            div += c == 0 ? dx : (c == 1 ? dy : dz);
-          } else {
-            r[0] = fma(-ih, dx, r[0]);
-            r[1] = fma(-ih, dy, r[1]);
-            r[2] = fma(-ih, dz, r[2]);
-          }
+        const T dx = fma(a3, s[cidx + 3] - s[cidx - 3],
+                         fma(a1, s[cidx + 1] - s[cidx - 1], a2 * (s[cidx + 2] - s[cidx - 2])));
+        const T dy = fma(a3, s[cidx + 3 * W] - s[cidx - 3 * W],
+                         fma(a1, s[cidx + W] - s[cidx - W],
+                             a2 * (s[cidx + 2 * W] - s[cidx - 2 * W])));
+        const T dz =
+            fma(a3, q[c][6] - q[c][0], fma(a1, q[c][4] - q[c][2], a2 * (q[c][5] - q[c][1])));
+        if (c < 3) {
+          const T lap = (lap1(s[cidx - 2], s[cidx - 1], s[cidx], s[cidx + 1], s[cidx + 2]) +
+                         lap1(s[cidx - 2 * W], s[cidx - W], s[cidx], s[cidx + W],
+                              s[cidx + 2 * W])) +
+                        lap1(q[c][1], q[c][2], q[c][3], q[c][4], q[c][5]);
+          const T conv = fma(w, dz * ih, fma(u, dx * ih, v * (dy * ih)));
+          r[c] = fma(lap * ih2, nu, -conv);
+          div = fma(c == 0 ? dx : (c == 1 ? dy : dz), ih, div);
         } else {
-          const T dx = fma(a3, s[cidx + 3] - s[cidx - 3],
-                           fma(a1, s[cidx + 1] - s[cidx - 1], a2 * (s[cidx + 2] - s[cidx - 2])));
-          const T dy = fma(a3, s[cidx + 3 * W] - s[cidx - 3 * W],
-                           fma(a1, s[cidx + W] - s[cidx - W],
-                               a2 * (s[cidx + 2 * W] - s[cidx - 2 * W])));
-          const T dz =
-              fma(a3, q[c][6] - q[c][0], fma(a1, q[c][4] - q[c][2], a2 * (q[c][5] - q[c][1])));
-          if (c < 3) {
-            const T lap = (lap1(s[cidx - 2], s[cidx - 1], s[cidx], s[cidx + 1], s[cidx + 2]) +
-                           lap1(s[cidx - 2 * W], s[cidx - W], s[cidx], s[cidx + W],
-                                s[cidx + 2 * W])) +
-                          lap1(q[c][1], q[c][2], q[c][3], q[c][4], q[c][5]);
-            const T conv = fma(w, dz * ih, fma(u, dx * ih, v * (dy * ih)));
-            r[c] = fma(lap * ih2, nu, -conv);
-            div = fma(c == 0 ? dx : (c == 1 ? dy : dz), ih, div);
-          } else {
-            r[0] = fma(-dx, ih, r[0]);
-            r[1] = fma(-dy, ih, r[1]);
-            r[2] = fma(-dz, ih, r[2]);
-          }
+          r[0] = fma(-dx, ih, r[0]);
+          r[1] = fma(-dy, ih, r[1]);
+          r[2] = fma(-dz, ih, r[2]);
         }
       }
-      r[3] = fma(sizeof(T) == 8 ? -c0sq * ih : -c0sq, div, -cg * pr);
+      r[3] = fma(-c0sq, div, -cg * pr);
       if (PEN) {
         const wacm_params& p = a.p;
         T chi = pchi, sp = psp, us[3] = {pus[0], pus[1], pus[2]};
@@ -390,9 +366,7 @@ void stage_kernel(StageArgs<T> a) {
           const T u0 = MODE == 1 ? val[c] : unv[c];
           // (U^n + Y2)/3 = 2/3 U^n + dt/6 k1, from the input Y2 = U^n + dt/2 k1
           if (MODE == 2)
-            ntstore(sizeof(T) == 8 ? fma(fA, r[c], (u0 + val[c]) * T(1.0 / 3.0))
-                                   : fma(u0 + val[c], T(1.0 / 3.0), fA * r[c]),
-                    accb + c * afs + z * azs, a.nt);
+            ntstore(fma(u0 + val[c], T(1.0 / 3.0), fA * r[c]), accb + c * afs + z * azs, a.nt);
           outb[c * ofs + z * ozs] = fma(fB, r[c], u0);
         }
         // a padded output's rows are written whole as in stage 4 (the next
