@@ -114,21 +114,23 @@ typedef struct {
  * L2), 2 does the same through per-XCD work counters from which each
  * workgroup takes its next item, moving on to the other XCDs' runs when its
  * own is empty (calls on one grid must then not overlap in time: they share
- * the counters), 0 deals the work items round-robin; prefetch: 1 loads U^n and the accumulator before a plane's barrier, 0
- * after the rhs, -1 default; nontemporal: 1 streams U^n and the accumulator
- * with non-temporal loads/stores; tile_rows: 0 gives each workgroup a whole
- * block (bs^2 threads), 8 a tile of 8 rows of the block's columns (8 bs
- * threads, smaller workgroups, more of them per CU); pen_split: 2 runs the
- * blocks where the penalization and sponge terms vanish at every point (far
- * from the mask by 20 smoothing widths, 12 with clipping, and outside the
- * sponge) through the unpenalized variant and the others through the
- * penalized one, 1 does so when it pays (at least 2048 active blocks and,
- * for a static mask or sponge, at least 512 without penalization), 0 runs
- * every block through the penalized one when a mask, sponge or dus is
- * present.  Results are the same bit for bit.  Default {0, 1, -1, 1, 0, 1};
- * as long as no schedule is set on a grid the library departs from it by size
- * and type (tiles of 8 rows and early loads for FP64 blocks of 24^3 and more;
- * work counters, in the call's own work buffer, for large grids). */
+ * the counters), 0 deals the work items round-robin; prefetch: 1 loads U^n and
+ * the accumulator before a plane's barrier, 0 after the rhs; nontemporal: 1
+ * streams U^n and the accumulator with non-temporal loads/stores; tile_rows: 0
+ * gives each workgroup a whole block (bs^2 threads), 8 a tile of 8 rows of the
+ * block's columns (8 bs threads, smaller workgroups, more of them per CU);
+ * pen_split: 2 runs the blocks where the penalization and sponge terms vanish
+ * at every point (far from the mask by 20 smoothing widths, 12 with clipping,
+ * and outside the sponge) through the unpenalized variant and the others
+ * through the penalized one, 1 does so when it pays (at least 2048 active
+ * blocks and, for a static mask or sponge, at least 512 without penalization),
+ * 0 runs every block through the penalized one when a mask, sponge or dus is
+ * present.  Results are the same bit for bit.  xcd_map, prefetch or tile_rows
+ * -1 leaves that knob to the library, whatever the others are set to: tiles of
+ * 8 rows for FP64 blocks of 24^3 and more; on large grids tiles from work
+ * counters in the call's own work buffer (nothing shared: as xcd_map 1); else
+ * whole blocks and xcd_map 1; early loads for FP32 and, with tile_rows -1 too,
+ * for those FP64 blocks.  Default {0, -1, -1, 1, -1, 1}. */
 typedef struct {
   int32_t wg_per_cu;
   int32_t xcd_map;
@@ -233,8 +235,9 @@ int wacm_set_wavelet(wacm_grid* grid, int32_t wavelet, void* ws, size_t ws_bytes
 int wacm_get_wavelet(const wacm_grid* grid);
 
 /* Set / read the stage-kernel schedule (values checked: wg_per_cu in [0, 16],
- * xcd_map in {0, 1, 2}, nontemporal in {0, 1}, prefetch in {-1, 0, 1}, tile_rows in
- * {0, 8}, pen_split in {0, 1, 2}). */
+ * xcd_map in {-1, 0, 1, 2}, nontemporal in {0, 1}, prefetch in {-1, 0, 1}, tile_rows
+ * in {-1, 0, 8}, pen_split in {0, 1, 2}).  What is read is what was set, so that a
+ * program may change one knob and write the others back as it read them. */
 int wacm_set_schedule(wacm_grid* grid, const wacm_schedule* s);
 int wacm_get_schedule(const wacm_grid* grid, wacm_schedule* s);
 

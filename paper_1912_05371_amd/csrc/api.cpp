@@ -275,12 +275,11 @@ size_t wacm_work_bytes(const wacm_grid* g) {
 int wacm_set_schedule(wacm_grid* g, const wacm_schedule* s) {
   GridScope gs(g);
   if (!g || !s) return fail(WACM_E_INVAL, "NULL argument");
-  if (s->wg_per_cu < 0 || s->wg_per_cu > 16 || s->xcd_map < 0 || s->xcd_map > 2 ||
+  if (s->wg_per_cu < 0 || s->wg_per_cu > 16 || s->xcd_map < -1 || s->xcd_map > 2 ||
       s->prefetch < -1 || s->prefetch > 1 || (s->nontemporal != 0 && s->nontemporal != 1) ||
-      (s->tile_rows != 0 && s->tile_rows != 8) || (s->pen_split < 0 || s->pen_split > 2))
+      (s->tile_rows != -1 && s->tile_rows != 0 && s->tile_rows != 8) || (s->pen_split < 0 || s->pen_split > 2))
     return fail(WACM_E_INVAL, "schedule value out of range");
   g->sched = *s;
-  g->sched_set = true;
   return WACM_OK;
 }
 

@@ -9,6 +9,7 @@
 #include <mutex>
 
 #include "resolve.h"
+#include "schedule.h"
 #include "stage.h"
 #include "wacm_internal.h"
 
@@ -1359,31 +1360,6 @@ static int* face_queue(const StageArgs<T>& a) {
   return a.queue ? a.queue + 8 * QSTRIDE : nullptr;
 }
 
-// The RK stages' schedule: the caller's, or if none was set on the grid the
-// default one with, for FP64 blocks of 24^3 and more, tiles of 8 rows and early
-// epilogue loads (ms per step, whole blocks -> tiles: 24^3 1.10 -> 1.07 at 603
-// blocks, 10.30 -> 9.40 at 6000; 32^3 8.91 -> 5.17 at 1520, where a whole
-// block's 16 waves leave 128 registers and spill).  FP32 keeps whole blocks
-// below the size of large_grid (24^3, 2024 blocks: 1.90 against 1.95).
-static wacm_schedule stage_schedule(const wacm_grid* g) {
-  wacm_schedule s = g->sched;
-  if (!g->sched_set && g->d.dtype == WACM_F64 && g->d.bs >= 24) {
-    s.tile_rows = 8;
-    s.prefetch = 1;
-  }
-  return s;
-}
-
-// Whether a grid without a schedule of its own takes tiles from work counters:
-// from 4096 blocks of 24^3 on (ms per step at 6000 blocks, static -> counters:
-// FP64 9.40 -> 9.20, FP32 whole blocks 5.48 -> 5.30; at 20028 blocks FP64 31.4 ->
-// 30.0; no gain at 2024 blocks, for 16^3, or for FP32 32^3).
-static bool large_grid(const wacm_grid* g) {
-  const int bs = g->d.bs;
-  return !g->sched_set && (bs == 24 || (bs == 32 && g->d.dtype == WACM_F64)) &&
-         g->nb * (int64_t)(bs * bs * bs) >= (int64_t)4096 * 24 * 24 * 24;
-}
-
 // Room for a call's own work counters in its work buffer: the halo of a face
 // next to a leaf of the same level is read in place and never stored.  -1: none.
 static int64_t spare_face(const wacm_grid* g) {
@@ -1399,7 +1375,7 @@ static StageArgs<T> base_args(const wacm_grid* g, const wacm_params* p) {
   a.tab = g->d_tab;
   a.nb = g->nb;
   a.L = g->d.L;
-  a.xcd_map = g->sched.xcd_map;
+  a.xcd_map = g->sched.xcd_map < 0 ? 1 : g->sched.xcd_map;
   a.queue = g->sched.xcd_map == 2 ? g->d_queue : nullptr;
   a.nt = g->sched.nontemporal;
   a.kscale = 1.0;
@@ -1464,7 +1440,7 @@ static hipError_t rhs_t(const wacm_grid* g, const wacm_params* p, double t, cons
   a.Lacc = pool_layout(g);
   a.dus = dus;
   a.t_host = t;
-  return stage_run<T>(0, g->d.bs, a, g->sched, st);
+  return stage_run<T>(0, g->d.bs, a, rhs_schedule(g->sched), st);
 }
 
 hipError_t launch_rhs(const wacm_grid* g, const wacm_params* p, double t, const void* U,
@@ -1549,7 +1525,8 @@ static hipError_t stage_input_t(const wacm_grid* g, const wacm_params* p, int s,
   if (g->n_cface > 0)
     if (hipError_t e = nlface_launch<T>(g, in, a.Lin, hb, face_queue(a), st); e != hipSuccess)
       return e;
-  return stage_run<T>(s == 1 ? 1 : 3, g->d.bs, a, stage_schedule(g), st);
+  return stage_run<T>(s == 1 ? 1 : 3, g->d.bs, a,
+                      stage_schedule(g->sched, sizeof(T) == 8, g->d.bs, g->nb, false), st);
 }
 
 hipError_t launch_stage_input(const wacm_grid* g, const wacm_params* p, int s, double t,
@@ -1595,14 +1572,13 @@ static hipError_t rk4_t(const wacm_grid* g, const wacm_params* p, double* t_dev,
   T* ins[4] = {U, ping, pong, ping};
   T* outs[4] = {ping, pong, ping, U};
   Layout lins[4] = {Lp, Ls, Ls, Ls};
-  wacm_schedule sched = stage_schedule(g);
-  if (large_grid(g))
-    if (const int64_t f = spare_face(g); f >= 0) {
-      // counters of this call alone: calls on one grid may overlap in time
-      a.queue = reinterpret_cast<int*>(hb + f * 12 * g->d.bs * g->d.bs);
-      a.xcd_map = 2;
-      sched.tile_rows = 8;
-    }
+  const bool f64 = sizeof(T) == 8;
+  const int64_t face = large_grid(f64, g->d.bs, g->nb) ? spare_face(g) : -1;
+  const wacm_schedule sched = stage_schedule(g->sched, f64, g->d.bs, g->nb, face >= 0);
+  if (sched.xcd_map == XCD_OWN_COUNTERS) {
+    a.queue = reinterpret_cast<int*>(hb + face * 12 * g->d.bs * g->d.bs);
+    a.xcd_map = 2;
+  }
   const double hmin = g->d.L / (double(int64_t(1) << g->jfine) * g->d.bs);
   int64_t nmax = 0;  // velocity maxima the last stage of the previous step left
   // blocks without penalization first (the adaptation lists are free

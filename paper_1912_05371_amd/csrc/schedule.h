@@ -1,0 +1,52 @@
+// Which variant of the stage kernel a launch takes: what of the grid's
+// schedule is left to the library (-1) is chosen here by element type and
+// size.  Host code without HIP, so that the rules can be tested anywhere.
+#pragma once
+
+#include <cstdint>
+
+#include "wacm.h"
+
+namespace wacm {
+
+// Resolved xcd_map of a launch that takes its items from work counters of the
+// call's own (in its work buffer), not the grid's.
+constexpr int XCD_OWN_COUNTERS = 3;
+
+// Whether an RK step without an xcd_map of its own takes tiles from work
+// counters: from 4096 blocks of 24^3 on (ms per step at 6000 blocks, static ->
+// counters: FP64 9.40 -> 9.20, FP32 whole blocks 5.48 -> tiles 5.30; at 20028
+// blocks FP64 31.4 -> 30.0; no gain at 2024 blocks, for 16^3, or for FP32 32^3).
+inline bool large_grid(bool f64, int bs, int64_t nb) {
+  return (bs == 24 || (bs == 32 && f64)) &&
+         nb * (int64_t)(bs * bs * bs) >= (int64_t)4096 * 24 * 24 * 24;
+}
+
+// The RK stages' schedule.  Left to the library: tiles of 8 rows with early
+// epilogue loads for FP64 blocks of 24^3 and more (ms per step, whole blocks ->
+// tiles: 24^3 1.10 -> 1.07 at 603 blocks, 10.30 -> 9.40 at 6000; 32^3 8.91 ->
+// 5.17 at 1520, where a whole block's 16 waves leave 128 registers and spill).
+// FP32 keeps whole blocks below the size of large_grid (24^3, 2024 blocks: 1.90
+// against 1.95).  A knob that is set is taken as it is, and setting one leaves
+// the others' choice as it was; only the early loads go with tiles that are the
+// library's (with tile_rows 8 set, prefetch -1 has always meant late for FP64).
+// counters: the call has room for counters of its own.
+inline wacm_schedule stage_schedule(const wacm_schedule& set, bool f64, int bs, int64_t nb,
+                                    bool counters) {
+  wacm_schedule s = set;
+  const bool large = counters && large_grid(f64, bs, nb);
+  if (s.tile_rows < 0 && s.prefetch < 0 && f64 && bs >= 24) s.prefetch = 1;
+  if (s.tile_rows < 0) s.tile_rows = (f64 && bs >= 24) || large ? 8 : 0;
+  if (s.xcd_map < 0) s.xcd_map = large ? XCD_OWN_COUNTERS : 1;
+  return s;
+}
+
+// The schedule of the rhs alone: whole blocks, statically mapped.
+inline wacm_schedule rhs_schedule(const wacm_schedule& set) {
+  wacm_schedule s = set;
+  if (s.tile_rows < 0) s.tile_rows = 0;
+  if (s.xcd_map < 0) s.xcd_map = 1;
+  return s;
+}
+
+}  // namespace wacm

@@ -193,8 +193,8 @@ struct wacm_grid {
   std::vector<wacm::Tab> h_tab_next;  // the next tables' buffer (allocation reused)
   double adapt_ms[2] = {0, 0};   // last wacm_adapt: host work, device work (ms)
   hipEvent_t adapt_ev[2] = {nullptr, nullptr};  // around wacm_adapt's kernels
-  wacm_schedule sched{0, 1, -1, 1, 0, 1};  // launch schedule of the stage kernel
-  bool sched_set = false;  // by wacm_set_schedule: else tiles and counters by size
+  // launch schedule of the stage kernel; -1 is left to schedule.h
+  wacm_schedule sched{0, -1, -1, 1, -1, 1};
   wacm::AdjPlan plan[2];         // ghost-fill transposes: all layers / face star
   // restriction wavelet: 0 CDF 4/0 (decimation), 1 CDF 4/4 (lifted); with
   // CDF 4/4, the work items of the lifted ghost phase (12 int32 each) and
