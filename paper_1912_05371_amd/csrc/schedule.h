@@ -13,6 +13,9 @@ namespace wacm {
 // call's own (in its work buffer), not the grid's.
 constexpr int XCD_OWN_COUNTERS = 3;
 
+// Resolved prefetch of tiles that the library chose: see early_loads.
+constexpr int PREFETCH_TILES = 2;
+
 // Whether an RK step without an xcd_map of its own takes tiles from work
 // counters: from 4096 blocks of 24^3 on (ms per step at 6000 blocks, static ->
 // counters: FP64 9.40 -> 9.20, FP32 whole blocks 5.48 -> tiles 5.30; at 20028
@@ -35,10 +38,19 @@ inline wacm_schedule stage_schedule(const wacm_schedule& set, bool f64, int bs, 
                                     bool counters) {
   wacm_schedule s = set;
   const bool large = counters && large_grid(f64, bs, nb);
-  if (s.tile_rows < 0 && s.prefetch < 0 && f64 && bs >= 24) s.prefetch = 1;
+  if (s.tile_rows < 0 && s.prefetch < 0 && f64 && bs >= 24) s.prefetch = PREFETCH_TILES;
   if (s.tile_rows < 0) s.tile_rows = (f64 && bs >= 24) || large ? 8 : 0;
   if (s.xcd_map < 0) s.xcd_map = large ? XCD_OWN_COUNTERS : 1;
   return s;
+}
+
+// Whether a launch whose planes are cut into `runs` loads U^n and the
+// accumulator early: as set; left to the library, early for FP32 and, in whole
+// columns, for its FP64 tiles.  (Late against early with 2 runs, FP64 tiles: no
+// mask 1.02 to 1.05, sphere 0.89 to 0.91, plate 0.89 to 0.96.)
+inline bool early_loads(const wacm_schedule& resolved, bool f64, int runs) {
+  if (resolved.prefetch == PREFETCH_TILES) return runs == 1;
+  return resolved.prefetch < 0 ? !f64 : resolved.prefetch != 0;
 }
 
 // The schedule of the rhs alone: whole blocks, statically mapped.

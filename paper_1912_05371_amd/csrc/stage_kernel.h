@@ -5,6 +5,7 @@
 #include <algorithm>
 
 #include "resolve.h"
+#include "schedule.h"
 #include "stage.h"
 #include "wacm_internal.h"
 
@@ -457,58 +458,58 @@ static hipError_t stage_launch_z(const StageArgs<T>& a, int64_t slots, hipStream
   return hipGetLastError();
 }
 
-template <typename T, int BS, int TY, int MODE, bool PEN, bool PREF>
+// EARLY, RUNS: epilogue operands loaded before the plane's barrier, in whole
+// columns and in runs of planes.  The rhs and the first stage have none: one
+// kernel for both.
+template <typename T, int BS, int TY, int MODE, bool PEN, bool EARLY, bool RUNS>
 static hipError_t stage_launch_t(const StageArgs<T>& a, int wg_per_cu, hipStream_t st) {
+  constexpr bool E = EARLY && MODE % 10 >= 2, R = RUNS && MODE % 10 >= 2;
   static const int resident =
-      resident_per_cu(stage_kernel<T, BS, TY, MODE, PEN, PREF, 1>, BS * TY);
+      resident_per_cu(stage_kernel<T, BS, TY, MODE, PEN, E, 1>, BS * TY);
   const int64_t slots = (int64_t)(wg_per_cu > 0 ? wg_per_cu : resident) * num_cus();
   // the lists of blocks with and without penalization are counted on the
-  // device only; the split is for large grids.  The runs of planes have one
-  // kernel for both prefetch choices (the type's default): a matter of few
-  // workgroups per CU, where the choice makes no difference.
+  // device only; the split is for large grids
   const int nz = a.blist ? 1 : plane_runs(a.nb * (BS / TY), slots, BS);
-  if (nz == 4) return stage_launch_z<T, BS, TY, MODE, PEN, sizeof(T) == 4, 4>(a, slots, st);
-  if (nz == 2) return stage_launch_z<T, BS, TY, MODE, PEN, sizeof(T) == 4, 2>(a, slots, st);
-  return stage_launch_z<T, BS, TY, MODE, PEN, PREF, 1>(a, slots, st);
+  if (nz == 4) return stage_launch_z<T, BS, TY, MODE, PEN, R, 4>(a, slots, st);
+  if (nz == 2) return stage_launch_z<T, BS, TY, MODE, PEN, R, 2>(a, slots, st);
+  return stage_launch_z<T, BS, TY, MODE, PEN, E, 1>(a, slots, st);
+}
+
+template <typename T, int BS, int TY, int MODE, bool PEN>
+static hipError_t stage_launch_e(const StageArgs<T>& a, const wacm_schedule& s, hipStream_t st) {
+  constexpr bool f64 = sizeof(T) == 8;
+  const int w = s.wg_per_cu;
+  if (!early_loads(s, f64, 1)) return stage_launch_t<T, BS, TY, MODE, PEN, false, false>(a, w, st);
+  if constexpr (f64 && TY == 8)  // early_loads tells whole columns from runs for its FP64 tiles
+    if (!early_loads(s, f64, 2)) return stage_launch_t<T, BS, TY, MODE, PEN, true, false>(a, w, st);
+  return stage_launch_t<T, BS, TY, MODE, PEN, true, true>(a, w, st);
 }
 
 // tile_rows 0: whole-block work items; 8: tiles of 8 rows (bs >= 24, where the
 // halo of a tile plane fits in one point per thread; smaller blocks use whole
 // blocks)
-template <typename T, int BS, int MODE, bool PEN, bool PREF>
-static hipError_t stage_launch_pp(const StageArgs<T>& a, const wacm_schedule& s,
-                                  hipStream_t st) {
+template <typename T, int BS, int MODE, bool PEN>
+static hipError_t stage_launch_p(const StageArgs<T>& a, const wacm_schedule& s, hipStream_t st) {
   if constexpr (BS >= 24) {
-    if (s.tile_rows == 8) return stage_launch_t<T, BS, 8, MODE, PEN, PREF>(a, s.wg_per_cu, st);
+    if (s.tile_rows == 8) return stage_launch_e<T, BS, 8, MODE, PEN>(a, s, st);
   }
-  return stage_launch_t<T, BS, BS, MODE, PEN, PREF>(a, s.wg_per_cu, st);
+  return stage_launch_e<T, BS, BS, MODE, PEN>(a, s, st);
 }
 
-// Schedule knobs: prefetch = 1 issues the epilogue loads before the plane's
-// barrier (more bytes in flight, more registers), 0 after the rhs; -1 picks
-// the default (early for FP32, late for FP64, whose 9-wave workgroup is at
-// its VGPR limit).
 template <typename T, int BS, int MODE>
 static hipError_t stage_launch(const StageArgs<T>& a, const wacm_schedule& s, hipStream_t st) {
   const bool pen = a.p.mask || a.p.sponge || a.dus;
-  const bool pref = s.prefetch < 0 ? sizeof(T) == 4 : s.prefetch != 0;
   if (pen && a.blist) {
     // the blocks where the penalization vanishes take the unpenalized
     // variant, the others the penalized one
     StageArgs<T> f = a, n = a;
     f.bsel = 0;
     n.bsel = 1;
-    hipError_t e = pref ? stage_launch_pp<T, BS, MODE, false, true>(f, s, st)
-                        : stage_launch_pp<T, BS, MODE, false, false>(f, s, st);
-    if (e != hipSuccess) return e;
-    return pref ? stage_launch_pp<T, BS, MODE, true, true>(n, s, st)
-                : stage_launch_pp<T, BS, MODE, true, false>(n, s, st);
+    hipError_t e = stage_launch_p<T, BS, MODE, false>(f, s, st);
+    return e != hipSuccess ? e : stage_launch_p<T, BS, MODE, true>(n, s, st);
   }
-  if (pen)
-    return pref ? stage_launch_pp<T, BS, MODE, true, true>(a, s, st)
-                : stage_launch_pp<T, BS, MODE, true, false>(a, s, st);
-  return pref ? stage_launch_pp<T, BS, MODE, false, true>(a, s, st)
-              : stage_launch_pp<T, BS, MODE, false, false>(a, s, st);
+  return pen ? stage_launch_p<T, BS, MODE, true>(a, s, st)
+             : stage_launch_p<T, BS, MODE, false>(a, s, st);
 }
 
 template <typename T, int MODE>
@@ -528,12 +529,11 @@ static hipError_t stage_dispatch(int bs, const StageArgs<T>& a, const wacm_sched
 
 template <typename T, int BS, int S>
 static hipError_t stage_owng_bs(const StageArgs<T>& a, int wg_per_cu, hipStream_t st) {
-  constexpr bool PREF = sizeof(T) == 4;
+  constexpr bool early = sizeof(T) == 4;
   return a.p.mask || a.p.sponge || a.dus
-             ? stage_launch_t<T, BS, 8, 10 + S, true, PREF>(a, wg_per_cu, st)
-             : stage_launch_t<T, BS, 8, 10 + S, false, PREF>(a, wg_per_cu, st);
+             ? stage_launch_t<T, BS, 8, 10 + S, true, early, early>(a, wg_per_cu, st)
+             : stage_launch_t<T, BS, 8, 10 + S, false, early, early>(a, wg_per_cu, st);
 }
-
 
 template <typename T, int BS>
 static hipError_t stage_owng_mode(int s, const StageArgs<T>& a, int w, hipStream_t st) {

@@ -3,7 +3,8 @@
 //   f64(0/1) bs nb counters(0/1) n, then n times: knob value
 // sets the knobs one call each on a new grid, the way the Python binding does
 // (read the schedule, change the knob, write it back), and prints the schedule
-// read at the end, then the RK stages' and the rhs's resolved ones.
+// read at the end, then the RK stages' and the rhs's resolved ones, and whether
+// the RK stages load their operands early with 1, 2 and 4 runs of planes.
 #include <cstdio>
 #include <cstring>
 
@@ -43,6 +44,10 @@ int main() {
     show(s);
     show(wacm::stage_schedule(g.sched, f64 != 0, bs, nb, counters != 0));
     show(wacm::rhs_schedule(g.sched));
+    for (int runs = 1; runs <= 4; runs *= 2)
+      printf("%d ", (int)wacm::early_loads(
+                        wacm::stage_schedule(g.sched, f64 != 0, bs, nb, counters != 0),
+                        f64 != 0, runs));
     printf("\n");
   }
   return 0;

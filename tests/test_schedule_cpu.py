@@ -26,15 +26,17 @@ def harness():
     return BIN
 
 
-def run(harness, cases):
+def run(harness, cases, early=False):
     """Per case (f64, bs, nb, counters, [(knob, value), ...]): the schedule read
-    at the end, the RK stages' and the rhs's."""
+    at the end, the RK stages' and the rhs's; with early, for 1, 2 and 4 runs of
+    planes, whether the RK stages load their operands early."""
     text = "".join(f"{f} {bs} {nb} {c} {len(k)} " + " ".join(f"{a} {b}" for a, b in k) + "\n"
                    for f, bs, nb, c, k in cases)
     r = subprocess.run([harness], input=text, capture_output=True, text=True)
     assert r.returncode == 0, (r.returncode, r.stderr)
     rows = [[int(v) for v in line.split()] for line in r.stdout.splitlines()]
-    return [tuple(dict(zip(KNOBS, v[i:i + 6])) for i in (0, 6, 12)) for v in rows]
+    return [tuple(dict(zip(KNOBS, v[i:i + 6])) for i in (0, 6, 12)) for v in rows] if not early \
+        else [v[18:21] for v in rows]
 
 
 @pytest.mark.parametrize("knobs", [[("none", 0)], [("pen_split", 0)], [("wg_per_cu", 2)],
@@ -73,3 +75,17 @@ def test_a_knob_that_is_set_is_taken_as_it_is(harness, knob, value):
             # (the early loads go with tiles that the library chose)
             skip = (knob, "prefetch") if knob == "tile_rows" else (knob,)
             assert all(g[k] == f[k] for k in KNOBS if k not in skip), size
+
+
+@pytest.mark.parametrize("tiles", [-1, 0, 8])
+def test_early_loads_as_set_with_any_number_of_runs(harness, tiles):
+    for value in (0, 1):
+        knobs = [("tile_rows", tiles), ("prefetch", value)]
+        for size, got in zip(SIZES, run(harness, [(*s, 1, knobs) for s in SIZES], early=True)):
+            assert got == [value] * 3, (size, value)
+    # left to the library: FP32, and FP64 tiles in whole columns where the tiles
+    # are its own too
+    for (f64, bs, nb), got in zip(SIZES, run(harness, [(*s, 1, [("tile_rows", tiles)])
+                                                       for s in SIZES], early=True)):
+        own = f64 and bs >= 24 and tiles < 0
+        assert got == ([int(own), 0, 0] if f64 else [1, 1, 1]), (f64, bs, nb)
