@@ -85,8 +85,9 @@ __device__ __forceinline__ double box_factor(double b, double lo, double hi, dou
 
 template <int BS>
 __device__ __forceinline__ void plate_tab_fill(const wacm_params& p, const MaskTime& mt,
-                                               const int32_t* meta, double h, PlateTab<BS>& t) {
-  for (int q = threadIdx.x; q < BS * BS; q += blockDim.x) {
+                                               const int32_t* meta, double h, PlateTab<BS>& t,
+                                               int z0 = 0, int nz = BS) {
+  for (int q = z0 * BS + threadIdx.x; q < (z0 + nz) * BS; q += blockDim.x) {  // nz planes
     const int x = q % BS, z = q / BS;
     const double rx = (double)(meta[2] * BS + x) * h - p.x_le[0];
     const double rz = (double)(meta[4] * BS + z) * h - p.x_le[2];

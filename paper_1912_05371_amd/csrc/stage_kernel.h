@@ -247,7 +247,7 @@ void stage_kernel(StageArgs<T> a) {
       masked = (reach & 1) != 0;
       sponged = (reach & 2) != 0;
       if (masked && a.p.mask == WACM_MASK_PLATE) {
-        plate_tab_fill<BS>(a.p, mt, meta, hdd, ptab);
+        plate_tab_fill<BS>(a.p, mt, meta, hdd, ptab, z0, ZR);
         lds_barrier();
       }
       pen_at(z0);
@@ -424,26 +424,6 @@ static int resident_per_cu(K kernel, int threads) {
   return n;
 }
 
-// Runs of planes per tile.  A workgroup marches through its planes one memory
-// latency apart, whatever the grid, so with fewer tiles than resident
-// workgroups (or a last round that is nearly empty) the tiles are cut along z:
-// the number of rounds times the planes of a run, plus about 2 planes for its
-// first loads, is what a stage takes.  64 blocks of 16^3 FP64: 27 -> 13 us per
-// stage with 4 runs; 736 blocks with mask and sponge: 140 -> 120 us with 2.
-// Large grids keep whole tiles (each run reads 6 planes of its neighbours).
-static int plane_runs(int64_t tiles, int64_t slots, int bs) {
-  int best = 1;
-  int64_t cost = INT64_MAX;
-  for (int n = 1; n <= 4; n *= 2) {
-    const int64_t c = (tiles * n + slots - 1) / slots * (bs / n + 2);
-    if (c < cost) {
-      cost = c;
-      best = n;
-    }
-  }
-  return best;
-}
-
 template <typename T, int BS, int TY, int MODE, bool PEN, bool PREF, int NZ>
 static hipError_t stage_launch_z(const StageArgs<T>& a, int64_t slots, hipStream_t st) {
   const int64_t items = a.nb * (BS / TY) * NZ;
@@ -466,10 +446,11 @@ static hipError_t stage_launch_t(const StageArgs<T>& a, int wg_per_cu, hipStream
   constexpr bool E = EARLY && MODE % 10 >= 2, R = RUNS && MODE % 10 >= 2;
   static const int resident =
       resident_per_cu(stage_kernel<T, BS, TY, MODE, PEN, E, 1>, BS * TY);
-  const int64_t slots = (int64_t)(wg_per_cu > 0 ? wg_per_cu : resident) * num_cus();
+  const int cus = num_cus(), per_cu = wg_per_cu > 0 ? wg_per_cu : resident;
+  const int64_t slots = (int64_t)per_cu * cus;
   // the lists of blocks with and without penalization are counted on the
   // device only; the split is for large grids
-  const int nz = a.blist ? 1 : plane_runs(a.nb * (BS / TY), slots, BS);
+  const int nz = a.blist ? 1 : plane_runs(a.nb * (BS / TY), per_cu, cus, BS, PEN);
   if (nz == 4) return stage_launch_z<T, BS, TY, MODE, PEN, R, 4>(a, slots, st);
   if (nz == 2) return stage_launch_z<T, BS, TY, MODE, PEN, R, 2>(a, slots, st);
   return stage_launch_z<T, BS, TY, MODE, PEN, E, 1>(a, slots, st);
