@@ -58,30 +58,22 @@ inline bool early_loads(const wacm_schedule& resolved, bool f64, int runs) {
 // latency apart, so a grid of few tiles ends sooner cut along z: 64 blocks of
 // 16^3, FP64, 27 -> 11 us per stage with 4 runs.  Large grids keep whole
 // columns: each run reads 6 planes of its neighbours.
-//   Without penalization, in units of a plane's latency: the workgroups that a
-// compute unit holds together take p + 1 for p planes, or 0.6 (p + 3) each
-// where their traffic bounds them; the fullest unit's rounds add up, and a cut
-// has to gain 3%.  Over 284 grids of 60 to 3400 blocks (16^3 to 32^3, both
-// types, rhs and RK steps) it takes 0.8% more than the best of 1, 2 and 4, and
-// in 5 of them 2 to 5% more than whole columns; counting rounds of the whole
-// chip alone, 1.1%, and 20 grids 2 to 11% more (498 blocks of 16^3, rhs, FP32:
-// 32.2 us whole, 36.0 in 2 runs).
-//   With penalization the kernel for runs holds fewer registers (FP64 tiles of
-// 32^3 with a mask: half the time), so rounds of the chip alone decide.
-inline int plane_runs(int64_t tiles, int per_cu, int cus, int bs, bool pen) {
+//   In units of a plane's latency, q workgroups that a compute unit holds
+// together take p + 3 for p planes each, or 0.65 q times that where their
+// traffic bounds them; the fullest unit's rounds add up.  Over 1364 measurements
+// (60 to 3400 blocks of 16^3 to 32^3, both types, rhs and RK steps, without and
+// with a mask) that takes 1.5% more than the best of 1, 2 and 4, and 12 of them
+// are more than 1.5% (at most 6.5%) slower than whole columns; counting rounds
+// of the whole chip alone: 1.8%, and 96 of them, up to 16% (498 blocks of 16^3,
+// rhs, FP32: 32.2 us whole, 36.0 in 2 runs).
+inline int plane_runs(int64_t tiles, int per_cu, int cus, int bs) {
   auto cost = [&](int n) {
-    const int64_t items = tiles * n;
-    const double p = (double)bs / n;
-    if (pen) return (double)((items + (int64_t)per_cu * cus - 1) / ((int64_t)per_cu * cus)) * (p + 2);
-    auto round = [&](int64_t q) {
-      const double traffic = 0.6 * (double)q * (p + 3);
-      return q == 0 ? 0.0 : traffic > p + 1 ? traffic : p + 1;
-    };
-    const int64_t k = (items + cus - 1) / cus;
-    return (double)(k / per_cu) * round(per_cu) + round(k % per_cu);
+    auto round = [](int64_t q) { return q * 0.65 > 1.0 ? q * 0.65 : q > 0 ? 1.0 : 0.0; };
+    const int64_t k = (tiles * n + cus - 1) / cus;
+    return ((double)bs / n + 3.0) * ((double)(k / per_cu) * round(per_cu) + round(k % per_cu));
   };
   int best = 1;
-  double c = (pen ? 1.0 : 0.97) * cost(1);
+  double c = cost(1);
   for (int n = 2; n <= 4; n *= 2)
     if (const double d = cost(n); d < c) {
       c = d;

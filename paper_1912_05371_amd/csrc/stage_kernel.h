@@ -200,8 +200,9 @@ void stage_kernel(StageArgs<T> a) {
     double m2 = 0.0;  // stage 4: max |u|^2 of this thread's new points
     // mask, solid velocity and sponge of this thread's point of the next
     // plane, evaluated at the end of the previous plane where fewer values
-    // are live
-    T pchi = T(0), psp = T(0), pus[3] = {T(0), T(0), T(0)};
+    // are live (the extra solid velocity loaded with the rhs's terms instead:
+    // 134 registers spilled instead of 49, FP64 16^3)
+    T pchi = T(0), psp = T(0), pus[3] = {T(0), T(0), T(0)}, pdu[3];
     int reach = 0;  // whether the mask (1) and the sponge (2) reach this block
     bool masked = false, sponged = false;
     auto pen_at = [&](int zz) {
@@ -216,6 +217,12 @@ void stage_kernel(StageArgs<T> a) {
           pus[2] = opaque(T(-mt.ad * (xg - a.p.x_le[0])));
         } else if (masked) {
           pchi = T(sphere_chi(a.p, xg, yg, zg));
+        }
+        if (masked && a.dus) {
+          const T* du = a.dus + (int64_t)slot * 3 * BS * BS * BS + (zz * BS + y) * BS + x;
+          pdu[0] = du[0];
+          pdu[1] = du[BS * BS * BS];
+          pdu[2] = du[2 * BS * BS * BS];
         }
       }
       if (sponged) psp = T(sponge_eval(a.p, a.L, xg, yg, zg));
@@ -317,10 +324,8 @@ void stage_kernel(StageArgs<T> a) {
         const wacm_params& p = a.p;
         T chi = pchi, sp = psp, us[3] = {pus[0], pus[1], pus[2]};
         if (masked && a.dus) {
-          const T* du = a.dus + (int64_t)slot * 3 * BS * BS * BS + (z * BS + y) * BS + x;
-          us[0] += du[0];
-          us[1] += du[BS * BS * BS];
-          us[2] += du[2 * BS * BS * BS];
+#pragma unroll
+          for (int d = 0; d < 3; ++d) us[d] += pdu[d];
         }
         const T iceta = masked ? T(1.0 / p.c_eta) : T(0), icsp = sponged ? T(1.0 / p.c_sp) : T(0);
         const T val[4] = {u, v, w, pr};
@@ -450,7 +455,7 @@ static hipError_t stage_launch_t(const StageArgs<T>& a, int wg_per_cu, hipStream
   const int64_t slots = (int64_t)per_cu * cus;
   // the lists of blocks with and without penalization are counted on the
   // device only; the split is for large grids
-  const int nz = a.blist ? 1 : plane_runs(a.nb * (BS / TY), per_cu, cus, BS, PEN);
+  const int nz = a.blist ? 1 : plane_runs(a.nb * (BS / TY), per_cu, cus, BS);
   if (nz == 4) return stage_launch_z<T, BS, TY, MODE, PEN, R, 4>(a, slots, st);
   if (nz == 2) return stage_launch_z<T, BS, TY, MODE, PEN, R, 2>(a, slots, st);
   return stage_launch_z<T, BS, TY, MODE, PEN, E, 1>(a, slots, st);

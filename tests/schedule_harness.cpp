@@ -5,7 +5,7 @@
 // (read the schedule, change the knob, write it back), and prints the schedule
 // read at the end, then the RK stages' and the rhs's resolved ones, and whether
 // the RK stages load their operands early with 1, 2 and 4 runs of planes.
-//   schedule_harness runs: lines "tiles per_cu cus bs pen", prints plane_runs
+//   schedule_harness runs: lines "tiles per_cu cus bs", prints plane_runs
 #include <cstdio>
 #include <cstring>
 
@@ -29,9 +29,9 @@ static void show(const wacm_schedule& s) {
 int main(int argc, char**) {
   if (argc > 1) {
     long tiles;
-    int per_cu, cus, bs, pen;
-    while (scanf("%ld %d %d %d %d", &tiles, &per_cu, &cus, &bs, &pen) == 5)
-      printf("%d\n", wacm::plane_runs(tiles, per_cu, cus, bs, pen != 0));
+    int per_cu, cus, bs;
+    while (scanf("%ld %d %d %d", &tiles, &per_cu, &cus, &bs) == 4)
+      printf("%d\n", wacm::plane_runs(tiles, per_cu, cus, bs));
     return 0;
   }
   int f64, bs, counters, n;

@@ -91,19 +91,17 @@ def test_early_loads_as_set_with_any_number_of_runs(harness, tiles):
         assert got == ([int(own), 0, 0] if f64 else [1, 1, 1]), (f64, bs, nb)
 
 
-# (tiles, resident workgroups per compute unit, bs, with penalization) on 256
-# compute units, and the runs of planes that were fastest, or within 1.5% of it
-@pytest.mark.parametrize("tiles,per_cu,bs,pen,runs", [
-    (64, 2, 16, 0, (4,)), (71, 4, 16, 0, (4,)), (71, 1, 24, 0, (2,)), (71, 1, 32, 0, (2,)),
-    (372, 4, 16, 0, (2, 4)), (295, 1, 24, 0, (2, 4)), (295, 1, 32, 0, (2, 4)),
+# (tiles, resident workgroups per compute unit, bs) on 256 compute units, and the
+# runs of planes that were fastest, or within 3% of it
+@pytest.mark.parametrize("tiles,per_cu,bs,runs", [
+    (64, 2, 16, (4,)), (71, 4, 16, (4,)), (71, 1, 24, (2,)), (71, 1, 32, (2,)),
+    (372, 4, 16, (2, 4)), (295, 1, 24, (2, 4)), (295, 1, 32, (2, 4)), (736, 2, 16, (2,)),
     # whole columns: 2 runs took 1.08, 1.11, 1.09, 1.07, 1.05, 1.05 and 1.11 times as long
-    (442, 4, 16, 0, (1, 4)), (498, 4, 16, 0, (1, 4)), (589, 4, 16, 0, (1, 4)), (1723, 2, 16, 0, (1,)),
-    (2612, 3, 16, 0, (1,)), (2166, 2, 24, 0, (1,)), (2712, 2, 24, 0, (1,)),
-    (20028, 2, 24, 0, (1,)), (60084, 2, 24, 0, (1,)),
-    # the penalized kernel is faster in runs
-    (736, 2, 16, 1, (2,)), (759, 2, 24, 1, (2,)), (1656, 2, 32, 1, (2,)), (3672, 2, 32, 1, (2,)),
+    (442, 4, 16, (1, 4)), (498, 4, 16, (1, 4)), (589, 4, 16, (1, 4)), (1723, 2, 16, (1,)),
+    (2612, 3, 16, (1,)), (2166, 2, 24, (1,)), (2712, 2, 24, (1,)),
+    (20028, 2, 24, (1,)), (60084, 2, 24, (1,)),
 ])
-def test_runs_of_planes(harness, tiles, per_cu, bs, pen, runs):
-    r = subprocess.run([harness, "runs"], input=f"{tiles} {per_cu} 256 {bs} {pen}\n",
+def test_runs_of_planes(harness, tiles, per_cu, bs, runs):
+    r = subprocess.run([harness, "runs"], input=f"{tiles} {per_cu} 256 {bs}\n",
                        capture_output=True, text=True)
     assert int(r.stdout) in runs
