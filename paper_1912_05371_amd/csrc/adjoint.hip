@@ -362,10 +362,12 @@ __global__ __launch_bounds__(NT_GEN) void rhs_adj_kernel(AdjArgs<T> a) {
 }
 
 // Gradient of weight * F_x (the x-force, Sec. 2.2 midpoint rule) at time t.
-template <typename T, int bs>
+// PLATE: the factor tables are the plate's; a sphere's kernel does without their
+// LDS (904 blocks of 32^3, FP64: 516 us with it, 440 without).
+template <typename T, int bs, bool PLATE>
 __global__ __launch_bounds__(NT_GEN) void force_adj_kernel(AdjArgs<T> a) {
   __shared__ double red[3][NT_GEN];
-  __shared__ PlateAdjTab<bs> ptab;
+  __shared__ typename std::conditional<PLATE, PlateAdjTab<bs>, NoTab>::type ptab;
   const int ng = a.L.ng, P = a.L.P;
   constexpr int n3 = bs * bs * bs;
   const wacm_params& p = a.p;
@@ -378,10 +380,11 @@ __global__ __launch_bounds__(NT_GEN) void force_adj_kernel(AdjArgs<T> a) {
     const int64_t base = (int64_t)slot * a.L.bstride;
     double th[3] = {0, 0, 0};
     const bool masked = (pen_reach(p, a.Ldom, bs, m, pm.ca, pm.sa) & 1) != 0;
-    const bool plate = masked && p.mask == WACM_MASK_PLATE;
-    if (plate) {  // uniform; the last block's reduction has ended
-      plate_adj_tab_fill<bs>(p, pm, m, h, 0, bs, ptab);
-      __syncthreads();
+    if constexpr (PLATE) {
+      if (masked) {  // uniform; the last block's reduction has ended
+        plate_adj_tab_fill<bs>(p, pm, m, h, 0, bs, ptab);
+        __syncthreads();
+      }
     }
     for (int qi = threadIdx.x; qi < n3; qi += NT_GEN) {
       const int i = qi % bs, j = (qi / bs) % bs, k = qi / (bs * bs);
@@ -391,18 +394,19 @@ __global__ __launch_bounds__(NT_GEN) void force_adj_kernel(AdjArgs<T> a) {
         for (int k2 = 0; k2 < 3; ++k2) th[k2] += 0.0 * (double)a.U[o];
         continue;
       }
+      const T u0 = a.U[o], b0 = a.Ub[o];  // in flight while the mask is evaluated
       const double xg = (double)(m[2] * bs + i) * h, yg = (double)(m[3] * bs + j) * h,
                    zg = (double)(m[4] * bs + k) * h;
       double chi, dchi = 0.0, us[3] = {0, 0, 0}, dsd[3] = {0, 0, 0};
-      if (plate)
+      if constexpr (PLATE)
         plate_adj_tab_point<bs>(p, pm, ptab, i, j, k, xg, zg, chi, dchi, us, dsd);
       else
-        chi = sphere_chi(p, xg, yg, zg);
+        chi = sphere_chi<false>(p, xg, yg, zg);
       const double cw = a.weight * chi * vol / p.c_eta;
-      a.Ub[o] += T(cw);
+      a.Ub[o] = b0 + T(cw);
       if (a.dusbar) a.dusbar[((int64_t)slot * 3) * n3 + qi] -= cw;
       const double e = a.dus ? (double)a.dus[((int64_t)slot * 3) * n3 + qi] : 0.0;
-      const double gal = a.weight * dchi * ((double)a.U[o] - us[0] - e) * vol / p.c_eta;
+      const double gal = a.weight * dchi * ((double)u0 - us[0] - e) * vol / p.c_eta;
       const double gad = -cw * dsd[0];
       for (int k2 = 0; k2 < 3; ++k2) th[k2] += gal * pm.dal[k2] + gad * pm.dad[k2];
     }
@@ -1087,6 +1091,14 @@ hipError_t launch_rhs_adj(const wacm_grid* g, const wacm_params* p, double t, co
                          (const float*)dus, st);
 }
 
+template <typename T, int BS>
+static void force_adj_launch(const wacm_grid* g, const AdjArgs<T>& a, hipStream_t st) {
+  if (a.p.mask == WACM_MASK_PLATE)
+    force_adj_kernel<T, BS, true><<<grid_n(g->nb), NT_GEN, 0, st>>>(a);
+  else
+    force_adj_kernel<T, BS, false><<<grid_n(g->nb), NT_GEN, 0, st>>>(a);
+}
+
 template <typename T>
 static hipError_t force_adj_t(const wacm_grid* g, const wacm_params* p, double t, double weight,
                               const T* U, T* Ub, double* dtheta, double* dusbar, const T* dus,
@@ -1096,13 +1108,13 @@ static hipError_t force_adj_t(const wacm_grid* g, const wacm_params* p, double t
   a.weight = weight;
   switch (g->d.bs) {
     case 16:
-      force_adj_kernel<T, 16><<<grid_n(g->nb), NT_GEN, 0, st>>>(a);
+      force_adj_launch<T, 16>(g, a, st);
       break;
     case 24:
-      force_adj_kernel<T, 24><<<grid_n(g->nb), NT_GEN, 0, st>>>(a);
+      force_adj_launch<T, 24>(g, a, st);
       break;
     case 32:
-      force_adj_kernel<T, 32><<<grid_n(g->nb), NT_GEN, 0, st>>>(a);
+      force_adj_launch<T, 32>(g, a, st);
       break;
     default:
       return hipErrorInvalidValue;

@@ -39,3 +39,8 @@ def test_penalized_rhs_of_small_blocks_does_not_spill(kernels):
     # of 904 blocks of 16^3 FP64 with a sphere took 180 and 184 us
     for n, k in pick(kernels, r"wacm::stage_kernel<double, 16, 16, 0, true, \w+, \d>").items():
         assert k[".vgpr_spill_count"] == 0, n
+
+
+def test_force_gradient_of_a_sphere_holds_no_factor_tables(kernels):
+    for n, k in pick(kernels, r"wacm::force_adj_kernel<\w+, \d+, false>").items():
+        assert k[".group_segment_fixed_size"] == 3 * 256 * 8, n  # its reduction
