@@ -478,53 +478,62 @@ __global__ void advance_time(double* t, const double* dt) {
 // diagnostics partials per block: [max|u|^2, max|u|, max|v|, max|w|, max|p|,
 // sum chi(u-us) x3 (times h^3/C_eta), sum |u|^2 (times h^3/2), number of
 // NaN or Inf values]; the maxima ignore NaN, the count sees it
+// MASK: that of the parameters (the plate's factors take LDS and the masks take
+// registers that the kernel without one would miss: 12034 blocks of 16^3, FP32,
+// 330 us with them for 273 us).
 constexpr int NDIAG = 10;
-template <typename T, int bs>
+template <typename T, int bs, int MASK>
 __global__ __launch_bounds__(NT_GEN) void diag_kernel(const Tab* __restrict__ tab, int64_t nb,
                                                       const T* __restrict__ U, Layout L,
                                                       const T* __restrict__ dus, double Ldom,
                                                       wacm_params p, double t,
                                                       double* __restrict__ part) {
   __shared__ double red[NDIAG][NT_GEN];
-  __shared__ PlateTab<bs> ptab;
+  constexpr bool PLATE = MASK == WACM_MASK_PLATE;
+  __shared__ typename std::conditional<PLATE, PlateTab<bs>, NoTab>::type ptab;
   constexpr int n3 = bs * bs * bs;
-  const MaskTime mt = mask_time(p, t);
+  const MaskTime mt = MASK ? mask_time(p, t) : MaskTime{1.0, 0.0, 0.0};
   for (int64_t ib = blockIdx.x; ib < nb; ib += gridDim.x) {
     const int32_t* m = tab[ib].meta;
     const int slot = m[0], J = m[1];
     const double h = Ldom / (double(int64_t(1) << J) * bs);
     const T* b = U + (int64_t)slot * L.bstride;
-    const bool masked = (pen_reach(p, Ldom, bs, m, mt.ca, mt.sa) & 1) != 0;
-    const bool plate = masked && p.mask == WACM_MASK_PLATE;
-    if (plate) {  // uniform; the last block's reduction has ended
-      plate_tab_fill<bs>(p, mt, m, h, ptab);
-      __syncthreads();
+    const bool masked = MASK && (pen_reach(p, Ldom, bs, m, mt.ca, mt.sa) & 1) != 0;
+    if constexpr (PLATE) {
+      if (masked) {  // uniform; the last block's reduction has ended
+        plate_tab_fill<bs>(p, mt, m, h, ptab);
+        __syncthreads();
+      }
     }
     double acc[NDIAG] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
     for (int q = threadIdx.x; q < n3; q += NT_GEN) {
       const int i = q % bs, j = (q / bs) % bs, k = q / (bs * bs);
       const int64_t o = ((int64_t)(k + L.ng) * L.P + (j + L.ng)) * L.P + (i + L.ng);
-      double u[4];
-      for (int c = 0; c < 4; ++c) u[c] = b[o + c * L.fstride];
+      T v[4];
+      for (int c = 0; c < 4; ++c) v[c] = b[o + c * L.fstride];
+      // the mask while the loads are in flight
+      double chi = 0.0, us[3] = {0.0, 0.0, 0.0};
+      if (masked) {
+        const double xg = (double)(m[2] * bs + i) * h, yg = (double)(m[3] * bs + j) * h,
+                     zg = (double)(m[4] * bs + k) * h;
+        if constexpr (PLATE) {
+          chi = plate_tab_chi<bs>(p, ptab, i, j, k);
+          us[0] = mt.ad * (zg - p.x_le[2]);
+          us[2] = -mt.ad * (xg - p.x_le[0]);
+        } else {
+          chi = sphere_chi<false>(p, xg, yg, zg);
+        }
+        if (dus)
+          for (int d = 0; d < 3; ++d) us[d] += (double)dus[((int64_t)slot * 3 + d) * n3 + q];
+      }
+      const double u[4] = {(double)v[0], (double)v[1], (double)v[2], (double)v[3]};
       for (int c = 0; c < 4; ++c) acc[9] += isfinite(u[c]) ? 0.0 : 1.0;
       const double m2 = u[0] * u[0] + u[1] * u[1] + u[2] * u[2];
       acc[0] = fmax(acc[0], m2);
       for (int c = 0; c < 4; ++c) acc[1 + c] = fmax(acc[1 + c], fabs(u[c]));
       if (masked) {
-        const double xg = (double)(m[2] * bs + i) * h, yg = (double)(m[3] * bs + j) * h,
-                     zg = (double)(m[4] * bs + k) * h;
-        double chi, us[3] = {0.0, 0.0, 0.0};
-        if (plate) {
-          chi = plate_tab_chi<bs>(p, ptab, i, j, k);
-          us[0] = mt.ad * (zg - p.x_le[2]);
-          us[2] = -mt.ad * (xg - p.x_le[0]);
-        } else {
-          chi = sphere_chi(p, xg, yg, zg);
-        }
-        if (dus)
-          for (int d = 0; d < 3; ++d) us[d] += (double)dus[((int64_t)slot * 3 + d) * n3 + q];
         for (int d = 0; d < 3; ++d) acc[5 + d] += chi * (u[d] - us[d]);
-      } else if (p.mask) {
+      } else if (MASK) {
         // chi is 0; 0 times a value that is not finite is not
         for (int d = 0; d < 3; ++d) acc[5 + d] += 0.0 * u[d];
       }
@@ -1650,24 +1659,34 @@ hipError_t launch_rk4(const wacm_grid* g, const wacm_params* p, double* t_dev, d
                                         dt_mode, nsteps, st);
 }
 
+template <typename T, int BS>
+static void diag_launch(const wacm_grid* g, const wacm_params* p, double t, const T* U,
+                        const T* dus, hipStream_t st) {
+  auto run = [&](auto kernel) {
+    kernel<<<grid_for(g->nb, 8), NT_GEN, 0, st>>>(g->d_tab, g->nb, U, pool_layout(g), dus, g->d.L,
+                                                  *p, t, g->d_part);
+  };
+  if (p->mask == WACM_MASK_PLATE)
+    run(diag_kernel<T, BS, WACM_MASK_PLATE>);
+  else if (p->mask)
+    run(diag_kernel<T, BS, WACM_MASK_SPHERE>);
+  else
+    run(diag_kernel<T, BS, WACM_MASK_NONE>);
+}
+
 template <typename T>
 static hipError_t diag_t(const wacm_grid* g, const wacm_params* p, double t, const T* U,
                          const T* dus, double* out, hipStream_t st) {
   if (g->nb == 0) return hipSuccess;
-  const unsigned grid = grid_for(g->nb, 8);
-  const Layout L = pool_layout(g);
   switch (g->d.bs) {
     case 16:
-      diag_kernel<T, 16><<<grid, NT_GEN, 0, st>>>(g->d_tab, g->nb, U, L, dus, g->d.L, *p, t,
-                                                   g->d_part);
+      diag_launch<T, 16>(g, p, t, U, dus, st);
       break;
     case 24:
-      diag_kernel<T, 24><<<grid, NT_GEN, 0, st>>>(g->d_tab, g->nb, U, L, dus, g->d.L, *p, t,
-                                                   g->d_part);
+      diag_launch<T, 24>(g, p, t, U, dus, st);
       break;
     case 32:
-      diag_kernel<T, 32><<<grid, NT_GEN, 0, st>>>(g->d_tab, g->nb, U, L, dus, g->d.L, *p, t,
-                                                   g->d_part);
+      diag_launch<T, 32>(g, p, t, U, dus, st);
       break;
     default:
       return hipErrorInvalidValue;

@@ -44,3 +44,9 @@ def test_penalized_rhs_of_small_blocks_does_not_spill(kernels):
 def test_force_gradient_of_a_sphere_holds_no_factor_tables(kernels):
     for n, k in pick(kernels, r"wacm::force_adj_kernel<\w+, \d+, false>").items():
         assert k[".group_segment_fixed_size"] == 3 * 256 * 8, n  # its reduction
+
+
+def test_diagnostics_without_a_mask_hold_nothing_for_one(kernels):
+    # with a mask's registers (129) and LDS three of four waves fit a SIMD
+    for n, k in pick(kernels, r"wacm::diag_kernel<\w+, \d+, 0>").items():
+        assert k[".vgpr_count"] <= 64 and k[".group_segment_fixed_size"] <= 20480, n
