@@ -129,25 +129,26 @@ __global__ __launch_bounds__(BS* BS) void stage2d_kernel(const Tab* __restrict__
       for (int c = 0; c < 3; ++c) tile[c][(j + 3) * W + (i + 3)] = v[c];
     }
     __syncthreads();
-    // in explicit multiply-adds, so that every stage and type rounds alike
-    T dx[3], dy[3], lap[2];  // the first derivatives still without 1/h
+    // in explicit multiply-adds, so that every stage and type rounds alike; the
+    // pressure first, then each velocity's terms as soon as it is read, so that the
+    // rhs alone of 32^2 FP64 keeps to 64 registers and two of its workgroups share
+    // a compute unit (1501 blocks: 22.3 us with 66)
+    const T u = own[0], v = own[1], pr = own[2];
+    T dx[3], dy[3], r[3];  // the first derivatives still without 1/h
 #pragma unroll
-    for (int c = 0; c < 3; ++c) {
+    for (int k = 0; k < 3; ++k) {
+      const int c = k == 0 ? 2 : k - 1;
       const T* s = tile[c];
       dx[c] = fma(a3, s[ct + 3] - s[ct - 3],
                   fma(a1, s[ct + 1] - s[ct - 1], a2 * (s[ct + 2] - s[ct - 2])));
       dy[c] = fma(a3, s[ct + 3 * W] - s[ct - 3 * W],
                   fma(a1, s[ct + W] - s[ct - W], a2 * (s[ct + 2 * W] - s[ct - 2 * W])));
-      if (c < 2)
-        lap[c] = lap1(s[ct - 2], s[ct - 1], s[ct], s[ct + 1], s[ct + 2]) +
-                 lap1(s[ct - 2 * W], s[ct - W], s[ct], s[ct + W], s[ct + 2 * W]);
-    }
-    const T u = own[0], v = own[1], pr = own[2];
-    T r[3];
-#pragma unroll
-    for (int c = 0; c < 2; ++c) {
-      const T conv = fma(u, dx[c] * ih, v * (dy[c] * ih));
-      r[c] = fma(lap[c] * ih2, nu, fma(c == 0 ? -dx[2] : -dy[2], ih, -conv));
+      if (c < 2) {
+        const T lap = lap1(s[ct - 2], s[ct - 1], s[ct], s[ct + 1], s[ct + 2]) +
+                      lap1(s[ct - 2 * W], s[ct - W], s[ct], s[ct + W], s[ct + 2 * W]);
+        const T conv = fma(u, dx[c] * ih, v * (dy[c] * ih));
+        r[c] = fma(lap * ih2, nu, fma(c == 0 ? -dx[2] : -dy[2], ih, -conv));
+      }
     }
     r[2] = fma(-c0sq, fma(dy[1], ih, dx[0] * ih), -cg * pr);
     T nv[3];

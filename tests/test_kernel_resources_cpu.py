@@ -50,3 +50,8 @@ def test_diagnostics_without_a_mask_hold_nothing_for_one(kernels):
     # with a mask's registers (129) and LDS three of four waves fit a SIMD
     for n, k in pick(kernels, r"wacm::diag_kernel<\w+, \d+, 0>").items():
         assert k[".vgpr_count"] <= 64 and k[".group_segment_fixed_size"] <= 20480, n
+
+
+def test_rhs_of_large_2d_blocks_leaves_room_for_two_workgroups(kernels):
+    for n, k in pick(kernels, r"wacm::d2::stage2d_kernel<\w+, 32, 0>").items():
+        assert k[".vgpr_count"] <= 64 and k[".vgpr_spill_count"] == 0, n
