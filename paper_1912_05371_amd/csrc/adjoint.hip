@@ -464,9 +464,8 @@ struct AdjStage {
   T vs;
   const T* lam;  // adjoint of the step's output (pool layout)
   Layout Lp;
-  const T* sin;  // running sum lam + B_4 + ..., in and out
-  Layout Lsi;
-  T* sout;
+  const T* sum;  // running sum B_4 + ... (compact)
+  T* sout;       // the sum, or at the last stage lam with the sum added
   Layout Lso;
   T* kn;  // next rhs adjoint = lamw lam + kw B (compact), null at the last stage
   Layout Lc;
@@ -494,11 +493,14 @@ __device__ __forceinline__ int64_t point_in(const Layout& L, int bs, int slot, i
 // LDS barrier per plane, the next plane's loads and the point's other operands
 // issued before it, without branches (a conditional load, or a product with
 // what was loaded, would wait there).  The pointwise mask and sponge terms are
-// adj_pen_kernel's.  NEXT: another stage follows (kn is written).  1632 blocks
-// of 16^3, FP32: 245 us; the rhs transpose in gather form from the padded pool,
-// the zeroing, the transposed ghost fill and three combinations that it stands
-// for took 2.7 ms.
-template <typename T, int BS, int TY, bool NEXT>
+// adj_pen_kernel's.  FIRST, LAST: position of the stage in the reverse sweep.
+// The sum is of the B_s alone, lam joins it at the last stage: with lam in it
+// from the start, FP32 rounded lam once per kernel and stage, and the gradient of
+// 5 steps was 1.05 times as far from its 64-bit value as with one rounding per
+// stage.  1632 blocks of 16^3, FP32: 245 us; the rhs transpose in gather form
+// from the padded pool, the zeroing, the transposed ghost fill and three
+// combinations that it stands for took 2.7 ms.
+template <typename T, int BS, int TY, bool FIRST, bool LAST>
 __global__ __launch_bounds__(BS* TY) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 2 : 3)))
 void adj_stage_kernel(AdjStage<T> a) {
   constexpr int H = 3, W = BS + 2 * H, WY = TY + 2 * H, NT = BS * TY, NTY = BS / TY;
@@ -533,7 +535,7 @@ void adj_stage_kernel(AdjStage<T> a) {
   }
   const int ufs = (int)a.Lu.fstride, vfs = (int)a.Lv.fstride;
   const int vzs = a.Lv.P * a.Lv.P, pzs = a.Lp.P * a.Lp.P;
-  const int sizs = a.Lsi.P * a.Lsi.P, sozs = a.Lso.P * a.Lso.P;
+  const int sozs = a.Lso.P * a.Lso.P;
   const int64_t nitems = a.nb * NTY;
   BlockIter it(nitems, 1);
   for (; it.ib < it.end; it.ib += it.step) {
@@ -570,7 +572,7 @@ void adj_stage_kernel(AdjStage<T> a) {
     const T* ub = a.u + (int64_t)slot * a.Lu.bstride;
     const T* vb = a.v + (int64_t)slot * a.Lv.bstride;
     const T* lb = a.lam + (int64_t)slot * a.Lp.bstride;
-    const T* sib = a.sin + (int64_t)slot * a.Lsi.bstride;
+    const T* sib = a.sum + (int64_t)slot * a.Lc.bstride;
     T* sob = a.sout + (int64_t)slot * a.Lso.bstride;
     T* kob = a.kn + (int64_t)slot * a.Lc.bstride;
     const int ucol = xin ? xsplit_offset(BS, x, y, 0)
@@ -579,7 +581,7 @@ void adj_stage_kernel(AdjStage<T> a) {
     const int pcol = (a.Lp.ng * a.Lp.P + (y + a.Lp.ng)) * a.Lp.P + (x + a.Lp.ng);
     const int ccol = y * BS + x;
     const int vcol = a.Lv.ng ? pcol : ccol;
-    const int sicol = a.Lsi.ng ? pcol : ccol, socol = a.Lso.ng ? pcol : ccol;
+    const int socol = LAST ? pcol : ccol;
     // values of this thread's column at depth d below (f = 4) or above (f = 5)
     auto zu = [&](int f, int d, int c) -> T {
       const FaceDesc<T>& fz = fu[f];
@@ -671,8 +673,8 @@ void adj_stage_kernel(AdjStage<T> a) {
       }
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
-        sv[c] = sib[sicol + z * sizs + c * (int)a.Lsi.fstride];
-        if (NEXT) lv[c] = lb[pcol + z * pzs + c * (int)a.Lp.fstride];
+        if (!FIRST) sv[c] = sib[ccol + z * BS * BS + c * B3];
+        lv[c] = lb[pcol + z * pzs + c * (int)a.Lp.fstride];
       }
       lds_barrier();
       const T v[4] = {q[0][3], q[1][3], q[2][3], q[3][3]};
@@ -712,8 +714,9 @@ void adj_stage_kernel(AdjStage<T> a) {
       bad += T(0) * (v[0] + v[1] + v[2]);
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
-        sob[socol + z * sozs + c * (int)a.Lso.fstride] = sv[c] + acc[c];
-        if (NEXT) kob[ccol + z * BS * BS + c * B3] = fma(a.kw, acc[c], a.lamw * lv[c]);
+        const T sum = FIRST ? acc[c] : sv[c] + acc[c];
+        sob[socol + z * sozs + c * (int)a.Lso.fstride] = LAST ? lv[c] + sum : sum;
+        if (!LAST) kob[ccol + z * BS * BS + c * B3] = fma(a.kw, acc[c], a.lamw * lv[c]);
       }
       if (z + 1 < BS) {
         T(*nb_)[W * WY] = slab[(z + 1) & 1];
@@ -1161,11 +1164,11 @@ static AdjWork<T> adj_work(const wacm_grid* g, void* work) {
 }
 
 // the stage itself, grid of as many workgroups as are resident
-template <typename T, int BS, int TY, bool NEXT>
+template <typename T, int BS, int TY, bool FIRST, bool LAST>
 static void adj_stage_main(const AdjStage<T>& a, hipStream_t st) {
   static const int resident = [] {
     int n = 0, dev = 0, cus = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, adj_stage_kernel<T, BS, TY, NEXT>,
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, adj_stage_kernel<T, BS, TY, FIRST, LAST>,
                                                      BS * TY, 0) != hipSuccess ||
         n < 1)
       n = 1;
@@ -1176,7 +1179,7 @@ static void adj_stage_main(const AdjStage<T>& a, hipStream_t st) {
     return n * cus;
   }();
   const int64_t items = a.nb * (BS / TY);
-  adj_stage_kernel<T, BS, TY, NEXT>
+  adj_stage_kernel<T, BS, TY, FIRST, LAST>
       <<<(unsigned)std::min<int64_t>(items, resident), BS * TY, 0, st>>>(a);
 }
 
@@ -1188,10 +1191,12 @@ static hipError_t adj_stage_launch(const wacm_grid* g, const AdjStage<T>& a, dou
   if (g->n_cface > 0)
     adj_face_kernel<T, BS><<<grid_n(g->n_cface), NT_GEN, 0, st>>>(g->d_tab, g->d_cface,
                                                                   g->n_cface, a, fb);
-  if (a.kn)
-    adj_stage_main<T, BS, TY, true>(a, st);
+  if (!a.kn)
+    adj_stage_main<T, BS, TY, false, true>(a, st);
+  else if (!a.sum)
+    adj_stage_main<T, BS, TY, true, false>(a, st);
   else
-    adj_stage_main<T, BS, TY, false>(a, st);
+    adj_stage_main<T, BS, TY, false, false>(a, st);
   if (a.p.mask || a.p.sponge) {
     const int64_t n = a.nb * (BS / ADJ_PZ);
     adj_pen_kernel<T, BS, BS / TY><<<grid_n(n, 8192), NT_GEN, 0, st>>>(a);
@@ -1255,8 +1260,7 @@ static hipError_t rk4_adj_t(const wacm_grid* g, const wacm_params* p, double t, 
     a.v = s == 3 ? lam : w.k[(s + 1) & 1];
     a.Lv = s == 3 ? L : Lc;
     a.vs = s == 3 ? T(lamw[3]) : T(1);
-    a.sin = s == 3 ? lam : w.sum;
-    a.Lsi = s == 3 ? L : Lc;
+    a.sum = s == 3 ? nullptr : w.sum;
     a.sout = s == 0 ? lam : w.sum;
     a.Lso = s == 0 ? L : Lc;
     a.kn = s == 0 ? nullptr : w.k[s & 1];

@@ -75,3 +75,27 @@ def test_viscous_rhs_rounds_like_the_plain_order(bs, prec, schedule):
            for v in (got, plain)]
     log(f"  rms error: kernel {rms[0]:.3e}, plain order {rms[1]:.3e}")
     assert rms[0] <= rms[1]
+
+
+def test_step_adjoint_keeps_what_four_stages_add_together():
+    """A sponge on every point takes 8e-8 of lambda = 1 per step, at most a third
+    of it in one stage: less than half of lambda's last place (2^-25), so a sum
+    that starts from lambda loses every stage's part.  Summed among themselves
+    the stages' parts reach lambda: an error of half a last place per kernel that
+    writes it (two), 2^-24 per step."""
+    steps, dt = 64, 1e-6
+    lev, ix, iy, iz = inputs.uniform_leaves(1)
+    codes = [wacm.treecode_encode(*q) for q in zip(lev, ix, iy, iz)]
+    g = wacm.Grid(16, 4, 1.0, 1, 1, codes, lev, wacm.F32)
+    prm = cases.params(nu=0.0, c0=1.0, c_gamma=0.0, sponge=1, l_sp=0.6, c_sp=dt / 8e-8,
+                       u_inf=(0.0, 0.0, 0.0), p_inf=0.0)
+    U, lam, work = g.pool(), g.pool(), g.adj_work()
+    lam.fill_(1.0)
+    th = torch.zeros(3, dtype=torch.float64, device="cuda")
+    for n in range(steps):
+        g.rk4_step_adj(prm, n * dt, dt, U, lam, th, None, None, work)
+    i = slice(4, 20)
+    got = lam[:8, :, i, i, i].double()
+    err = float((got - np.exp(-8e-8 * steps)).abs().max())
+    log(f"lambda after {steps} steps: error {err:.2e} of {8e-8 * steps:.2e}")
+    assert err <= steps * 2.0 ** -24
