@@ -18,23 +18,20 @@ namespace wacm {
 // --------------------------------------------------------------------------
 // ghost synchronisation
 // --------------------------------------------------------------------------
-// Point-wise ghost fill: mode 0 every ghost point of all ng layers, mode 1 the
-// depth-3 face star (the points the rhs stencils read).  With skip_coarser,
-// points of regions that lie in a coarser leaf are left to
-// sync_coarser_kernel.  With `box` (the lifted step's read boxes,
-// LIFT_BOX_WORDS per block; mode 0): only the points inside the boxes of
-// regions in a finer leaf (the lifted phase reads same-level ones from the
-// neighbours' interiors), and the face star of regions in a coarser leaf
-// unless those are skipped; the rest of the face star is read in place (same
-// level) or overwritten by the lifted phase (finer leaf).  A block without
-// such boxes visits its face star alone, or nothing.
+// Point-wise ghost fill of all ng layers.  With skip_coarser, points of regions
+// that lie in a coarser leaf are left to sync_coarser_kernel.  With `box` (the
+// lifted step's read boxes, LIFT_BOX_WORDS per block): only the points inside the
+// boxes of regions in a finer leaf; the lifted phase reads same-level values from
+// the neighbours' interiors, and what it reads in a coarser leaf is
+// sync_coarser_kernel's.
 template <typename T>
 __global__ __launch_bounds__(NT_GEN) void sync_kernel(const Tab* __restrict__ tab, int64_t nb,
                                                       T* __restrict__ U, Layout L, int bs,
-                                                      int mode, int skip_coarser,
+                                                      int skip_coarser,
                                                       const int32_t* __restrict__ box) {
   __shared__ Tab st;
   __shared__ int32_t sbox[LIFT_BOX_WORDS];
+  const int npts = L.P * L.P * L.P - bs * bs * bs;
   for (int64_t ib = blockIdx.x; ib < nb; ib += gridDim.x) {
     __syncthreads();
     load_tab(tab + ib, st);
@@ -43,35 +40,27 @@ __global__ __launch_bounds__(NT_GEN) void sync_kernel(const Tab* __restrict__ ta
     __syncthreads();
     T* dst = U + (int64_t)st.meta[0] * L.bstride;
     int32_t have = 0;  // boxes of regions in a finer leaf (uniform)
-    if (box)
+    if (box) {
       for (int r = 0; r < 27; ++r)
         if (r != 13 && st.kind[r] > 0) have |= sbox[13] & (int32_t(1) << r);
-    if (box && have == 0 && skip_coarser) continue;
-    const int md = box && have == 0 ? 1 : mode;
-    const int npts = md == 1 ? 18 * bs * bs : L.P * L.P * L.P - bs * bs * bs;
+      if (have == 0) continue;
+    }
     for (int p = threadIdx.x; p < npts; p += blockDim.x) {
       int i, j, k;
-      shell_point(p, bs, L.ng, L.P, md, i, j, k);
+      shell_point(p, bs, L.ng, L.P, 0, i, j, k);
       const int r = region_of(i, bs) + 3 * region_of(j, bs) + 9 * region_of(k, bs);
       if (skip_coarser && st.kind[r] < 0) continue;
       if (box) {
-        bool in = false;
-        if ((have >> r) & 1) {
-          const int32_t b = sbox[r];
-          const int q[3] = {i, j, k};
-          in = true;
+        if (!((have >> r) & 1)) continue;
+        const int32_t b = sbox[r];
+        const int q[3] = {i, j, k};
+        bool in = true;
 #pragma unroll
-          for (int d = 0; d < 3; ++d) {
-            const int o = q[d] - (q[d] < 0 ? -L.ng : (q[d] < bs ? 0 : bs));
-            in = in && o >= ((b >> (10 * d)) & 31) && o <= ((b >> (10 * d + 5)) & 31);
-          }
+        for (int d = 0; d < 3; ++d) {
+          const int o = q[d] - (q[d] < 0 ? -L.ng : (q[d] < bs ? 0 : bs));
+          in = in && o >= ((b >> (10 * d)) & 31) && o <= ((b >> (10 * d + 5)) & 31);
         }
-        if (!in) {
-          const int out = (i < 0 || i >= bs) + (j < 0 || j >= bs) + (k < 0 || k >= bs);
-          if (st.kind[r] >= 0 || out != 1 || i < -3 || i >= bs + 3 || j < -3 || j >= bs + 3 ||
-              k < -3 || k >= bs + 3)
-            continue;
-        }
+        if (!in) continue;
       }
       T v[4];
       ghost_value<T>(st, bs, L, U, i, j, k, v);
@@ -1277,7 +1266,7 @@ static hipError_t sync_t(const wacm_grid* g, T* U, hipStream_t st) {
   if (g->nb == 0) return hipSuccess;
   const bool split = g->d.ng <= SC_MAXG && g->n_cregion > 0;
   sync_kernel<T><<<grid_for(g->nb, 8), NT_GEN, 0, st>>>(g->d_tab, g->nb, U, pool_layout(g),
-                                                        g->d.bs, 0, split ? 1 : 0, nullptr);
+                                                        g->d.bs, split ? 1 : 0, nullptr);
   if (split) {
     switch (g->d.bs) {
       case 16:
@@ -1332,23 +1321,23 @@ static hipError_t sync_lifted_stage_t(const wacm_grid* g, T* U, const int32_t* b
                                       hipStream_t st) {
   if (g->nb == 0) return hipSuccess;
   if (g->d.ng > SC_MAXG || !box) return sync_t(g, U, st);
-  const bool split = g->n_cregion > 0;
+  // one level only: where a region lies in a finer leaf, that leaf sees the block
+  // as a coarser one
+  if (g->n_cregion == 0) return hipSuccess;
   sync_kernel<T><<<grid_for(g->nb, 8), NT_GEN, 0, st>>>(g->d_tab, g->nb, U, pool_layout(g),
-                                                        g->d.bs, 0, split ? 1 : 0, box);
-  if (split) {
-    switch (g->d.bs) {
-      case 16:
-        sync_coarser_launch<T, 16>(g, U, st);
-        break;
-      case 24:
-        sync_coarser_launch<T, 24>(g, U, st);
-        break;
-      case 32:
-        sync_coarser_launch<T, 32>(g, U, st);
-        break;
-      default:
-        return hipErrorInvalidValue;
-    }
+                                                        g->d.bs, 1, box);
+  switch (g->d.bs) {
+    case 16:
+      sync_coarser_launch<T, 16>(g, U, st);
+      break;
+    case 24:
+      sync_coarser_launch<T, 24>(g, U, st);
+      break;
+    case 32:
+      sync_coarser_launch<T, 32>(g, U, st);
+      break;
+    default:
+      return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
