@@ -21,6 +21,12 @@
  * - Asynchrony: calls that take a stream only enqueue work on it and return;
  *   errors raised by the device surface at the next synchronising call.
  *   Calls documented as "synchronous" wait for the stream.
+ * - Calls on one grid share the grid's workspace: the reductions' partial values
+ *   (the time step, WACM_DT_CFL steps, diagnostics, thresholding, the adjoint's
+ *   theta), the lists of blocks of a penalized step, CDF 4/4's staged ghost
+ *   values, schedule xcd_map 2's work counters.  Such calls must not overlap in
+ *   time; with CDF 4/0 ghost fills, right-hand sides and unpenalized
+ *   WACM_DT_FIXED steps with another work buffer each may.
  * - `stream` is a hipStream_t passed as void* (NULL = the default stream).
  * - Ownership: the library never allocates device memory.  The caller owns
  *   every device buffer: the state, the work registers and the workspaces

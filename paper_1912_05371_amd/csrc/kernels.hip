@@ -1574,6 +1574,7 @@ static hipError_t rk4_t(const wacm_grid* g, const wacm_params* p, double* t_dev,
   const int64_t face = large_grid(f64, g->d.bs, g->nb) ? spare_face(g) : -1;
   const wacm_schedule sched = stage_schedule(g->sched, f64, g->d.bs, g->nb, face >= 0);
   if (sched.xcd_map == XCD_OWN_COUNTERS) {
+    // (not the grid's: fixed steps without penalization may overlap in time)
     a.queue = reinterpret_cast<int*>(hb + face * 12 * g->d.bs * g->d.bs);
     a.xcd_map = 2;
   }
