@@ -56,7 +56,7 @@ inline bool early_loads(const wacm_schedule& resolved, bool f64, int runs) {
 // Runs of planes per tile (1, 2 or 4), for `per_cu` resident workgroups on each
 // of `cus` compute units.  A workgroup marches through its planes one memory
 // latency apart, so a grid of few tiles ends sooner cut along z: 64 blocks of
-// 16^3, FP64, 27 -> 11 us per stage with 4 runs.  Large grids keep whole
+// 16^3, FP64, 27 -> 13 us per stage with 4 runs.  Large grids keep whole
 // columns: each run reads 6 planes of its neighbours.
 //   In units of a plane's latency, q workgroups that a compute unit holds
 // together take p + 3 for p planes each, or 0.65 q times that where their
